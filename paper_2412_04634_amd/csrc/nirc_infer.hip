@@ -1,6 +1,7 @@
 // Inference-side kernels: weight packing, input encoding, direction sampling, training-sample
 // generation, per-query cache inference and the fused two-level estimator.
 #include "nirc_hash.hpp"
+#include "nirc_split.hpp"
 
 namespace nirc {
 
@@ -219,49 +220,102 @@ hipError_t launch_train_batch_multi(const TrainDesc *desc, uint32_t step, int64_
 
 // ------------------------------------------------------------------------------------------
 // Per-query cache inference (every query encodes its own surface features): a wave takes 16
-// queries at a time; the first layer runs over all 160 features.
-template <int W, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void k_infer_f32(Points pts, Queries q,
-                                                          const float *__restrict__ packed,
-                                                          float *__restrict__ rgb, int sig) {
+// queries at a time through the FP32 chain; the first layer runs over all 160 features.  sD: the
+// direction, hidden and output sections (LDS, or NULL: read from global memory inside each pass).
+template <int W>
+__device__ __forceinline__ void infer_tile_f32(const Points &pts, const Queries &q, const float *packed,
+                                               const float *sD, float *rgb, int sig, int64_t tile, int lane, int g,
+                                               int col) {
     constexpr F32Layout L{W};
     constexpr int MT = W / 16;
-    constexpr bool kLds = lds_weights(W);
-    constexpr int NW = kLds ? InferLds<W>::kWeights : 4;
-    __shared__ f32x4 smem4[NW / 4];
-    if constexpr (kLds) {
-        const f32x4 *src = (const f32x4 *)(packed + L.offset(SEC_D));
-        for (int i = threadIdx.x; i < NW / 4; i += WAVES * 64) smem4[i] = src[i];
-        __syncthreads();
-    }
-    const float *gS = packed + L.offset(SEC_S);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    if (!sD) sD = opaque(packed) + L.offset(SEC_D);
+    const float *sH = sD + L.size(SEC_D);
+    const float *sO = sH + 3 * L.size(SEC_H0);
     const int64_t Q = q.count;
-    const int64_t n_tiles = (Q + 15) >> 4;
-    for (int64_t tile = (int64_t)blockIdx.x * WAVES + wave; tile < n_tiles;
-         tile += (int64_t)gridDim.x * WAVES) {
-        const float *sD = kLds ? (const float *)smem4 : opaque(packed) + L.offset(SEC_D);
-        const float *sH = sD + L.size(SEC_D);
-        const float *sO = sH + 3 * L.size(SEC_H0);
-        const int64_t qi = min((tile << 4) + col, Q - 1);
-        const int64_t p = query_point(q, pts, qi);
-        const float xs[7] = {pts.px[p], pts.py[p], pts.pz[p], pts.nx[p], pts.ny[p], pts.nz[p], pts.rough[p]};
-        const float ws[3] = {q.wx[qi], q.wy[qi], q.wz[qi]};
-        f32x4 h[1][MT];
+    const int64_t qi = min((tile << 4) + col, Q - 1);
+    const int64_t p = query_point(q, pts, qi);
+    const float xs[7] = {pts.px[p], pts.py[p], pts.pz[p], pts.nx[p], pts.ny[p], pts.nz[p], pts.rough[p]};
+    f32x4 h[1][MT];
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) h[0][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        layer1_surface<W>(h[0], opaque(gS), xs, lane, g);
-        float dx[1] = {ws[0]}, dy[1] = {ws[1]}, dz[1] = {ws[2]};
-        layer1_direction<W, 1>(h, sD, dx, dy, dz, lane, g);
-        relu_all<W, 1>(h);
-        hidden_layers<W, 1>(h, sH, lane);
-        f32x4 y[1];
-        output_layer<W, 1>(y, h, sO, lane);
-        if (g == 0 && (tile << 4) + col < Q) {
-            float *o = rgb + 3 * ((tile << 4) + col);
-            o[0] = sig ? logistic(y[0][0]) : expf(y[0][0]);   // visibility cache: sigmoid outputs
-            o[1] = sig ? logistic(y[0][1]) : expf(y[0][1]);
-            o[2] = sig ? logistic(y[0][2]) : expf(y[0][2]);
+    for (int mt = 0; mt < MT; ++mt) h[0][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    layer1_surface<W>(h[0], opaque(packed) + L.offset(SEC_S), xs, lane, g);
+    const float dx[1] = {q.wx[qi]}, dy[1] = {q.wy[qi]}, dz[1] = {q.wz[qi]};
+    layer1_direction<W, 1>(h, sD, dx, dy, dz, lane, g);
+    relu_all<W, 1>(h);
+    hidden_layers<W, 1>(h, sH, lane);
+    f32x4 y[1];
+    output_layer<W, 1>(y, h, sO, lane);
+    if (g == 0 && (tile << 4) + col < Q) {
+        float *o = rgb + 3 * ((tile << 4) + col);
+        o[0] = sig ? logistic(y[0][0]) : expf(y[0][0]);   // visibility cache: sigmoid outputs
+        o[1] = sig ? logistic(y[0][1]) : expf(y[0][1]);
+        o[2] = sig ? logistic(y[0][2]) : expf(y[0][2]);
+    }
+}
+
+template <int W, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void k_infer_f32(Points pts, Queries q, const float *__restrict__ packed,
+                                                          float *__restrict__ rgb, int sig) {
+    static_assert(!lds_weights(W), "width 64 takes k_infer_split");
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    const int64_t n_tiles = (q.count + 15) >> 4;
+    for (int64_t tile = (int64_t)blockIdx.x * WAVES + wave; tile < n_tiles; tile += (int64_t)gridDim.x * WAVES)
+        infer_tile_f32<W>(pts, q, packed, nullptr, rgb, sig, tile, lane, g, col);
+}
+
+// The packed FP32 sections the FP32 chain reads from LDS ([D, T0) of F32Layout{64}).
+template <int WAVES>
+__device__ __forceinline__ void stage_f32(f32x4 *dst, const float *packed) {
+    static_assert(InferLds<64>::kWeights / 4 <= kSplitWeights, "the FP32 sections fit in the split weights' room");
+    const f32x4 *src = (const f32x4 *)(packed + F32Layout{64}.offset(SEC_D));
+    for (int i = threadIdx.x; i < InferLds<64>::kWeights / 4; i += WAVES * 64) dst[i] = src[i];
+}
+
+// Inference of FP32 models of width 64: T tiles of 16 queries per wave and pass through the split
+// chain (or tile by tile through the FP32 chain for models the split scales do not suit).
+template <int T, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void k_infer_split(Points pts, Queries q, const float *__restrict__ packed,
+                                                            float *__restrict__ rgb, int sig) {
+    __shared__ u32x4 wsm[kSplitWeights];
+    __shared__ SplitNorms s_norms;
+    SplitScale sc;
+    const bool split = split_stage<WAVES>(packed, wsm, &s_norms, sc);
+    if (!split) stage_f32<WAVES>((f32x4 *)wsm, packed);
+    __syncthreads();
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    const int64_t Q = q.count, n_tiles = (Q + 15) >> 4;
+    const int64_t first = T * ((int64_t)blockIdx.x * WAVES + wave), stride = T * (int64_t)gridDim.x * WAVES;
+    if (!split) {
+        for (int64_t t0 = first; t0 < n_tiles; t0 += stride)
+            for (int64_t t = t0; t < min(t0 + T, n_tiles); ++t)
+                infer_tile_f32<64>(pts, q, packed, (const float *)wsm, rgb, sig, t, lane, g, col);
+        return;
+    }
+    for (int64_t t0 = first; t0 < n_tiles; t0 += stride) {
+        float xs[T][7], dx[T], dy[T], dz[T];
+#pragma unroll
+        for (int tt = 0; tt < T; ++tt) {
+            const int64_t qi = min(((t0 + tt) << 4) + col, Q - 1);
+            const int64_t p = query_point(q, pts, qi);
+            xs[tt][0] = pts.px[p], xs[tt][1] = pts.py[p], xs[tt][2] = pts.pz[p];
+            xs[tt][3] = pts.nx[p], xs[tt][4] = pts.ny[p], xs[tt][5] = pts.nz[p], xs[tt][6] = pts.rough[p];
+            dx[tt] = q.wx[qi], dy[tt] = q.wy[qi], dz[tt] = q.wz[qi];
+        }
+        f32x4 acc[T][4];
+#pragma unroll
+        for (int tt = 0; tt < T; ++tt)
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt) acc[tt][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        split_surface<T>(acc, wsm, xs, lane, g);
+        const f32x4 z = split_mlp<T>(acc, wsm, sc, dx, dy, dz, lane, g, col);
+        // lane (g, col): channel col % 3 of queries 4 g + i of tile col / 3
+        const int tt = col / 3, c = col - 3 * tt;
+        if (tt < T) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int64_t qo = ((t0 + tt) << 4) + 4 * g + i;
+                if (qo < Q) rgb[3 * qo + c] = sig ? logistic(z[i]) : expf(z[i]);
+            }
         }
     }
 }
@@ -271,7 +325,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_infer_f32(Points pts, Queries q,
 // OCC: the occluded-scene variants (visibility cache, radiance cache of the occluded scene),
 // selected at run time by `mode`; the radiance cache of the plain scene compiles without them.
 // ENC 1: the hash-grid model's direction input (spherical harmonics; width 64).
-template <int W, int T, bool OCC, int ENC = 0, bool N16 = false>
+template <int W, int T, bool OCC, int ENC = 0>
 __device__ __forceinline__ void tlmc_tiles_f32(int T0, int s0, int n_cache, DivN dn, const float *db, const float *hs,
                                                const float *sD, const float *sH, const float *sO,
                                                const nirc_lobes &lobes, const float *rrad, int64_t pc,
@@ -326,7 +380,7 @@ __device__ __forceinline__ void tlmc_tiles_f32(int T0, int s0, int n_cache, DivN
             y2 = __expf(y[tt][2]);
         }
         if (Tt < n_cache) {
-            reduce_cache_tile<N16>(Tt, n_cache, col, y0, y1, y2, fc0, fc1, fc2);
+            reduce_cache_tile(Tt, n_cache, col, y0, y1, y2, fc0, fc1, fc2);
         } else {
             float Lr[3];
             if (rrad) {   // uniform: the caller's residual radiance
@@ -364,7 +418,7 @@ __device__ __forceinline__ void tlmc_tiles_f32(int T0, int s0, int n_cache, DivN
 // field and subtracts.  Only the final per-point values leave the chip.
 // One point group (16 points from p0) through the FP32 chain.
 // ENC 1: the hash-grid model (surface part from the grid `slv`/`table` and phi).
-template <int W, bool OCC, int ENC = 0, bool N16 = false>
+template <int W, bool OCC, int ENC = 0>
 __device__ __forceinline__ void tlmc_group_f32(const Points &pts, int64_t p0, int n_cache, DivN dn, uint32_t key0,
                                                uint32_t key1, uint32_t frame, int mode, const float *rrad,
                                                float *out_tl,
@@ -407,11 +461,11 @@ __device__ __forceinline__ void tlmc_group_f32(const Points &pts, int64_t p0, in
         constexpr int TP = W <= 64 ? 4 : 2;   // tiles per pass (register budget)
 #pragma unroll 1
         for (; t + TP <= tend; t += TP)
-            tlmc_tiles_f32<W, TP, OCC, ENC, N16>(t, t - tb, n_cache, dn, db, hs, sD, sH, sO, lobes, rrad, pc, pts, p0, mode, xs,
+            tlmc_tiles_f32<W, TP, OCC, ENC>(t, t - tb, n_cache, dn, db, hs, sD, sH, sO, lobes, rrad, pc, pts, p0, mode, xs,
                                             lane, g, col, fc0, fc1, fc2, fr0, fr1, fr2);
 #pragma unroll 1
         for (; t < tend; ++t)
-            tlmc_tiles_f32<W, 1, OCC, ENC, N16>(t, t - tb, n_cache, dn, db, hs, sD, sH, sO, lobes, rrad, pc, pts, p0, mode, xs,
+            tlmc_tiles_f32<W, 1, OCC, ENC>(t, t - tb, n_cache, dn, db, hs, sD, sH, sO, lobes, rrad, pc, pts, p0, mode, xs,
                                            lane, g, col, fc0, fc1, fc2, fr0, fr1, fr2);
         tb = tend;
     }
@@ -419,77 +473,183 @@ __device__ __forceinline__ void tlmc_group_f32(const Points &pts, int64_t p0, in
         store_estimate(p0 + col, 1.0f / (float)n_cache, fc0, fc1, fc2, fr0, fr1, fr2, out_tl, out_c, out_r);
 }
 
-// N16: n_cache is a multiple of 16 (the per-point sums' other paths compiled out).
-template <int W, int WAVES, bool OCC, bool N16 = false>
+// T query tiles (first tile T0, staged directions from batch slot s0) through the split chain.
+template <int T, bool OCC, bool N16>
+__device__ __forceinline__ void tlmc_tiles_split(int T0, int s0, int n_cache, DivN dn, const GroupSlab &gs,
+                                                 const u32x4 *w, const SplitScale &sc, int lane, int g, int col,
+                                                 float &rdx, float &rdy, float &rdz, const Points &pts, int64_t p0,
+                                                 int mode, const nirc_lobes &lobes) {
+    f32x4 acc[T][4];
+    float dx[T], dy[T], dz[T];
+#pragma unroll
+    for (int tt = 0; tt < T; ++tt) {
+        const int Tt = T0 + tt, qi = 16 * (s0 + tt) + col;
+        dx[tt] = gs.db[qi];
+        dy[tt] = gs.db[kDirSlots + qi];
+        dz[tt] = gs.db[2 * kDirSlots + qi];
+        if (Tt == n_cache) {   // residual tile: keep this column's direction for the final combine
+            rdx = dx[tt];
+            rdy = dy[tt];
+            rdz = dz[tt];
+        }
+        const int j = (Tt < n_cache) ? (int)div_n((uint32_t)(N16 ? 16 * Tt : 16 * Tt + col), dn) : col;
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) acc[tt][mt] = *(const f32x4 *)(gs.hs + j * 64 + 16 * mt + 4 * g);
+    }
+    const f32x4 z = split_mlp<T>(acc, w, sc, dx, dy, dz, lane, g, col);
+    tlmc_sums<T, OCC, N16, true>(z, T0, s0, n_cache, dn, gs, lane, g, col, pts, p0, mode, lobes);
+}
+
+// One point group (16 points from p0) through the split chain; the slab's surface projections are
+// in the first layer's accumulator scale.
+template <bool OCC, bool N16>
+__device__ __forceinline__ void tlmc_group_split(const Points &pts, int64_t p0, int n_cache, DivN dn, uint32_t key0,
+                                                 uint32_t key1, uint32_t frame, int mode, const float *rrad,
+                                                 float *out_tl, float *out_c, float *out_r, const nirc_lobes &lobes,
+                                                 const u32x4 *w, const SplitScale &sc, const GroupSlab &gs, int lane,
+                                                 int g, int col) {
+    const int64_t P = pts.count, pc = min(p0 + col, P - 1);
+    const int n_tiles = n_cache + 1;
+    const float xs[1][7] = {{pts.px[pc], pts.py[pc], pts.pz[pc], pts.nx[pc], pts.ny[pc], pts.nz[pc], pts.rough[pc]}};
+    {
+        f32x4 hsum[1][4];
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) hsum[0][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        split_surface<1>(hsum, w, xs, lane, g);
+        wave_sync();   // the previous group's readers of the slab are done
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) *(f32x4 *)(gs.hs + col * 64 + 16 * mt + 4 * g) = hsum[0][mt];
+        gs.psum[lane] = 0.0f;
+        if (g < 3) gs.nrm[16 * g + col] = g == 0 ? xs[0][3] : g == 1 ? xs[0][4] : xs[0][5];
+        wave_sync();
+    }
+    float rdx = 0.f, rdy = 0.f, rdz = 0.f;
+    for (int tb = 0; tb < n_tiles;) {
+        const bool fold = n_tiles - tb == 9;   // last 8 cache tiles + the residual tile
+        gen_dirs_batch_nrm<false>((uint32_t)p0, tb, n_cache, dn, key0, key1, frame, lane, gs.db, gs.nrm, fold);
+        const int tend = fold ? n_tiles : min(tb + 8, n_tiles);
+        int t = tb;
+#pragma unroll 1
+        for (; t + 4 <= tend; t += 4)
+            tlmc_tiles_split<4, OCC, N16>(t, t - tb, n_cache, dn, gs, w, sc, lane, g, col, rdx, rdy, rdz, pts, p0,
+                                          mode, lobes);
+#pragma unroll 1
+        for (; t < tend; ++t)
+            tlmc_tiles_split<1, OCC, N16>(t, t - tb, n_cache, dn, gs, w, sc, lane, g, col, rdx, rdy, rdz, pts, p0,
+                                          mode, lobes);
+        tb = tend;
+    }
+    wave_sync();
+    tlmc_finish<OCC>(gs, xs[0], rdx, rdy, rdz, p0, P, pc, n_cache, mode, rrad, out_tl, out_c, out_r, lobes, g, col);
+}
+
+// Fused estimator of FP32 models of width 64: the split chain, or the FP32 chain for models the
+// split scales do not suit.
+template <int WAVES, bool OCC, bool N16>
+__global__ __launch_bounds__(WAVES * 64) void k_tlmc_split(Points pts, nirc_lobes lobes,
+                                                           const float *__restrict__ packed, int n_cache, DivN dn,
+                                                           uint32_t key0, uint32_t key1, uint32_t frame, int mode,
+                                                           const float *__restrict__ rrad, float *__restrict__ out_tl,
+                                                           float *__restrict__ out_c, float *__restrict__ out_r) {
+    static_assert(InferLds<64>::kWeights / 4 <= kSplitWeights, "the FP32 sections fit in the split weights' room");
+    __shared__ u32x4 wsm[kSplitWeights];
+    __shared__ f32x4 slab4[WAVES * kSplitSlab / 4];
+    __shared__ nirc_lobes s_lobes;
+    __shared__ SplitNorms s_norms;
+    if (threadIdx.x == 0) s_lobes = lobes;
+    SplitScale sc;
+    const bool split = split_stage<WAVES>(packed, wsm, &s_norms, sc);
+    if (!split) stage_f32<WAVES>((f32x4 *)wsm, packed);
+    __syncthreads();
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    float *slab = (float *)slab4 + wave * kSplitSlab;
+    const int64_t n_groups = (pts.count + 15) >> 4, stride = (int64_t)gridDim.x * WAVES;
+    if (split) {
+        const GroupSlab gs = group_slab(slab, 64);
+        for (int64_t grp = (int64_t)blockIdx.x * WAVES + wave; grp < n_groups; grp += stride)
+            tlmc_group_split<OCC, N16>(pts, grp << 4, n_cache, dn, key0, key1, frame, mode, rrad, out_tl, out_c, out_r,
+                                       s_lobes, wsm, sc, gs, lane, g, col);
+    } else {
+        constexpr F32Layout L{64};
+        const float *sD = (const float *)wsm, *sH = sD + L.size(SEC_D), *sO = sH + 3 * L.size(SEC_H0);
+        for (int64_t grp = (int64_t)blockIdx.x * WAVES + wave; grp < n_groups; grp += stride)
+            tlmc_group_f32<64, OCC>(pts, grp << 4, n_cache, dn, key0, key1, frame, mode, rrad, out_tl, out_c, out_r,
+                                    s_lobes, packed + L.offset(SEC_S), sD, sH, sO, slab, slab + 16 * 64, lane, g, col);
+    }
+}
+
+// The estimator of FP32 models of width 128 (weights read from global memory inside each pass).
+template <int W, int WAVES, bool OCC>
 __global__ __launch_bounds__(WAVES * 64) void k_tlmc_f32(Points pts, nirc_lobes lobes,
                                                          const float *__restrict__ packed,
                                                          int n_cache, DivN dn, uint32_t key0, uint32_t key1,
                                                          uint32_t frame, int mode, const float *__restrict__ rrad,
                                                          float *__restrict__ out_tl, float *__restrict__ out_c,
                                                          float *__restrict__ out_r) {
+    static_assert(!lds_weights(W), "width 64 takes k_tlmc_split");
     constexpr F32Layout L{W};
-    constexpr bool kLds = lds_weights(W);
-    constexpr int NW = kLds ? InferLds<W>::kWeights : 0;
     constexpr int SLAB = TlmcLds<W>::kSlab;
-    __shared__ f32x4 smem4[(NW + WAVES * SLAB) / 4];
+    __shared__ f32x4 smem4[WAVES * SLAB / 4];
     __shared__ nirc_lobes s_lobes;
-    float *smem = (float *)smem4;
-    {
-        const f32x4 *src = (const f32x4 *)(packed + L.offset(SEC_D));
-        for (int i = threadIdx.x; i < NW / 4; i += WAVES * 64) smem4[i] = src[i];
-        if (threadIdx.x == 0) s_lobes = lobes;
-    }
+    if (threadIdx.x == 0) s_lobes = lobes;
     __syncthreads();
-    const float *sD = kLds ? (const float *)smem : packed + L.offset(SEC_D);
-    const float *sH = sD + L.size(SEC_D);   // LDS for width 64, global memory above
+    const float *sD = packed + L.offset(SEC_D);
+    const float *sH = sD + L.size(SEC_D);
     const float *sO = sH + 3 * L.size(SEC_H0);
     const float *gS = packed + L.offset(SEC_S);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
-    float *hs = smem + NW + wave * SLAB;   // [16 points][W]
-    float *db = hs + 16 * W;               // directions, SoA [3][kDirSlots]
+    float *hs = (float *)smem4 + wave * SLAB;   // [16 points][W]
+    float *db = hs + 16 * W;                    // directions, SoA [3][kDirSlots]
     const int64_t n_groups = (pts.count + 15) >> 4;
     for (int64_t grp = (int64_t)blockIdx.x * WAVES + wave; grp < n_groups; grp += (int64_t)gridDim.x * WAVES)
-        tlmc_group_f32<W, OCC, 0, N16>(pts, grp << 4, n_cache, dn, key0, key1, frame, mode, rrad, out_tl, out_c, out_r,
-                                       s_lobes, gS, sD, sH, sO, hs, db, lane, g, col);
+        tlmc_group_f32<W, OCC>(pts, grp << 4, n_cache, dn, key0, key1, frame, mode, rrad, out_tl, out_c, out_r, s_lobes,
+                               gS, sD, sH, sO, hs, db, lane, g, col);
 }
 
-// Continuous batching with the FP32 chain (see k_tlmc_multi_h16).
-template <int W, int WAVES, bool OCC>
-__global__ __launch_bounds__(WAVES * 64) void k_tlmc_multi_f32(const BatchDesc *__restrict__ desc) {
-    constexpr F32Layout L{W};
-    constexpr int NW = InferLds<W>::kWeights;
-    constexpr int SLAB = TlmcLds<W>::kSlab;
-    __shared__ f32x4 smem4[(NW + WAVES * SLAB) / 4];
+// Continuous batching of FP32 models (see k_tlmc_multi_h16): the weights, split or FP32, are
+// staged again when the request changes.
+template <int WAVES, bool OCC>
+__global__ __launch_bounds__(WAVES * 64) void k_tlmc_multi_split(const BatchDesc *__restrict__ desc) {
+    constexpr F32Layout L{64};
+    __shared__ u32x4 wsm[kSplitWeights];
+    __shared__ f32x4 slab4[WAVES * kSplitSlab / 4];
     __shared__ BatchRequest s_req;
-    float *smem = (float *)smem4;
-    const float *sD = smem;
-    const float *sH = smem + L.size(SEC_D);
-    const float *sO = sH + 3 * L.size(SEC_H0);
+    __shared__ SplitNorms s_norms;
+    const float *sD = (const float *)wsm, *sH = sD + L.size(SEC_D), *sO = sH + 3 * L.size(SEC_H0);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
-    float *hs = smem + NW + wave * SLAB;
-    float *db = hs + 16 * W;
+    float *slab = (float *)slab4 + wave * kSplitSlab;
+    const GroupSlab gs = group_slab(slab, 64);
     const int n_req = desc->n_requests;
     const int total = desc->total_chunks;
     int cur = -1;
+    bool split = false;
+    SplitScale sc;
     for (int chunk = blockIdx.x; chunk < total; chunk += gridDim.x) {
         int r = 0;
         for (int i = 1; i < n_req; ++i)
             if (desc->req[i].chunk_begin <= chunk) r = i;
         if (r != cur) {
-            __syncthreads();
+            __syncthreads();   // every wave is done with the previous request's weights
             if (threadIdx.x == 0) s_req = desc->req[r];
             __syncthreads();
-            const f32x4 *src = (const f32x4 *)((const float *)s_req.packed + L.offset(SEC_D));
-            for (int i = threadIdx.x; i < NW / 4; i += WAVES * 64) smem4[i] = src[i];
+            split = split_stage<WAVES>((const float *)s_req.packed, wsm, &s_norms, sc);
+            if (!split) stage_f32<WAVES>((f32x4 *)wsm, (const float *)s_req.packed);
             __syncthreads();
             cur = r;
         }
         const int64_t grp = (int64_t)(chunk - s_req.chunk_begin) * WAVES + wave;
-        if (grp < (s_req.pts.count + 15) >> 4)
-            tlmc_group_f32<W, OCC>(s_req.pts, grp << 4, s_req.n_cache, s_req.dn, s_req.key0, s_req.key1, s_req.frame,
-                              __builtin_amdgcn_readfirstlane(s_req.mode), uniform_ptr(s_req.rrad), s_req.out_tl,
-                              s_req.out_c, s_req.out_r, s_req.lobes,
-                              (const float *)s_req.packed + L.offset(SEC_S), sD, sH, sO, hs, db, lane, g, col);
+        if (grp < (s_req.pts.count + 15) >> 4) {
+            const int mode = __builtin_amdgcn_readfirstlane(s_req.mode);
+            if (split)
+                tlmc_group_split<OCC, false>(s_req.pts, grp << 4, s_req.n_cache, s_req.dn, s_req.key0, s_req.key1,
+                                             s_req.frame, mode, uniform_ptr(s_req.rrad), s_req.out_tl, s_req.out_c,
+                                             s_req.out_r, s_req.lobes, wsm, sc, gs, lane, g, col);
+            else
+                tlmc_group_f32<64, OCC>(s_req.pts, grp << 4, s_req.n_cache, s_req.dn, s_req.key0, s_req.key1,
+                                        s_req.frame, mode, uniform_ptr(s_req.rrad), s_req.out_tl, s_req.out_c,
+                                        s_req.out_r, s_req.lobes, (const float *)s_req.packed + L.offset(SEC_S), sD, sH,
+                                        sO, slab, slab + 16 * 64, lane, g, col);
+        }
     }
 }
 
@@ -561,10 +721,15 @@ hipError_t launch_infer(int W, int prec, const Points &pts, const Queries &q, co
     if (q.count == 0) return hipSuccess;
     if (prec != NIRC_FP32) return launch_infer_h16(W, prec, pts, q, packed, rgb, sig, s);
     constexpr int WAVES = 4;
-    const unsigned grid = grid_for((q.count + 15) / 16, WAVES, 2 * kMaxResidentBlocks);
-    if (W == 64)
-        hipLaunchKernelGGL((k_infer_f32<64, WAVES>), dim3(grid), dim3(WAVES * 64), 0, s, pts, q, (const float *)packed,
-                           rgb, sig);
+    const int64_t tiles = (q.count + 15) / 16;
+    const unsigned grid = grid_for(tiles, WAVES, 2 * kMaxResidentBlocks);
+    // one workgroup per CU (100 KB of split weights): 4 tiles per pass once every wave has them
+    if (W == 64 && tiles > 8 * kMaxResidentBlocks)
+        hipLaunchKernelGGL((k_infer_split<4, 8>), dim3(grid_for((tiles + 3) / 4, 8, kMaxResidentBlocks)), dim3(512), 0, s,
+                           pts, q, (const float *)packed, rgb, sig);
+    else if (W == 64)
+        hipLaunchKernelGGL((k_infer_split<1, 8>), dim3(grid_for(tiles, 8, kMaxResidentBlocks)), dim3(512), 0, s, pts, q,
+                           (const float *)packed, rgb, sig);
     else if (W == 128)
         hipLaunchKernelGGL((k_infer_f32<128, WAVES>), dim3(grid), dim3(WAVES * 64), 0, s, pts, q,
                            (const float *)packed, rgb, sig);
@@ -578,9 +743,9 @@ hipError_t launch_tlmc_multi_f32(int W, int mode, const BatchDesc *desc, int gri
     static_assert(WAVES == kBatchChunkGroups, "chunk size");
     if (W != 64) return hipErrorInvalidValue;
     if (mode == NIRC_OUTPUT_RADIANCE)
-        hipLaunchKernelGGL((k_tlmc_multi_f32<64, WAVES, false>), dim3(grid), dim3(WAVES * 64), 0, s, desc);
+        hipLaunchKernelGGL((k_tlmc_multi_split<WAVES, false>), dim3(grid), dim3(WAVES * 64), 0, s, desc);
     else
-        hipLaunchKernelGGL((k_tlmc_multi_f32<64, WAVES, true>), dim3(grid), dim3(WAVES * 64), 0, s, desc);
+        hipLaunchKernelGGL((k_tlmc_multi_split<WAVES, true>), dim3(grid), dim3(WAVES * 64), 0, s, desc);
     return hipGetLastError();
 }
 
@@ -599,14 +764,14 @@ hipError_t launch_tlmc(int W, int prec, const Points &pts, const nirc_lobes &lob
     const float *pk = (const float *)packed;
     const bool occ = mode != NIRC_OUTPUT_RADIANCE;
     if (W == 64 && !occ && n_cache % 16 == 0)
-        hipLaunchKernelGGL((k_tlmc_f32<64, WAVES, false, true>), dim3(grid), dim3(WAVES * 64), 0, s, pts, lobes, pk,
+        hipLaunchKernelGGL((k_tlmc_split<WAVES, false, true>), dim3(grid), dim3(WAVES * 64), 0, s, pts, lobes, pk,
                            n_cache, dn, k0, k1, f, mode, rrad, out_tl, out_c, out_r);
     else if (W == 64 && !occ)
-        hipLaunchKernelGGL((k_tlmc_f32<64, WAVES, false>), dim3(grid), dim3(WAVES * 64), 0, s, pts, lobes, pk, n_cache,
-                           dn, k0, k1, f, mode, rrad, out_tl, out_c, out_r);
+        hipLaunchKernelGGL((k_tlmc_split<WAVES, false, false>), dim3(grid), dim3(WAVES * 64), 0, s, pts, lobes, pk,
+                           n_cache, dn, k0, k1, f, mode, rrad, out_tl, out_c, out_r);
     else if (W == 64)
-        hipLaunchKernelGGL((k_tlmc_f32<64, WAVES, true>), dim3(grid), dim3(WAVES * 64), 0, s, pts, lobes, pk, n_cache,
-                           dn, k0, k1, f, mode, rrad, out_tl, out_c, out_r);
+        hipLaunchKernelGGL((k_tlmc_split<WAVES, true, false>), dim3(grid), dim3(WAVES * 64), 0, s, pts, lobes, pk,
+                           n_cache, dn, k0, k1, f, mode, rrad, out_tl, out_c, out_r);
     // width 128: one wave per SIMD (the width-128 FP32 pass needs more than 256 registers)
     else if (W == 128 && !occ)
         hipLaunchKernelGGL((k_tlmc_f32<128, 4, false>), dim3(grid128), dim3(4 * 64), 0, s, pts, lobes, pk, n_cache,
