@@ -174,16 +174,23 @@ struct HashCell {
     float f[3];
 };
 
-// Cell of x (clamped to the unit cube) at resolution N: lower corner and fractions.
+// Cell of x (clamped to the unit cube) at resolution N: lower corner and fractions.  EXACT: the
+// fraction takes the unrounded product x N (a fused multiply-add); otherwise the product is rounded
+// first, which moves the fraction by up to 2^-24 N.  Written out, because a compiler that contracts
+// one kernel's expression and not another's would give the lookup and the scatter of one step
+// different weights.
+template <bool EXACT = true>
 __host__ __device__ __forceinline__ HashCell hash_cell(float x0, float x1, float x2, int N) {
+#pragma clang fp contract(off)
     HashCell h;
     const float xs[3] = {x0, x1, x2};
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        const float p = fminf(fmaxf(xs[d], 0.0f), 1.0f) * (float)N;
+        const float x = fminf(fmaxf(xs[d], 0.0f), 1.0f);
+        const float p = x * (float)N;
         const int ci = min((int)floorf(p), N - 1);
         h.c[d] = ci;
-        h.f[d] = p - (float)ci;
+        h.f[d] = EXACT ? fmaf(x, (float)N, -(float)ci) : p - (float)ci;
     }
     return h;
 }
@@ -200,28 +207,46 @@ __host__ __device__ __forceinline__ uint32_t hash_entry(const HashLevel &lv, uin
     return lv.off + (lv.dense ? dense : hashed);
 }
 
-// The 24 corner features lane group g needs at x (levels 3g..3g+2, 8 corners each): loads only,
-// so that they can be issued one point group ahead of their use.  The y and z parts of the
-// dense index and of the hash are formed once per level and shared by the corners.
+// The 8 corner features of a level at x: loads only, so that they can be issued ahead of their use.
+// The y and z parts of the dense index and of the hash are formed once and shared by the corners.
+__host__ __device__ __forceinline__ void hash_fetch8(const HashLevel &lv, uint32_t tmask, const float2 *table, float x0,
+                                                     float x1, float x2, float2 *t) {
+    const HashCell h = hash_cell(x0, x1, x2, lv.res);
+    const uint32_t n1 = (uint32_t)lv.res + 1u;
+    const uint32_t c0 = (uint32_t)h.c[0], c1 = (uint32_t)h.c[1], c2 = (uint32_t)h.c[2];
+    const uint32_t dy = n1 * (c1 + n1 * c2);                          // dense: corner (0, 0, 0)
+    const uint32_t hy0 = c1 * 2654435761u, hz0 = c2 * 805459861u;     // hash: y and z parts
+    const uint32_t hy1 = hy0 + 2654435761u, hz1 = hz0 + 805459861u;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        const uint32_t bx = c & 1, by = (c >> 1) & 1, bz = (c >> 2) & 1;
+        const uint32_t dense = c0 + bx + dy + (by ? n1 : 0u) + (bz ? n1 * n1 : 0u);
+        const uint32_t hashed = ((c0 + bx) ^ (by ? hy1 : hy0) ^ (bz ? hz1 : hz0)) & tmask;
+        t[c] = table[lv.off + (lv.dense ? dense : hashed)];
+    }
+}
+
+// Trilinear blend of a level's fetched corner features.
+template <bool EXACT = true>
+__host__ __device__ __forceinline__ float2 hash_blend2(const HashLevel &lv, float x0, float x1, float x2,
+                                                       const float2 *t) {
+    const HashCell h = hash_cell<EXACT>(x0, x1, x2, lv.res);
+    float a = 0.0f, b = 0.0f;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        const float w = ((c & 1) ? h.f[0] : 1.0f - h.f[0]) * (((c >> 1) & 1) ? h.f[1] : 1.0f - h.f[1]) *
+                        (((c >> 2) & 1) ? h.f[2] : 1.0f - h.f[2]);
+        a += w * t[c].x;
+        b += w * t[c].y;
+    }
+    return make_float2(a, b);
+}
+
+// The 24 corner features lane group g needs at x (levels 3g..3g+2, 8 corners each).
 __host__ __device__ __forceinline__ void hash_fetch24(const HashLevel *slv, uint32_t tmask, const float2 *table, float x0,
                                              float x1, float x2, int g, float2 (&t)[24]) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const HashLevel lv = slv[3 * g + k];
-        const HashCell h = hash_cell(x0, x1, x2, lv.res);
-        const uint32_t n1 = (uint32_t)lv.res + 1u;
-        const uint32_t c0 = (uint32_t)h.c[0], c1 = (uint32_t)h.c[1], c2 = (uint32_t)h.c[2];
-        const uint32_t dy = n1 * (c1 + n1 * c2);                          // dense: corner (0, 0, 0)
-        const uint32_t hy0 = c1 * 2654435761u, hz0 = c2 * 805459861u;     // hash: y and z parts
-        const uint32_t hy1 = hy0 + 2654435761u, hz1 = hz0 + 805459861u;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const uint32_t bx = c & 1, by = (c >> 1) & 1, bz = (c >> 2) & 1;
-            const uint32_t dense = c0 + bx + dy + (by ? n1 : 0u) + (bz ? n1 * n1 : 0u);
-            const uint32_t hashed = ((c0 + bx) ^ (by ? hy1 : hy0) ^ (bz ? hz1 : hz0)) & tmask;
-            t[8 * k + c] = table[lv.off + (lv.dense ? dense : hashed)];
-        }
-    }
+    for (int k = 0; k < 3; ++k) hash_fetch8(slv[3 * g + k], tmask, table, x0, x1, x2, t + 8 * k);
 }
 
 // Trilinear blend of fetched corner features into lane group g's six grid values.
@@ -229,18 +254,9 @@ __host__ __device__ __forceinline__ void hash_blend6(const HashLevel *slv, float
                                             const float2 (&t)[24], float (&v)[6]) {
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        const HashLevel lv = slv[3 * g + k];
-        const HashCell h = hash_cell(x0, x1, x2, lv.res);
-        float a = 0.0f, b = 0.0f;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const float w = ((c & 1) ? h.f[0] : 1.0f - h.f[0]) * (((c >> 1) & 1) ? h.f[1] : 1.0f - h.f[1]) *
-                            (((c >> 2) & 1) ? h.f[2] : 1.0f - h.f[2]);
-            a += w * t[8 * k + c].x;
-            b += w * t[8 * k + c].y;
-        }
-        v[2 * k] = a;
-        v[2 * k + 1] = b;
+        const float2 r = hash_blend2(slv[3 * g + k], x0, x1, x2, t + 8 * k);
+        v[2 * k] = r.x;
+        v[2 * k + 1] = r.y;
     }
 }
 
@@ -488,9 +504,72 @@ __device__ __forceinline__ void grid_acc_add(const GridAcc &g, size_t i, float v
 hipError_t launch_grid_acc_finish(const GridAcc &g, float *grad, int64_t n, float scale, uint32_t *bad,
                                   hipStream_t s);
 
-hipError_t launch_hash_grad32(const Points &pts, const Queries &q, const float *packed, const float *table,
-                              const HashGridArgs &grid, TrainArgs a, float *partials, float *loss_partials,
-                              GridAcc gacc, int nblocks, hipStream_t s);
+// Samples of a training step between its kernels (workspace): point attributes [B][8]; grid values,
+// their gradients (two features each) and the slices each cell's corner rows touch (4 bytes), each
+// [12 levels][hash_level_stride(B)].
+struct HashTrainBufs {
+    float *attr;
+    float2 *vals, *dvals;
+    uint32_t *codes;
+};
+// Samples from one level to the next (16-byte aligned levels whatever the batch).
+__host__ __device__ constexpr int64_t hash_level_stride(int64_t B) { return (B + 63) / 64 * 64; }
+
+// Slices of the grid-gradient sums: kSliceEntries entries (128 KB of sums, one workgroup's LDS) of a
+// hashed level, or whole x rows of a dense one.
+constexpr int kSliceEntries = 8192;
+struct HashScatterLevel {
+    int32_t slices;   // slices of the level
+    int32_t rows;     // dense: x rows per slice
+    uint32_t magic;   // dense: row / rows = umulhi(row, magic) (rows > 1)
+    int32_t reps;     // workgroups sharing a slice, each over `per` samples
+    int32_t per;
+    int32_t task0;    // first task of the level
+    int32_t merge0;   // shared slices: the level's first merged accumulator, else -1
+};
+struct HashScatterPlan {
+    HashScatterLevel lv[kHashLevels];
+    int32_t tasks;
+    int32_t first;          // task of the first workgroup (they go on in turn from there)
+    int64_t merged_elems;   // accumulators of the shared levels
+};
+// False when the grid does not suit the slices (rows or hashed resolutions beyond a slice, more than
+// 256 slices in a level): the caller takes the global-atomic sums.
+bool hash_scatter_plan(const HashGridArgs &grid, int64_t B, HashScatterPlan *plan);
+
+// Adam state of the grid's parameters (pointers to the first one; the MLP's lie below).
+struct HashAdam {
+    float *w, *m, *v;
+    const int64_t *step;
+    uint32_t *bad;
+    float lr, b1, b2, eps;
+};
+
+// A contribution w d to an entry must fit the fixed-point sums (grid_acc_add's test, for the largest
+// of the cell's eight weights: products round monotonically, so it decides for all of them).
+__device__ __forceinline__ void grid_grad_check(const GridAcc &ga, float d, float x0, float x1, float x2, int res) {
+    if (fabsf(d) * 0x1p36f < 0x1p62f) return;
+    const HashCell h = hash_cell(x0, x1, x2, res);
+    const float w = fmaxf(h.f[0], 1.0f - h.f[0]) * fmaxf(h.f[1], 1.0f - h.f[1]) * fmaxf(h.f[2], 1.0f - h.f[2]);
+    if (!(fabsf(w * d * 0x1p36f) < 0x1p62f)) atomicOr(ga.nonfinite, 1u);
+}
+
+// exact: the cells' fractions from the unrounded position product (hash_cell): FP32 models.  first:
+// the batch's first part (clears the non-finite flag).
+hipError_t launch_hash_prep(const Points &pts, const Queries &q, const float *table, const HashGridArgs &grid,
+                            const HashScatterPlan &plan, bool sliced, bool exact, bool first,
+                            const HashTrainBufs &bufs, GridAcc gacc, hipStream_t s);
+// The grid gradient from bufs.dvals by slices: Adam on the grid and (from mlp_grad) the MLP
+// parameters, or (adam false) the grid gradient times scale into grad (the grid's first entry).
+hipError_t launch_hash_scatter(const HashGridArgs &grid, const HashScatterPlan &plan, const HashTrainBufs &bufs,
+                               GridAcc gacc, int64_t B, float scale, const float *mlp_grad, float *grad,
+                               const HashAdam &ad, bool adam, hipStream_t s);
+// ... or by global atomics into gacc (zeroed by the caller).
+hipError_t launch_hash_scatter_atomic(const HashGridArgs &grid, const HashTrainBufs &bufs, GridAcc gacc, int64_t B,
+                                      hipStream_t s);
+hipError_t launch_hash_grad32(const Queries &q, const float *packed, const HashGridArgs &grid, TrainArgs a,
+                              const HashTrainBufs &bufs, float *partials, float *loss_partials, GridAcc gacc,
+                              int nblocks, bool add, hipStream_t s);
 hipError_t launch_hash_infer32(const Points &pts, const Queries &q, const float *packed, const float *table,
                                const HashGridArgs &grid, float *rgb, hipStream_t s);
 hipError_t launch_hash_tlmc32(const Points &pts, const nirc_lobes &lobes, const float *packed, const float *table,
@@ -501,10 +580,11 @@ hipError_t launch_hash_infer(int prec, const Points &pts, const Queries &q, cons
 hipError_t launch_hash_tlmc(int prec, const Points &pts, const nirc_lobes &lobes, const uint16_t *packed,
                             const float *table, const HashGridArgs &grid, int n_cache, uint64_t seed, uint64_t frame,
                             const float *rrad, float *out_tl, float *out_c, float *out_r, hipStream_t s);
-// Gradient partials of the MLP ([nblocks][16,576]) and the grid-entry gradient, accumulated with
-// atomics into gtab ([entries][2], zeroed by the caller); both carry the loss scale of `a`.
-hipError_t launch_hash_grad(int prec, const Points &pts, const Queries &q, const uint16_t *packed, const float *table,
-                            const HashGridArgs &grid, TrainArgs a, float *partials, float *loss_partials,
-                            GridAcc gacc, int nblocks, hipStream_t s);
+// Gradient partials of the MLP ([nblocks][16,576]) and the gradients of the samples' grid values
+// (bufs.dvals); both carry the loss scale of `a`.  add: the partials of a batch's later part are added
+// to what is there.
+hipError_t launch_hash_grad(int prec, const Queries &q, const uint16_t *packed, const HashGridArgs &grid, TrainArgs a,
+                            const HashTrainBufs &bufs, float *partials, float *loss_partials, GridAcc gacc,
+                            int nblocks, bool add, hipStream_t s);
 
 }  // namespace nirc

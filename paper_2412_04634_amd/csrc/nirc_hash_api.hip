@@ -32,12 +32,13 @@ struct HashState {
 };
 
 // Workspace: MLP partials [nblocks][16,576] | loss partials [nblocks] | gradient [np] | loss |
-// training samples of nirc_hash_train_frame (point [B], wx, wy, wz [B], target [B][3]).
-// Workspace: MLP partials | loss partials | gradient [np] | loss | grid-gradient fixed-point
-// accumulators [np - kHashMlp] int64 and their non-finite flag | samples of the frame loop.
+// grid-gradient fixed-point accumulators [np - kHashMlp] int64 and their non-finite flag | the
+// batch's samples between the step's kernels (HashTrainBufs) | training samples of
+// nirc_hash_train_frame (point [B], wx, wy, wz [B], target [B][3]).
 struct HashWork {
-    size_t partials, loss_partials, grad, loss, gacc, gflag, samples, total;
-    HashWork(int64_t np, int nblocks, int64_t sample_batch = 0) {
+    size_t partials, loss_partials, grad, loss, gacc, gflag, attr, vals, dvals, codes, samples, total;
+    HashWork(int64_t np, int nblocks, int64_t batch) {
+        const size_t B = ((size_t)batch + 63) / 64 * 64 + (batch ? 0 : 64);   // whole gradient rounds
         size_t o = 0;
         partials = o; o += align_up((size_t)nblocks * kHashMlp * sizeof(float));
         loss_partials = o; o += align_up((size_t)nblocks * sizeof(float));
@@ -45,8 +46,15 @@ struct HashWork {
         loss = o; o += align_up(sizeof(float));
         gacc = o; o += align_up((size_t)(np - kHashMlp) * sizeof(unsigned long long));
         gflag = o; o += align_up(sizeof(uint32_t));
-        samples = o; o += align_up((size_t)sample_batch * 7 * sizeof(float));
+        attr = o; o += align_up(B * 8 * sizeof(float));
+        vals = o; o += align_up(B * 24 * sizeof(float));
+        dvals = o; o += align_up(B * kHashLevels * sizeof(float2));
+        codes = o; o += align_up(B * kHashLevels * sizeof(uint32_t));
+        samples = o; o += align_up(B * 7 * sizeof(float));
         total = o;
+    }
+    HashTrainBufs bufs(char *ws) const {
+        return HashTrainBufs{(float *)(ws + attr), (float2 *)(ws + vals), (float2 *)(ws + dvals), (uint32_t *)(ws + codes)};
     }
 };
 
@@ -254,56 +262,91 @@ nirc_status nirc_hash_estimate(const nirc_hash_model *model, nirc_points points,
                                    out_r, (hipStream_t)stream));
 }
 
-// Loss and gradient into grad/loss; the step's `bad` flag is raised on a non-finite value.
-static nirc_status hash_grad_into(nirc_hash_model *model, const nirc_points &points, const nirc_queries &queries,
-                                  const float *target, float *grad, float *loss, uint32_t *err, hipStream_t s) {
-    nirc_status st = check_points_h(points);
-    if (st == NIRC_OK) st = check_queries_h(queries, points);
-    if (st != NIRC_OK) return st;
-    if (queries.count < 1 || !grad || !target) return NIRC_ERR_INVALID_ARG;
-    const int nb = train_blocks16(queries.count);
-    const HashWork wl(model->np, nb);
-    if (!model->ws || model->ws_bytes < wl.total) return NIRC_ERR_WORKSPACE;
-    float *partials = (float *)(model->ws + wl.partials);
-    float *lpart = (float *)(model->ws + wl.loss_partials);
-    // the batch size is folded into the loss scale (per-sample deltas near unit magnitude in the
-    // 16-bit operands; the FP32 kernel takes the same convention); the reductions divide it out again
-    const float scale = model->cfg.loss_scale * (float)queries.count;
-    const TrainArgs a{target, nullptr, model->cfg.loss_eps, scale, model->cfg.loss, nullptr, 0};
-    const int64_t nt = model->np - kHashMlp;
-    float *gtab = grad + kHashMlp;
-    const GridAcc ga{(unsigned long long *)(model->ws + wl.gacc), (uint32_t *)(model->ws + wl.gflag)};
-    hipError_t e = launch_fill_u32((uint32_t *)ga.acc, 2 * nt, 0u, s);
-    if (e == hipSuccess) e = launch_fill_u32(ga.nonfinite, 1, 0u, s);
-    if (e == hipSuccess)
-        e = model->cfg.precision == NIRC_FP32
-                ? launch_hash_grad32(pts_of(points), queries_of(queries, err), model->packed32(), model->table(),
-                                     model->grid, a, partials, lpart, ga, nb, s)
-                : launch_hash_grad(model->cfg.precision, pts_of(points), queries_of(queries, err), model->packed16,
-                                   model->table(), model->grid, a, partials, lpart, ga, nb, s);
-    if (e == hipSuccess)
-        e = launch_reduce_grad_n(kHashMlp, partials, lpart, nb, 1.0f / scale, 1.0f / (3.0f * (float)queries.count),
-                                 grad, loss, model->bad, s);
-    if (e == hipSuccess) e = launch_grid_acc_finish(ga, gtab, nt, 1.0f / scale, model->bad, s);
-    return hip_st(e);
+static HashAdam hash_adam_args(const nirc_hash_model *m) {
+    return HashAdam{m->master + kHashMlp, m->m + kHashMlp, m->v + kHashMlp, m->step, m->bad, m->cfg.lr, m->cfg.beta1,
+                    m->cfg.beta2, m->cfg.adam_eps};
+}
+
+static hipError_t hash_repack_commit(nirc_hash_model *model, hipStream_t s) {
+    return model->cfg.precision == NIRC_FP32
+               ? launch_hash_pack32(model->packed32(), model->master, s, model->step, model->flags, model->bad)
+               : launch_hash_pack16(model->packed16, model->master, model->cfg.precision, s, model->step, model->flags,
+                                    model->bad);
 }
 
 static hipError_t hash_adam(nirc_hash_model *model, const float *grad, hipStream_t s) {
     hipError_t e = launch_adam_n(model->np, model->master, model->m, model->v, grad, model->step, model->bad,
                                  model->cfg.lr, model->cfg.beta1, model->cfg.beta2, model->cfg.adam_eps, s);
+    return e == hipSuccess ? hash_repack_commit(model, s) : e;
+}
+
+// Loss and gradient into grad/loss, the step's `bad` flag raised on a non-finite value; with `adam`
+// the whole step (the grid's part of grad is then not written).
+static nirc_status hash_grad_into(nirc_hash_model *model, const nirc_points &points, const nirc_queries &queries,
+                                  const float *target, float *grad, float *loss, uint32_t *err, bool adam,
+                                  hipStream_t s) {
+    nirc_status st = check_points_h(points);
+    if (st == NIRC_OK) st = check_queries_h(queries, points);
+    if (st != NIRC_OK) return st;
+    if (queries.count < 1 || !grad || !target) return NIRC_ERR_INVALID_ARG;
+    const int64_t B = queries.count;
+    const int nb = train_blocks16(B);
+    // a batch beyond the workspace's (which the partials may still suit) runs in parts that fit
+    int64_t part = B;
+    while (part > 64 && model->ws_bytes < HashWork(model->np, nb, part).samples) part = (part / 2 + 63) / 64 * 64;
+    const HashWork wl(model->np, nb, part);
+    if (!model->ws || model->ws_bytes < wl.samples) return NIRC_ERR_WORKSPACE;
+    float *partials = (float *)(model->ws + wl.partials);
+    float *lpart = (float *)(model->ws + wl.loss_partials);
+    const HashTrainBufs bufs = wl.bufs(model->ws);
+    const int64_t nt = model->np - kHashMlp;
+    float *gtab = grad + kHashMlp;
+    const GridAcc ga{(unsigned long long *)(model->ws + wl.gacc), (uint32_t *)(model->ws + wl.gflag)};
+    HashScatterPlan plan;
+    memset(&plan, 0, sizeof(plan));
+    const bool sliced = part == B && hash_scatter_plan(model->grid, B, &plan);
+    const float inv = 1.0f / (model->cfg.loss_scale * (float)B);
+    // sums reach 2^27: below 2^90 the scale cannot make a gradient entry infinite, so that the
+    // step's flags are complete before the slices' Adam
+    const bool fused = adam && sliced && inv < 0x1p90f;
+    const bool exact = model->cfg.precision == NIRC_FP32;
+    hipError_t e = hipSuccess;
+    if (!sliced) e = launch_fill_u32((uint32_t *)ga.acc, 2 * nt, 0u, s);
+    for (int64_t b0 = 0; b0 < B && e == hipSuccess; b0 += part) {
+        const int64_t n = B - b0 < part ? B - b0 : part;
+        // queries without point indices name points b0.. themselves
+        const nirc_queries qp{queries.wx + b0, queries.wy + b0, queries.wz + b0,
+                              queries.point ? queries.point + b0 : nullptr, n};
+        nirc_points pp = points;
+        if (!queries.point) pp = nirc_points{points.px + b0, points.py + b0, points.pz + b0, points.nx + b0,
+                                             points.ny + b0, points.nz + b0, points.rough + b0, n};
+        const Queries q = queries_of(qp, err);
+        // the batch size is folded into the loss scale (per-sample deltas near unit magnitude in the
+        // 16-bit operands; the FP32 kernel takes the same convention); the reductions divide it out
+        const TrainArgs a{target + 3 * b0, nullptr, model->cfg.loss_eps, model->cfg.loss_scale * (float)n,
+                          model->cfg.loss, nullptr, 0};
+        e = launch_hash_prep(pts_of(pp), q, model->table(), model->grid, plan, sliced, exact, b0 == 0, bufs, ga, s);
+        if (e == hipSuccess)
+            e = model->cfg.precision == NIRC_FP32
+                    ? launch_hash_grad32(q, model->packed32(), model->grid, a, bufs, partials, lpart, ga, nb, b0 > 0, s)
+                    : launch_hash_grad(model->cfg.precision, q, model->packed16, model->grid, a, bufs, partials, lpart,
+                                       ga, nb, b0 > 0, s);
+        if (e == hipSuccess && !sliced) e = launch_hash_scatter_atomic(model->grid, bufs, ga, n, s);
+    }
     if (e == hipSuccess)
-        e = model->cfg.precision == NIRC_FP32
-                ? launch_hash_pack32(model->packed32(), model->master, s, model->step, model->flags, model->bad)
-                : launch_hash_pack16(model->packed16, model->master, model->cfg.precision, s, model->step,
-                                     model->flags, model->bad);
-    return e;
+        e = launch_reduce_grad_n(kHashMlp, partials, lpart, nb, inv, 1.0f / (3.0f * (float)B), grad, loss, model->bad, s);
+    if (e == hipSuccess)
+        e = sliced ? launch_hash_scatter(model->grid, plan, bufs, ga, B, inv, grad, gtab, hash_adam_args(model), fused, s)
+                   : launch_grid_acc_finish(ga, gtab, nt, inv, model->bad, s);
+    if (e == hipSuccess && adam) e = fused ? hash_repack_commit(model, s) : hash_adam(model, grad, s);
+    return hip_st(e);
 }
 
 nirc_status nirc_hash_loss_grad(nirc_hash_model *model, nirc_points points, nirc_queries queries,
                                 const float *target, float *grad, float *loss, void *stream) {
     if (!model) return NIRC_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
-    nirc_status st = hash_grad_into(model, points, queries, target, grad, loss, model->flags, s);
+    nirc_status st = hash_grad_into(model, points, queries, target, grad, loss, model->flags, false, s);
     if (st != NIRC_OK) return st;
     // a standalone gradient does not start a step: clear the step's flag again
     return hip_st(launch_fill_u32(model->bad, 1, 0u, s));
@@ -322,12 +365,10 @@ nirc_status nirc_hash_train_step(nirc_hash_model *model, nirc_points points, nir
     if (!model) return NIRC_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     if (!model->ws) return NIRC_ERR_WORKSPACE;
-    const HashWork wl(model->np, train_blocks16(queries.count > 0 ? queries.count : 1));
-    if (model->ws_bytes < wl.total) return NIRC_ERR_WORKSPACE;
-    float *grad = (float *)(model->ws + wl.grad);
-    nirc_status st = hash_grad_into(model, points, queries, target, grad, loss, model->bad, s);
-    if (st != NIRC_OK) return st;
-    return hip_st(hash_adam(model, grad, s));
+    // the reduced gradient's place does not depend on how much of the batch fits
+    const HashWork wl(model->np, train_blocks16(queries.count > 0 ? queries.count : 1), 0);
+    if (model->ws_bytes < wl.samples) return NIRC_ERR_WORKSPACE;
+    return hash_grad_into(model, points, queries, target, (float *)(model->ws + wl.grad), loss, model->bad, true, s);
 }
 
 nirc_status nirc_hash_train_frame(nirc_hash_model *model, nirc_points points, const nirc_lobes *field,

@@ -968,31 +968,24 @@ hipError_t launch_scale_check(float *g, int64_t n, float scale, uint32_t *bad, h
 
 // ------------------------------------------------------------------------------------------
 // The hash-grid model in FP32 (width 64): k_grad_f32's two phases with the 64 grid / SH / phi
-// inputs staged as rows [canonical input][sample] for the first layer's weight gradient.  Each
-// sample's gradient with respect to its 24 grid values (W1_grid^T delta1, from the transposed
-// TS32 section) is kept in registers through phase 2 and then scattered into the grid-entry
-// gradient by 64-bit fixed-point integer atomic adds (grid_acc_add; the 16 values of one
-// (sample, level) in 16 consecutive lanes, x neighbours in adjacent lane pairs, zero values
-// skipped), staged through LDS that phase 2 has released.
+// inputs staged as rows [canonical input][sample] for the first layer's weight gradient, the grid
+// values blended beforehand (bufs.vals).  Each sample's gradient with respect to its 24 grid values
+// (W1_grid^T delta1, from the transposed TS32 section) goes to bufs.dvals for the grid-entry sums.
 namespace {
-constexpr int kScatRow32 = 28;   // per sample: 24 grid-value gradients, position, pad
 struct HashGrad32Lds {
     static constexpr int kH = 4 * 64 * kStride;
     static constexpr int kD = 4 * 64 * kStride;
     static constexpr int kD5 = 4 * kStride;
     static constexpr int kE = kHashIn * kStride;
     static constexpr int kTotal = kH + kD + kD5 + kE;
-    static_assert(kTrainWaves * 16 * kScatRow32 <= kH, "scatter staging reuses the activation rows");
 };
 }  // namespace
 
-__global__ __launch_bounds__(kTrainWaves * 64) void k_hash_grad_f32(Points pts, Queries q,
-                                                                    const float *__restrict__ packed,
-                                                                    const float2 *__restrict__ table,
+__global__ __launch_bounds__(kTrainWaves * 64) void k_hash_grad_f32(Queries q, const float *__restrict__ packed,
                                                                     HashGridArgs grid, TrainArgs args,
-                                                                    float *__restrict__ partials,
+                                                                    HashTrainBufs bufs, float *__restrict__ partials,
                                                                     float *__restrict__ loss_partials,
-                                                                    GridAcc gacc) {
+                                                                    GridAcc gacc, bool add) {
     constexpr int W = 64, MT = 4, KQ = 4;
     using S = HashGrad32Lds;
     __shared__ f32x4 smem4[(S::kTotal + 3) / 4];
@@ -1007,7 +1000,7 @@ __global__ __launch_bounds__(kTrainWaves * 64) void k_hash_grad_f32(Points pts, 
     __syncthreads();
 
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
-    const int64_t B = q.count;
+    const int64_t B = q.count, stride = hash_level_stride(B);
     const bool rel = args.loss_kind == NIRC_LOSS_REL_L2;
     // the host passes loss_scale * B: k = 2 loss_scale / 3 per sample
     const float kscale = 2.0f * args.loss_scale / (3.0f * (float)B);
@@ -1025,22 +1018,21 @@ __global__ __launch_bounds__(kTrainWaves * 64) void k_hash_grad_f32(Points pts, 
     const int64_t n_chunks = (B + kChunk - 1) / kChunk;
     for (int64_t chunk = blockIdx.x; chunk < n_chunks; chunk += gridDim.x) {
         // ---------------- phase 1: forward + backward of this wave's 16 samples
-        f32x4 de[2];   // rows 16 m + 4 g + i of W1_grid^T delta1 (grid values 2 k + f of level k)
-        float x0, x1, x2;
-        bool valid;
         {
             const float *pk = opaque(packed);
             const int s = 16 * wave + col;
             const int64_t b = chunk * kChunk + s;
-            valid = b < B;
+            const bool valid = b < B;
             const int64_t bi = valid ? b : B - 1;
-            const int64_t p = query_point(q, pts, bi);
-            const float xs[7] = {pts.px[p], pts.py[p], pts.pz[p], pts.nx[p], pts.ny[p], pts.nz[p], pts.rough[p]};
-            x0 = xs[0];
-            x1 = xs[1];
-            x2 = xs[2];
+            const f32x4 xa = *(const f32x4 *)(bufs.attr + 8 * bi), xb = *(const f32x4 *)(bufs.attr + 8 * bi + 4);
+            const float xs[7] = {xa[0], xa[1], xa[2], xa[3], xb[0], xb[1], xb[2]};
             float v[6], ph[4], sd[8];
-            hash_values6(s_lv, grid.tmask, table, xs[0], xs[1], xs[2], g, v);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const float2 t = bufs.vals[(3 * g + k) * stride + bi];
+                v[2 * k] = t.x;
+                v[2 * k + 1] = t.y;
+            }
             hash_phi4(xs[3], xs[4], xs[5], xs[6], g, ph);
             hash_dir_values_f32(q.wx[bi], q.wy[bi], q.wz[bi], g, sd);
             // canonical input rows: grid 6 g + k, SH 24 + 4 k + g, phi 49 + 4 j + g
@@ -1168,15 +1160,25 @@ __global__ __launch_bounds__(kTrainWaves * 64) void k_hash_grad_f32(Points pts, 
                     }
             }
             // d = delta1; the grid-value gradient of this sample (column col)
+            // (rows 16 m + 4 g + i of W1_grid^T delta1: the two values of levels 8 m + 2 g and 8 m + 2 g + 1)
             const float *sec = pk + kHash32TS;
 #pragma unroll
             for (int m = 0; m < 2; ++m) {
-                de[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+                f32x4 de = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int kq = 0; kq < KQ; ++kq) {
                     const f32x4 a = *(const f32x4 *)(sec + ((m * KQ + kq) * 64 + lane) * 4);
 #pragma unroll
-                    for (int kk = 0; kk < 4; ++kk) de[m] = mfma4(a[kk], d[kq][kk], de[m]);
+                    for (int kk = 0; kk < 4; ++kk) de = mfma4(a[kk], d[kq][kk], de);
+                }
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const int level = 8 * m + 2 * g + k;
+                    if (valid && level < kHashLevels) {
+                        grid_grad_check(gacc, de[2 * k], xs[0], xs[1], xs[2], s_lv[level].res);
+                        grid_grad_check(gacc, de[2 * k + 1], xs[0], xs[1], xs[2], s_lv[level].res);
+                        bufs.dvals[level * stride + b] = make_float2(de[2 * k], de[2 * k + 1]);
+                    }
                 }
             }
         }
@@ -1213,54 +1215,24 @@ __global__ __launch_bounds__(kTrainWaves * 64) void k_hash_grad_f32(Points pts, 
             }
         }
         __syncthreads();
-        // ---------------- scatter of the grid-value gradients (staging in the released rows)
-        {
-            float *sg = smem + wave * (16 * kScatRow32);
-#pragma unroll
-            for (int m = 0; m < 2; ++m)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int k = 16 * m + 4 * g + i;
-                    if (k < 24) sg[col * kScatRow32 + k] = valid ? de[m][i] : 0.0f;
-                }
-            if (g == 0) {
-                sg[col * kScatRow32 + 24] = x0;
-                sg[col * kScatRow32 + 25] = x1;
-                sg[col * kScatRow32 + 26] = x2;
-            }
-            wave_sync();
-            const int qd = lane >> 4, corner = (lane & 15) >> 1, f = lane & 1;
-#pragma unroll 4
-            for (int it = 0; it < 16 * kHashLevels / 4; ++it) {
-                const int pr = 4 * it + qd;
-                const int smp = pr / kHashLevels, level = pr - kHashLevels * smp;
-                const float *row = sg + smp * kScatRow32;
-                const float dv = row[2 * level + f];
-                const HashLevel lv = s_lv[level];
-                const HashCell cell = hash_cell(row[24], row[25], row[26], lv.res);
-                float w;
-                const uint32_t e = hash_entry(lv, grid.tmask, cell, corner, w);
-                grid_acc_add(gacc, 2 * (size_t)e + f, w * dv);
-            }
-        }
-        __syncthreads();   // the next chunk's rows overwrite the staging
     }
 
     float *out = partials + (int64_t)blockIdx.x * kHashMlp;
+    auto put = [&](int64_t i, float v) { out[i] = add ? out[i] + v : v; };
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) out[(int64_t)(16 * mt + 4 * g + i) * kHashIn + 16 * wave + col] = g1[mt][i];
+        for (int i = 0; i < 4; ++i) put((int64_t)(16 * mt + 4 * g + i) * kHashIn + 16 * wave + col, g1[mt][i]);
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                out[W * kHashIn + a * W * W + (int64_t)(16 * mt + 4 * g + i) * W + 16 * wave + col] = gh[a][mt][i];
+                put(W * kHashIn + a * W * W + (int64_t)(16 * mt + 4 * g + i) * W + 16 * wave + col, gh[a][mt][i]);
     if (g == 0) {
 #pragma unroll
-        for (int i = 0; i < 3; ++i) out[W * kHashIn + 3 * W * W + (int64_t)i * W + 16 * wave + col] = g5[i];
+        for (int i = 0; i < 3; ++i) put(W * kHashIn + 3 * W * W + (int64_t)i * W + 16 * wave + col, g5[i]);
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) loss_acc += __shfl_xor(loss_acc, d, 64);
@@ -1269,16 +1241,16 @@ __global__ __launch_bounds__(kTrainWaves * 64) void k_hash_grad_f32(Points pts, 
     if (threadIdx.x == 0) {
         float t = 0.0f;
         for (int w = 0; w < kTrainWaves; ++w) t += sLoss[w];
-        loss_partials[blockIdx.x] = t;
+        loss_partials[blockIdx.x] = add ? loss_partials[blockIdx.x] + t : t;
     }
 }
 
-hipError_t launch_hash_grad32(const Points &pts, const Queries &q, const float *packed, const float *table,
-                              const HashGridArgs &grid, TrainArgs a, float *partials, float *loss_partials,
-                              GridAcc gacc, int nblocks, hipStream_t s) {
+hipError_t launch_hash_grad32(const Queries &q, const float *packed, const HashGridArgs &grid, TrainArgs a,
+                              const HashTrainBufs &bufs, float *partials, float *loss_partials, GridAcc gacc,
+                              int nblocks, bool add, hipStream_t s) {
     if (!a.target) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_hash_grad_f32, dim3(nblocks), dim3(kTrainWaves * 64), 0, s, pts, q, packed,
-                       (const float2 *)table, grid, a, partials, loss_partials, gacc);
+    hipLaunchKernelGGL(k_hash_grad_f32, dim3(nblocks), dim3(kTrainWaves * 64), 0, s, q, packed, grid, a, bufs, partials,
+                       loss_partials, gacc, add);
     return hipGetLastError();
 }
 

@@ -725,13 +725,10 @@ hipError_t launch_train_step_multi(const TrainDesc *desc, int prec, uint32_t ste
 
 // ------------------------------------------------------------------------------------------
 // The hash-grid model (width 64): the same two phases as k_grad_h16 with the 64 grid / SH / phi
-// inputs.  In addition, after the first layer's delta, each sample's gradient with respect to
-// its 24 grid values (W1_grid^T delta1, from the TS section) is scattered into the grid-entry
-// gradient: each of the 8 corners of the sample's cell at a level receives its trilinear weight
-// times the level's two values, by 64-bit fixed-point integer atomic adds (grid_acc_add; zero
-// values are skipped), so that the sums do not depend on the order of the adds.
+// inputs, the grid values blended beforehand (bufs.vals).  In addition, after the first layer's
+// delta, each sample's gradient with respect to its 24 grid values (W1_grid^T delta1, from the TS
+// section) goes to bufs.dvals for the grid-entry sums.
 namespace {
-constexpr int kScatRow = 28;   // per sample: 24 grid-value gradients, position, pad
 struct HashGrad16Lds {
     static constexpr int kH = 4 * 64 * kRow16;
     static constexpr int kD = 4 * 64 * kRow16;
@@ -742,18 +739,15 @@ struct HashGrad16Lds {
 }  // namespace
 
 template <int PREC>
-__global__ __launch_bounds__(kWaves16 * 64) void k_hash_grad_h16(Points pts, Queries q,
-                                                                 const uint16_t *__restrict__ packed,
-                                                                 const float2 *__restrict__ table, HashGridArgs grid,
-                                                                 TrainArgs args, float *__restrict__ partials,
-                                                                 float *__restrict__ loss_partials,
-                                                                 GridAcc gacc) {
+__global__ __launch_bounds__(kWaves16 * 64) void k_hash_grad_h16(Queries q, const uint16_t *__restrict__ packed,
+                                                                 HashGridArgs grid, TrainArgs args, HashTrainBufs bufs,
+                                                                 float *__restrict__ partials,
+                                                                 float *__restrict__ loss_partials, GridAcc gacc, bool add) {
     constexpr int MT = 4, KB = 2, W = 64;
     using S = HashGrad16Lds;
     __shared__ u32x4 smem4[(S::kTotal + 7) / 8];
     __shared__ float sLoss[kWaves16];
     __shared__ HashLevel s_lv[kHashLevels];
-    __shared__ float sScat[kWaves16 * 16 * kScatRow];
     uint16_t *smem = (uint16_t *)smem4;
     uint16_t *sH = smem;
     uint16_t *sD = sH + S::kH;
@@ -763,7 +757,7 @@ __global__ __launch_bounds__(kWaves16 * 64) void k_hash_grad_h16(Points pts, Que
     __syncthreads();
 
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
-    const int64_t B = q.count;
+    const int64_t B = q.count, stride = hash_level_stride(B);
     const bool rel = args.loss_kind == NIRC_LOSS_REL_L2;
     // the host passes loss_scale * B: k = 2 loss_scale / 3 per sample
     const float kscale = 2.0f * args.loss_scale / (3.0f * (float)B);
@@ -786,13 +780,19 @@ __global__ __launch_bounds__(kWaves16 * 64) void k_hash_grad_h16(Points pts, Que
             const int64_t b = chunk * kChunk16 + s;
             const bool valid = b < B;
             const int64_t bi = valid ? b : B - 1;
-            const int64_t p = query_point(q, pts, bi);
-            const float xs[7] = {pts.px[p], pts.py[p], pts.pz[p], pts.nx[p], pts.ny[p], pts.nz[p], pts.rough[p]};
+            const f32x4 xa = *(const f32x4 *)(bufs.attr + 8 * bi), xb = *(const f32x4 *)(bufs.attr + 8 * bi + 4);
+            const float xs[7] = {xa[0], xa[1], xa[2], xa[3], xb[0], xb[1], xb[2]};
 
             // inputs: operands for the MFMAs and 16-bit rows [canonical input][sample] for dW1
             u32x4 b0, b1;
-            float v[6], ph[15];
-            hash_surface_operands<PREC>(s_lv, grid.tmask, table, xs, g, b0, b1, v, ph);
+            float v[6];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const float2 t = bufs.vals[(3 * g + k) * stride + bi];
+                v[2 * k] = t.x;
+                v[2 * k + 1] = t.y;
+            }
+            hash_pack_surface<PREC>(xs, g, v, b0, b1);
             float Y[25];
             sh25(q.wx[bi], q.wy[bi], q.wz[bi], Y);
             const u32x4 bd0 = sh_operand_of<PREC>(Y, g);
@@ -909,39 +909,20 @@ __global__ __launch_bounds__(kWaves16 * 64) void k_hash_grad_h16(Points pts, Que
                     de[mt] = mfma16<PREC>(*(const u32x4 *)(sec + ((mt * KB + kb) * 64 + lane) * 8), db1[kb],
                                           de[mt]);
             }
-            // scatter.  The L2 performs float atomics per cache line and instruction, so the 16
-            // values of one (sample, level) - 8 corners x 2 features - go to 16 consecutive lanes,
-            // corners along x (neighbouring entries: dense rows, and the hash's x multiplier is 1)
-            // in consecutive lane pairs; one instruction covers 4 (sample, level) pairs.  The
-            // wave's gradients and positions are staged in LDS first.
-            float *sg = sScat + wave * (16 * kScatRow);
+            // (lane (g, col): levels 8 mt + 2 g and 8 mt + 2 g + 1 of sample col)
+            if (valid) {
 #pragma unroll
-            for (int mt = 0; mt < 2; ++mt)
+                for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int k = 16 * mt + 4 * g + i;
-                    if (k < 24) sg[col * kScatRow + k] = valid ? de[mt][i] : 0.0f;
-                }
-            if (g == 0) {
-                sg[col * kScatRow + 24] = xs[0];
-                sg[col * kScatRow + 25] = xs[1];
-                sg[col * kScatRow + 26] = xs[2];
-            }
-            wave_sync();
-            {
-                const int q = lane >> 4, corner = (lane & 15) >> 1, f = lane & 1;
-#pragma unroll 4
-                for (int it = 0; it < 16 * kHashLevels / 4; ++it) {
-                    const int pr = 4 * it + q;
-                    const int smp = pr / kHashLevels, level = pr - kHashLevels * smp;
-                    const float *row = sg + smp * kScatRow;
-                    const float d = row[2 * level + f];
-                    const HashLevel lv = s_lv[level];
-                    const HashCell cell = hash_cell(row[24], row[25], row[26], lv.res);
-                    float w;
-                    const uint32_t e = hash_entry(lv, grid.tmask, cell, corner, w);
-                    grid_acc_add(gacc, 2 * (size_t)e + f, w * d);
-                }
+                    for (int k = 0; k < 2; ++k) {
+                        const int level = 8 * mt + 2 * g + k;
+                        if (level < kHashLevels) {
+                            const float d0 = de[mt][2 * k], d1 = de[mt][2 * k + 1];
+                            grid_grad_check(gacc, d0, xs[0], xs[1], xs[2], s_lv[level].res);
+                            grid_grad_check(gacc, d1, xs[0], xs[1], xs[2], s_lv[level].res);
+                            bufs.dvals[level * stride + b] = make_float2(d0, d1);
+                        }
+                    }
             }
         }
         __syncthreads();
@@ -977,20 +958,21 @@ __global__ __launch_bounds__(kWaves16 * 64) void k_hash_grad_h16(Points pts, Que
     }
 
     float *out = partials + (int64_t)blockIdx.x * kHashMlp;
+    auto put = [&](int64_t i, float v) { out[i] = add ? out[i] + v : v; };
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) out[(int64_t)(16 * mt + 4 * g + i) * kHashIn + 16 * wave + col] = g1[mt][i];
+        for (int i = 0; i < 4; ++i) put((int64_t)(16 * mt + 4 * g + i) * kHashIn + 16 * wave + col, g1[mt][i]);
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                out[W * kHashIn + a * W * W + (int64_t)(16 * mt + 4 * g + i) * W + 16 * wave + col] = gh[a][mt][i];
+                put(W * kHashIn + a * W * W + (int64_t)(16 * mt + 4 * g + i) * W + 16 * wave + col, gh[a][mt][i]);
     if (g == 0) {
 #pragma unroll
-        for (int i = 0; i < 3; ++i) out[W * kHashIn + 3 * W * W + (int64_t)i * W + 16 * wave + col] = g5[i];
+        for (int i = 0; i < 3; ++i) put(W * kHashIn + 3 * W * W + (int64_t)i * W + 16 * wave + col, g5[i]);
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) loss_acc += __shfl_xor(loss_acc, d, 64);
@@ -999,21 +981,20 @@ __global__ __launch_bounds__(kWaves16 * 64) void k_hash_grad_h16(Points pts, Que
     if (threadIdx.x == 0) {
         float t = 0.0f;
         for (int w = 0; w < kWaves16; ++w) t += sLoss[w];
-        loss_partials[blockIdx.x] = t;
+        loss_partials[blockIdx.x] = add ? loss_partials[blockIdx.x] + t : t;
     }
 }
 
-hipError_t launch_hash_grad(int prec, const Points &pts, const Queries &q, const uint16_t *packed, const float *table,
-                            const HashGridArgs &grid, TrainArgs a, float *partials, float *loss_partials,
-                            GridAcc gacc, int nblocks, hipStream_t s) {
+hipError_t launch_hash_grad(int prec, const Queries &q, const uint16_t *packed, const HashGridArgs &grid, TrainArgs a,
+                            const HashTrainBufs &bufs, float *partials, float *loss_partials, GridAcc gacc,
+                            int nblocks, bool add, hipStream_t s) {
     if (!a.target) return hipErrorInvalidValue;
-    const float2 *t2 = (const float2 *)table;
     if (prec == NIRC_BF16)
-        hipLaunchKernelGGL((k_hash_grad_h16<NIRC_BF16>), dim3(nblocks), dim3(kWaves16 * 64), 0, s, pts, q, packed, t2,
-                           grid, a, partials, loss_partials, gacc);
+        hipLaunchKernelGGL((k_hash_grad_h16<NIRC_BF16>), dim3(nblocks), dim3(kWaves16 * 64), 0, s, q, packed, grid, a,
+                           bufs, partials, loss_partials, gacc, add);
     else if (prec == NIRC_FP16)
-        hipLaunchKernelGGL((k_hash_grad_h16<NIRC_FP16>), dim3(nblocks), dim3(kWaves16 * 64), 0, s, pts, q, packed, t2,
-                           grid, a, partials, loss_partials, gacc);
+        hipLaunchKernelGGL((k_hash_grad_h16<NIRC_FP16>), dim3(nblocks), dim3(kWaves16 * 64), 0, s, q, packed, grid, a,
+                           bufs, partials, loss_partials, gacc, add);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
