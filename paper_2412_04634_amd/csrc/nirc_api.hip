@@ -62,7 +62,7 @@ struct WorkLayout {
 
 int64_t var_rows(const nirc_config &cfg, int64_t batch) { return cfg.loss == NIRC_LOSS_VAR ? batch : 0; }
 
-// Gradient-partial slabs of a batch: the grid of the precision's gradient kernel.  Every
+// Gradient-partial slabs of a batch: at least the workgroups of the model's gradient kernel.  Every
 // workspace layout of a model (sizing, the partials, the reduced gradient after them) takes its
 // count from here, so that the layouts agree whatever the kernels' rounds are.
 int grad_blocks(int32_t precision, int64_t batch) {
@@ -391,9 +391,10 @@ static nirc_status grad_into(nirc_model *model, const nirc_points &points, const
     if (st != NIRC_OK) return st;
     if (queries.count < 1 || !grad) return NIRC_ERR_INVALID_ARG;
     const bool h16 = model->packed16 != nullptr;
-    const int nb = grad_blocks(model->cfg.precision, queries.count);
+    const int slabs = grad_blocks(model->cfg.precision, queries.count);
+    const int nb = h16 ? grad_blocks16(model->W, queries.count) : slabs;
     const bool var = target && model->cfg.loss == NIRC_LOSS_VAR;
-    const WorkLayout wl(model->W, nb, var ? queries.count : 0);
+    const WorkLayout wl(model->W, slabs, var ? queries.count : 0);
     if (!ws || ws_bytes < wl.total) return NIRC_ERR_WORKSPACE;
     float *partials = (float *)(ws + wl.partials);
     float *lpart = (float *)(ws + wl.loss_partials);
@@ -654,8 +655,8 @@ nirc_status nirc_train_list_build(const nirc_train_request *requests, int32_t n,
             if (requests[j].model == m) return NIRC_ERR_INVALID_ARG;   // one step of a model at a time
         if (check_points(r.points) != NIRC_OK || r.points.count < 1) return NIRC_ERR_INVALID_ARG;
         if (r.batch < 1 || r.batch > max_batch) return NIRC_ERR_INVALID_ARG;
-        const int nb = grad_blocks(m->cfg.precision, r.batch);
-        const WorkLayout wl(m->W, nb, 0, r.batch);
+        const int nb = grad_blocks16(m->W, r.batch);
+        const WorkLayout wl(m->W, grad_blocks(m->cfg.precision, r.batch), 0, r.batch);
         if (!m->ws || m->ws_bytes < wl.total) return NIRC_ERR_WORKSPACE;
         TrainReq &t = d->req[i];
         t.pts = to_points(r.points);

@@ -290,11 +290,12 @@ static nirc_status hash_grad_into(nirc_hash_model *model, const nirc_points &poi
     if (st != NIRC_OK) return st;
     if (queries.count < 1 || !grad || !target) return NIRC_ERR_INVALID_ARG;
     const int64_t B = queries.count;
-    const int nb = train_blocks16(B);
+    const int slabs = train_blocks16(B);
+    const int nb = model->cfg.precision == NIRC_FP32 ? slabs : grad_blocks16(64, B);
     // a batch beyond the workspace's (which the partials may still suit) runs in parts that fit
     int64_t part = B;
-    while (part > 64 && model->ws_bytes < HashWork(model->np, nb, part).samples) part = (part / 2 + 63) / 64 * 64;
-    const HashWork wl(model->np, nb, part);
+    while (part > 64 && model->ws_bytes < HashWork(model->np, slabs, part).samples) part = (part / 2 + 63) / 64 * 64;
+    const HashWork wl(model->np, slabs, part);
     if (!model->ws || model->ws_bytes < wl.samples) return NIRC_ERR_WORKSPACE;
     float *partials = (float *)(model->ws + wl.partials);
     float *lpart = (float *)(model->ws + wl.loss_partials);

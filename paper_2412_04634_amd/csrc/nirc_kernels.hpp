@@ -557,7 +557,8 @@ __device__ inline void commit_step(int64_t *step, uint32_t *flags, uint32_t *bad
 constexpr int kFrBlocks = 256;
 hipError_t launch_residual_mean(const float *y, const float *t, int64_t B, float *part, float *fr, hipStream_t s);
 int train_blocks(int64_t batch);     // workgroups used by the FP32 gradient kernel for a batch
-int train_blocks16(int64_t batch);   // workgroups used by the 16-bit gradient kernel
+int train_blocks16(int64_t batch);   // partial slabs a 16-bit model's workspace holds for a batch
+int grad_blocks16(int W, int64_t batch);   // workgroups (slabs written) of the 16-bit gradient kernel
 hipError_t launch_grad_partials16(int W, int prec, const Points &pts, const Queries &q, const void *packed,
                                   TrainArgs a, float *partials, float *loss_partials, int nblocks, hipStream_t s);
 hipError_t launch_grad_partials(int W, const Points &pts, const Queries &q, const float *packed,

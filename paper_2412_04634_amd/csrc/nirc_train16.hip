@@ -10,18 +10,14 @@ namespace nirc {
 
 namespace {
 
-constexpr int kWaves16 = 4;
-constexpr int kChunk16 = 16 * kWaves16;   // samples per round (two 32-sample K-blocks)
-constexpr int kRow16 = kChunk16 + 8;      // LDS row stride in 16-bit elements (144 B)
+// Width 64: workgroups of 8 waves, rounds of 128 samples (four 32-sample K-blocks).
+constexpr int kWaves64 = 8;
+constexpr int kChunk64 = 16 * kWaves64;
 
-template <int W>
-struct Grad16Lds {
-    static constexpr int kH = 4 * W * kRow16;    // h1..h4 (after ReLU)  [layer][neuron][sample]
-    static constexpr int kD = 4 * W * kRow16;    // delta1..delta4       [layer][neuron][sample]
-    static constexpr int kD5 = 4 * kRow16;       // output-layer delta, rows 0..3
-    static constexpr int kE = kFeat * kRow16;    // input features      [canonical feature][sample]
-    static constexpr int kTotal = kH + kD + kD5 + kE;   // 16-bit elements
-};
+// Width 128: workgroups of 4 waves, rounds of 64 samples (two 32-sample K-blocks).
+constexpr int kWaves16 = 4;
+constexpr int kChunk16 = 16 * kWaves16;
+constexpr int kRow16 = kChunk16 + 8;      // LDS row stride in 16-bit elements (144 B)
 
 template <int PREC>
 __device__ __forceinline__ uint16_t to16(float x) {
@@ -98,191 +94,264 @@ __device__ __forceinline__ void load_point16(const Points &pts, const Queries &q
 
 }  // namespace
 
-// One workgroup of 4 waves processes rounds of 64 samples.  Phase 1: each wave takes 16 samples
-// through the 16-bit forward chain (packed weights read from global memory) and back through
-// the transposed sections, and stages the ReLU outputs, the deltas and the input features as
-// 16-bit rows [neuron][sample] in LDS (the ReLU masks come from the 16-bit activations).
-// Phase 2: each wave owns the same weight-gradient tiles as in the FP32 kernel and adds the
-// round with 16x16x32 MFMAs whose K dimension is the sample index.
-// Block `blk` of `nblk` over the batch (chunks blk, blk + nblk, ...): its partial gradient goes to
-// `out` [n_params], its loss partial to *loss_out.  smem: Grad16Lds<W>::kTotal 16-bit elements;
-// sLoss: kWaves16 floats.  Ends after a workgroup barrier, so a caller may run the next block on
-// the same LDS.  PLAIN: the caller guarantees the common case (targets given, relative L2 of
-// eq. 12, no residual-variance mean, exp outputs), so the general loss arithmetic is compiled out.
-template <int W, int PREC, bool PLAIN = false>
-__device__ __forceinline__ void grad16_block(const Points &pts, const Queries &q, const uint16_t *packed,
-                                             const TrainArgs &args, float *out, float *loss_out, int64_t blk,
-                                             int64_t nblk, uint16_t *smem, float *sLoss) {
-    static_assert(W == 64, "gradient kernel is laid out for width 64");
-    constexpr H16Layout L{W};
-    constexpr int MT = W / 16, KB = W / 32;
-    using S = Grad16Lds<W>;
-    uint16_t *sH = smem;
-    uint16_t *sD = sH + S::kH;
-    uint16_t *sD5 = sD + S::kD;
-    uint16_t *sE = sD5 + S::kD5;
+// ------------------------------------------------------------------------------------------
+// Width 64.  A weight gradient dW = sum_s delta_s h_s^T is an MFMA whose K dimension is the sample, so
+// its operands hold a neuron per lane and samples in registers, while the layer chain holds a sample
+// per lane and neurons in registers.  The change of sides is an MFMA too: with the chained
+// activations as the A operand, the product with a 0/1 selection matrix leaves lane (g, c) with neuron
+// c of samples 4 g + i - exactly the value each 16-bit operand holds - and the rows of two waves (32
+// samples in the order 4 g + i, 16 + 4 g + i, the same for both factors) make one operand.
+//
+// A workgroup of 8 waves takes rounds of 128 samples, 16 per wave, forward and back, layer by layer
+// from the last: each wave turns its delta_{l+1} and h_l and puts them in LDS (8-byte stores in
+// operand order), and after one barrier each wave adds its own tiles of dW_{l+1} over the round's four
+// K-blocks while it goes on to delta_l (two buffers, so that a layer needs one barrier).
+// The forward weights are in LDS (51 KB), the transposed ones (28 KB, one CU's L1) in global memory.
+// Bound by LDS and VALU work together: per wave and round 78 MFMAs forward and back, 43 to turn the
+// operands, 46 for the gradient, against ~600 VALU instructions.
+// (Before, four waves staged every value by a two-byte store as [neuron][sample] rows and read all
+// weights from L2: 36 us for a 65,536-sample BF16 gradient.)
+//
+// ENC 0: the frequency input (10 input tiles of 16 features).  ENC 1: the hash-grid model's 64 inputs
+// (6 tiles: two per K-block of its surface and direction operands; unused columns are not written).
+template <int ENC>
+struct Grad64 {
+    static constexpr int kIn = ENC == 0 ? 10 : 6;           // input tiles
+    static constexpr int kInKb = ENC == 0 ? 6 : 3;          // input operands (K-blocks)
+    static constexpr int kOwnIn = (4 * kIn + 7) / 8;        // W1 tiles per wave
+    // forward sections S, D, H0..H2, O: contiguous in both layouts
+    static constexpr int kFwd = ENC == 0 ? H16Layout{64}.offset(SEC_OS) : hash_sec(SEC_OS);   // 16-bit elements
+    static constexpr int kFwd4 = kFwd / 8, kE4 = kIn * 4 * 64, kBuf4 = 8 * 4 * 64;             // u32x4
+    static constexpr int kTotal4 = kFwd4 + kE4 + 2 * kBuf4;
+    __host__ __device__ static constexpr int sec(int s) { return ENC == 0 ? H16Layout{64}.offset(s) : hash_sec(s); }
+};
 
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
-    const int64_t B = q.count;
-    const bool use_loss = PLAIN || args.target != nullptr;
+// Selection operands (B: lane (g, c) holds K positions 8 g + j of column c): column c takes K position
+// 8 (c / 4) + c % 4 + 4 half, times `odd` where c is odd.
+template <int PREC>
+__device__ __forceinline__ u32x4 select_operand(int half, float odd, int g, int col) {
+    u32x4 v = u32x4{0u, 0u, 0u, 0u};
+    const uint32_t one = pack2<PREC>((col & 1) ? odd : 1.0f, 0.0f) & 0xFFFFu;
+    const uint32_t w = (col & 1) ? one << 16 : one;
+    if (g == (col >> 2)) {
+        const int d = 2 * half + ((col & 3) >> 1);
+        v = u32x4{d == 0 ? w : 0u, d == 1 ? w : 0u, d == 2 ? w : 0u, d == 3 ? w : 0u};
+    }
+    return v;
+}
+
+// Zeroes the 16-bit halves of d whose activation (a ReLU output, never negative) is +0.
+__device__ __forceinline__ uint32_t relu_mask2(uint32_t d, uint32_t h) {
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    const u16x2 hv = __builtin_bit_cast(u16x2, h), one = {1, 1};
+    const u16x2 on = hv < one ? hv : one;   // min(h, 1)
+    return __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, d) * on));
+}
+
+// Block `blk` of `nblk` over the batch (rounds blk, blk + nblk, ...): its partial gradient goes to
+// `out` (canonical layout), its loss partial to *loss_out.  smem: Grad64<ENC>::kTotal4; sLoss: kWaves64
+// floats.  Ends after a workgroup barrier, so a caller may run the next block on the same LDS.
+// PLAIN: the caller guarantees the common case (targets given, relative L2 of eq. 12, no
+// residual-variance mean, exp outputs), so the general loss arithmetic is compiled out.
+template <int ENC, int PREC, bool PLAIN>
+__device__ __forceinline__ void grad64_block(const Points &pts, const Queries &q, const uint16_t *packed,
+                                             const TrainArgs &args, const HashLevel *s_lv, const HashTrainBufs &bufs,
+                                             const GridAcc &gacc, bool add, float *out, float *loss_out, int64_t blk,
+                                             int64_t nblk, u32x4 *smem, float *sLoss) {
+    using G = Grad64<ENC>;
+    constexpr int MT = 4, KB = 2, W = 64;
+    u32x4 *sF = smem, *sE = sF + G::kFwd4, *sB = sE + G::kE4;
+    const uint16_t *fw = (const uint16_t *)sF;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int col = lane & 15, g = lane >> 4;
+    const int64_t B = q.count, stride = hash_level_stride(B);
+    const bool use_loss = PLAIN || ENC == 1 || args.target != nullptr;
     // the host passes loss_scale * B for 16-bit models (or the dynamic scale is taken times B):
     // k = 2 loss_scale / 3 per sample
     const float ls = args.dyn_scale ? *args.dyn_scale * (float)B : args.loss_scale;
     const float kscale = use_loss ? 2.0f * ls / (3.0f * (float)B) : ls;
 
-    f32x4 g1[3][MT], gh[3][MT], g5;
+    {
+        const u32x4 *src = (const u32x4 *)packed;
+        for (int i = threadIdx.x; i < G::kFwd4; i += kWaves64 * 64) sF[i] = src[i];
+    }
+    // this wave's tiles: W2..W4 column tile wave % 4, row tiles 2 (wave / 4) and the next; W5 column
+    // tile wave (waves 0..3); W1 row tile wave % 4, input tiles wave / 4 + 2 j
+    const int own_n = wave & 3, own_m = 2 * (wave >> 2);
+    f32x4 gh[3][2], g1[G::kOwnIn], g5 = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
+    for (int a = 0; a < 3; ++a) gh[a][0] = gh[a][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            g1[a][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-            gh[a][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-    g5 = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < G::kOwnIn; ++j) g1[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     float loss_acc = 0.0f;
+    const u32x4 sel[2] = {select_operand<PREC>(0, 1.0f, g, col), select_operand<PREC>(1, 1.0f, g, col)};
+    // the input features are (sin, 2 cos) pairs, the first layer's gradient takes (sin, cos)
+    const u32x4 sel_in[2] = {select_operand<PREC>(0, ENC == 0 ? 0.5f : 1.0f, g, col),
+                             select_operand<PREC>(1, ENC == 0 ? 0.5f : 1.0f, g, col)};
+    // turned rows of this wave's samples: half an operand of K-block wave / 2
+    auto put = [&](u32x4 *slot, const u32x4 &op, const u32x4 &sl) {
+        const f32x4 t = mfma16<PREC>(op, sl, f32x4{0.f, 0.f, 0.f, 0.f});
+        ((uint2 *)(slot + (wave >> 1) * 64 + lane))[wave & 1] = make_uint2(pack2<PREC>(t[0], t[1]), pack2<PREC>(t[2], t[3]));
+    };
+    int phase = 0;
+    // row slots 0..3 of a buffer: delta; 4..7: activations
+    auto buffer = [&]() { return sB + (phase & 1) * G::kBuf4; };
 
-    const int64_t n_chunks = (B + kChunk16 - 1) / kChunk16;
+    const int64_t n_chunks = (B + kChunk64 - 1) / kChunk64;
     const int s = 16 * wave + col;   // sample slot in the round
     Sample16 next;
-    if (blk < n_chunks) {
-        load_query16(q, args, blk * kChunk16 + s, B, next);
+    if (ENC == 0 && blk < n_chunks) {
+        load_query16(q, args, blk * kChunk64 + s, B, next);
         load_point16(pts, q, next);
     }
+    __syncthreads();
     for (int64_t chunk = blk; chunk < n_chunks; chunk += nblk) {
-        // ---------------- phase 1: forward + backward of this wave's 16 samples
-        {
-            const uint16_t *pk = opaque(packed);
+        const uint16_t *pk = opaque(packed);
+        const int64_t b = chunk * kChunk64 + s;
+        const bool valid = b < B;
+        const int64_t bi = valid ? b : B - 1;
+        const bool more = chunk + nblk < n_chunks;
+        float xs[7], tg[3];
+        u32x4 e[G::kInKb];   // input operands
+        if constexpr (ENC == 0) {
             const Sample16 cur = next;
-            const bool more = chunk + nblk < n_chunks;
-            if (more) load_query16(q, args, (chunk + nblk) * kChunk16 + s, B, next);
-            const bool valid = cur.valid;
-            const float *xs = cur.x, *ws = cur.w;
-            // scheduling fences between the steps of a round: left free, the compiler interleaves
-            // the steps' loads and LDS stores in an order that measured a third slower
+            if (more) load_query16(q, args, (chunk + nblk) * kChunk64 + s, B, next);
+            // scheduling fences between the steps of a round keep their loads and LDS traffic apart
             __builtin_amdgcn_sched_barrier(0);
-
-            // input features of frequencies 2g, 2g + 1: (sin, 2 cos) pairs for the MFMAs, and
-            // (sin, cos) rows for the first layer's gradient
-            float f[44];
 #pragma unroll
-            for (int i = 0; i < 7; ++i) enc_pair2_fast(xs[i], g, f[4 * i], f[4 * i + 1], f[4 * i + 2], f[4 * i + 3]);
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-                enc_pair2_fast(ws[i], g, f[28 + 4 * i], f[29 + 4 * i], f[30 + 4 * i], f[31 + 4 * i]);
-#pragma unroll
-            for (int t = 0; t < 28; ++t)
-                sE[feature_of(true, g, t) * kRow16 + s] = to16<PREC>((t & 1) ? 0.5f * f[t] : f[t]);
-#pragma unroll
-            for (int t = 0; t < 12; ++t)
-                sE[feature_of(false, g, t) * kRow16 + s] = to16<PREC>((t & 1) ? 0.5f * f[28 + t] : f[28 + t]);
-            __builtin_amdgcn_sched_barrier(0);
-
-            // forward
-            u32x4 hb[4][KB];   // h1..h4 after ReLU, as chained B operands
-            {
-                f32x4 h[MT];
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) h[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-                const uint16_t *gS = pk + L.offset(SEC_S);
-#pragma unroll
-                for (int kb = 0; kb < 4; ++kb) {
-                    const float *fk = f + 8 * kb;
-                    const u32x4 bop = kb < 3 ? u32x4{pack2<PREC>(fk[0], fk[1]), pack2<PREC>(fk[2], fk[3]),
-                                                     pack2<PREC>(fk[4], fk[5]), pack2<PREC>(fk[6], fk[7])}
-                                             : u32x4{pack2<PREC>(fk[0], fk[1]), pack2<PREC>(fk[2], fk[3]), 0u, 0u};
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
-                        h[mt] = mfma16<PREC>(*(const u32x4 *)(gS + ((mt * 4 + kb) * 64 + lane) * 8), bop, h[mt]);
-                }
-                const float *fd = f + 28;
-                const u32x4 bd0 = {pack2<PREC>(fd[0], fd[1]), pack2<PREC>(fd[2], fd[3]), pack2<PREC>(fd[4], fd[5]),
-                                   pack2<PREC>(fd[6], fd[7])};
-                const u32x4 bd1 = {pack2<PREC>(fd[8], fd[9]), pack2<PREC>(fd[10], fd[11]), 0u, 0u};
-                const uint16_t *gD = pk + L.offset(SEC_D);
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    h[mt] = mfma16<PREC>(*(const u32x4 *)(gD + ((mt * 2 + 0) * 64 + lane) * 8), bd0, h[mt]);
-                    h[mt] = mfma16<PREC>(*(const u32x4 *)(gD + ((mt * 2 + 1) * 64 + lane) * 8), bd1, h[mt]);
-                }
-#pragma unroll
-                for (int kb = 0; kb < KB; ++kb) hb[0][kb] = chain_operand<PREC>(h[2 * kb], h[2 * kb + 1]);
+            for (int kb = 0; kb < 6; ++kb) {
+                float f[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                const int i0 = kb < 4 ? 2 * kb : 2 * (kb - 4);
+                const float *v = kb < 4 ? cur.x : cur.w;
+                enc_pair2_fast(v[i0], g, f[0], f[1], f[2], f[3]);
+                if (i0 + 1 < (kb < 4 ? 7 : 3)) enc_pair2_fast(v[i0 + 1], g, f[4], f[5], f[6], f[7]);
+                e[kb] = u32x4{pack2<PREC>(f[0], f[1]), pack2<PREC>(f[2], f[3]), pack2<PREC>(f[4], f[5]),
+                              pack2<PREC>(f[6], f[7])};
             }
 #pragma unroll
-            for (int l = 1; l < 4; ++l) {
-                const uint16_t *sec = pk + L.offset(SEC_H0 + (l - 1));
-                f32x4 h[MT];
+            for (int c = 0; c < 3; ++c) tg[c] = cur.t[c];
+        } else {
+            const f32x4 xa = *(const f32x4 *)(bufs.attr + 8 * bi), xb = *(const f32x4 *)(bufs.attr + 8 * bi + 4);
+            xs[0] = xa[0], xs[1] = xa[1], xs[2] = xa[2], xs[3] = xa[3], xs[4] = xb[0], xs[5] = xb[1], xs[6] = xb[2];
+            float v[6];
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) h[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int k = 0; k < 3; ++k) {
+                const float2 t = bufs.vals[(3 * g + k) * stride + bi];
+                v[2 * k] = t.x;
+                v[2 * k + 1] = t.y;
+            }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) tg[c] = args.target[3 * bi + c];
+            hash_pack_surface<PREC>(xs, g, v, e[0], e[1]);
+            e[2] = sh_operand<PREC>(q.wx[bi], q.wy[bi], q.wz[bi], g);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+
+        // ---------------- forward
+        u32x4 hb[4][KB];   // h1..h4 after ReLU, as chained operands
+#pragma unroll
+        for (int l = 0; l < 4; ++l) {
+            f32x4 h[MT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) h[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (l == 0) {
+                constexpr int SK = ENC == 0 ? 4 : 2, DK = ENC == 0 ? 2 : 1;   // K-blocks of S and D
+#pragma unroll
+                for (int kb = 0; kb < SK; ++kb)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+                        h[mt] = mfma16<PREC>(*(const u32x4 *)(fw + ((mt * SK + kb) * 64 + lane) * 8), e[kb], h[mt]);
+                const uint16_t *sD = fw + (ENC == 0 ? H16Layout{64}.offset(SEC_D) : kHashSecD);
+#pragma unroll
+                for (int kb = 0; kb < DK; ++kb)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+                        h[mt] = mfma16<PREC>(*(const u32x4 *)(sD + ((mt * DK + kb) * 64 + lane) * 8), e[SK + kb], h[mt]);
+            } else {
+                const uint16_t *sec = fw + G::sec(SEC_H0 + (l - 1));
 #pragma unroll
                 for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
                     for (int mt = 0; mt < MT; ++mt)
-                        h[mt] = mfma16<PREC>(*(const u32x4 *)(sec + ((mt * KB + kb) * 64 + lane) * 8), hb[l - 1][kb],
-                                             h[mt]);
-#pragma unroll
-                for (int kb = 0; kb < KB; ++kb) hb[l][kb] = chain_operand<PREC>(h[2 * kb], h[2 * kb + 1]);
+                        h[mt] = mfma16<PREC>(*(const u32x4 *)(sec + ((mt * KB + kb) * 64 + lane) * 8), hb[l - 1][kb], h[mt]);
             }
-            f32x4 z5 = f32x4{0.f, 0.f, 0.f, 0.f};
-            {
-                const uint16_t *sec = pk + L.offset(SEC_O);
 #pragma unroll
-                for (int kb = 0; kb < KB; ++kb)
-                    z5 = mfma16<PREC>(*(const u32x4 *)(sec + (kb * 64 + lane) * 8), hb[3][kb], z5);
-            }
+            for (int kb = 0; kb < KB; ++kb) hb[l][kb] = chain_operand<PREC>(h[2 * kb], h[2 * kb + 1]);
+        }
+        f32x4 z5 = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+            z5 = mfma16<PREC>(*(const u32x4 *)(fw + G::sec(SEC_O) + (kb * 64 + lane) * 8), hb[3][kb], z5);
+        if constexpr (ENC == 0) {
             __builtin_amdgcn_sched_barrier(0);
             if (more) load_point16(pts, q, next);
-#pragma unroll
-            for (int l = 0; l < 4; ++l) stage_chain<W>(sH + l * W * kRow16, hb[l], g, s);
+        }
 
-            // output delta (rows 0..2 in lanes 0..15)
-            float d5[3] = {0.f, 0.f, 0.f};
-            if (g == 0 && valid) {
+        // output delta (channels 0..2 in lane group 0)
+        float d5[3] = {0.f, 0.f, 0.f};
+        if (g == 0 && valid) {
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    const float t = use_loss ? cur.t[c] : 0.0f;
-                    const float dr = use_loss ? 0.0f : cur.t[c];
-                    float lt;
-                    d5[c] = PLAIN ? out_grad16(z5[c], t, 0.0f, true, args.loss_eps, kscale, true, 0.0f, false, lt)
-                                  : out_grad16(z5[c], t, dr, use_loss, args.loss_eps, kscale,
-                                               args.loss_kind == NIRC_LOSS_REL_L2, args.fr ? args.fr[c] : 0.0f,
-                                               args.sig != 0, lt);
-                    loss_acc += lt;
-                }
+            for (int c = 0; c < 3; ++c) {
+                const float t = use_loss ? tg[c] : 0.0f, dr = use_loss ? 0.0f : tg[c];
+                float lt;
+                if constexpr (PLAIN)
+                    d5[c] = out_grad16(z5[c], t, 0.0f, true, args.loss_eps, kscale, true, 0.0f, false, lt);
+                else
+                    d5[c] = out_grad16(z5[c], t, dr, use_loss, args.loss_eps, kscale, args.loss_kind == NIRC_LOSS_REL_L2,
+                                       ENC == 0 && args.fr ? args.fr[c] : 0.0f, ENC == 0 && args.sig != 0, lt);
+                loss_acc += lt;
             }
-            if (g == 0) {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) sD5[c * kRow16 + s] = to16<PREC>(c < 3 ? d5[c] : 0.0f);
-            }
+        }
+        // OT holds output o at K position 8 g + j (j < 4, o = 4 g + j): only lane group 0 carries d5
+        const u32x4 d5op = g == 0 ? u32x4{pack2<PREC>(d5[0], d5[1]), pack2<PREC>(d5[2], 0.0f), 0u, 0u}
+                                  : u32x4{0u, 0u, 0u, 0u};
 
-            // backward: delta4 = (W5^T d5) .* [h4 > 0]; OT holds output o at K position 8g + j
-            // (j < 4, o = 4g + j), so only lane group 0 carries d5 in the B operand
-            f32x4 dl[MT];
-            {
-                const u32x4 bop = g == 0 ? u32x4{pack2<PREC>(d5[0], d5[1]), pack2<PREC>(d5[2], 0.0f), 0u, 0u}
-                                         : u32x4{0u, 0u, 0u, 0u};
-                const uint16_t *sec = pk + L.offset(SEC_OT);
+        // ---------------- backward and weight gradients, layer by layer
+        {
+            u32x4 *buf = buffer();
+            put(buf, d5op, sel[0]);
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    dl[mt] = mfma16<PREC>(*(const u32x4 *)(sec + (mt * 64 + lane) * 8), bop, f32x4{0.f, 0.f, 0.f, 0.f});
+            for (int n = 0; n < 4; ++n) put(buf + (4 + n) * 256, hb[3][n >> 1], sel[n & 1]);
+            __syncthreads();
+            if (wave < 4) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    g5 = mfma16<PREC>(buf[k * 64 + lane], buf[(4 + own_n) * 256 + k * 64 + lane], g5);
             }
+            ++phase;
+        }
+        // the inputs' turned rows (every wave is past the previous round's last use of them)
 #pragma unroll
-            for (int l = 3; l >= 0; --l) {
-                // mask with [h_{l+1} > 0]: result row i of tile mt is chained position
-                // (kb = mt / 2, j = 4 (mt % 2) + i) of hb[l]
-                u32x4 db[KB];
+        for (int i = 0; i < G::kIn; ++i) {
+            // ENC 0: surface inputs 0..6 in K-blocks 0..3, directions 0..2 in 4, 5
+            const int kb = ENC == 1 ? i >> 1 : i < 7 ? i >> 1 : 4 + ((i - 7) >> 1);
+            const int half = ENC == 1 ? i & 1 : i < 7 ? i & 1 : (i - 7) & 1;
+            put(sE + i * 256, e[kb], sel_in[half]);
+        }
+        f32x4 dl[MT];
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
+        for (int mt = 0; mt < MT; ++mt)
+            dl[mt] = mfma16<PREC>(*(const u32x4 *)(pk + G::sec(SEC_OT) + (mt * 64 + lane) * 8), d5op,
+                                  f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const uint16_t hv = half_of(hb[l][mt >> 1], 4 * (mt & 1) + i);
-                        if (hv == 0) dl[mt][i] = 0.0f;   // ReLU output is +0 exactly when inactive
-                    }
+        for (int l = 3; l >= 0; --l) {
+            // delta_{l+1} = (W^T delta) .* [h_{l+1} > 0]
+            u32x4 db[KB];
 #pragma unroll
-                for (int kb = 0; kb < KB; ++kb) db[kb] = chain_plain<PREC>(dl[2 * kb], dl[2 * kb + 1]);
-                stage_chain<W>(sD + l * W * kRow16, db, g, s);
-                if (l == 0) break;
-                // delta_l = (W_{l+1}^T delta_{l+1}) .* [h_l > 0]
-                const uint16_t *sec = pk + L.offset(SEC_T0 + (l - 1));
+            for (int kb = 0; kb < KB; ++kb) {
+                const u32x4 d = chain_plain<PREC>(dl[2 * kb], dl[2 * kb + 1]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) db[kb][i] = relu_mask2(d[i], hb[l][kb][i]);
+            }
+            u32x4 *buf = buffer();
+#pragma unroll
+            for (int m = 0; m < 4; ++m) put(buf + m * 256, db[m >> 1], sel[m & 1]);
+            if (l > 0) {
+#pragma unroll
+                for (int n = 0; n < 4; ++n) put(buf + (4 + n) * 256, hb[l - 1][n >> 1], sel[n & 1]);
+            }
+            if (l > 0) {
+                const uint16_t *sec = pk + G::sec(SEC_T0 + (l - 1));
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) dl[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -290,69 +359,80 @@ __device__ __forceinline__ void grad16_block(const Points &pts, const Queries &q
 #pragma unroll
                     for (int mt = 0; mt < MT; ++mt)
                         dl[mt] = mfma16<PREC>(*(const u32x4 *)(sec + ((mt * KB + kb) * 64 + lane) * 8), db[kb], dl[mt]);
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        __syncthreads();
-        __builtin_amdgcn_sched_barrier(0);
-        // ---------------- phase 2: owned gradient tiles += staged deltas x activations
-        // K position 8g + j of K-block kb <-> sample 32 kb + 8 g + j
+            } else if constexpr (ENC == 1) {
+                // gradient of the grid values: rows 16 mt + 4 g + i of W1_grid^T delta1 (lane (g, col):
+                // levels 8 mt + 2 g and 8 mt + 2 g + 1 of sample col)
+                const uint16_t *sec = pk + kHashSecTS;
 #pragma unroll
-        for (int kb = 0; kb < kChunk16 / 32; ++kb) {
-            const int s0 = 32 * kb + 8 * g;
+                for (int mt = 0; mt < 2; ++mt) {
+                    f32x4 de = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                const u32x4 bv = *(const u32x4 *)(sH + (a * W + 16 * wave + col) * kRow16 + s0);
+                    for (int kb = 0; kb < KB; ++kb)
+                        de = mfma16<PREC>(*(const u32x4 *)(sec + ((mt * KB + kb) * 64 + lane) * 8), db[kb], de);
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    const u32x4 av = *(const u32x4 *)(sD + ((a + 1) * W + 16 * mt + col) * kRow16 + s0);
-                    gh[a][mt] = mfma16<PREC>(av, bv, gh[a][mt]);
+                    for (int k = 0; k < 2; ++k) {
+                        const int level = 8 * mt + 2 * g + k;
+                        if (valid && level < kHashLevels) {
+                            const float d0 = de[2 * k], d1 = de[2 * k + 1];
+                            grid_grad_check(gacc, d0, xs[0], xs[1], xs[2], s_lv[level].res);
+                            grid_grad_check(gacc, d1, xs[0], xs[1], xs[2], s_lv[level].res);
+                            bufs.dvals[level * stride + b] = make_float2(d0, d1);
+                        }
+                    }
                 }
             }
-            {
-                const u32x4 bv = *(const u32x4 *)(sH + (3 * W + 16 * wave + col) * kRow16 + s0);
-                u32x4 av = u32x4{0u, 0u, 0u, 0u};
-                if (col < 3) av = *(const u32x4 *)(sD5 + col * kRow16 + s0);
-                g5 = mfma16<PREC>(av, bv, g5);
-            }
+            __syncthreads();
+            if (l > 0) {
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                const int input = wave + 4 * a;
-                if (input >= kInputs) break;
-                const u32x4 bv = *(const u32x4 *)(sE + (16 * input + col) * kRow16 + s0);
+                for (int k = 0; k < 4; ++k) {
+                    const u32x4 bv = buf[(4 + own_n) * 256 + k * 64 + lane];
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    const u32x4 av = *(const u32x4 *)(sD + (16 * mt + col) * kRow16 + s0);
-                    g1[a][mt] = mfma16<PREC>(av, bv, g1[a][mt]);
+                    for (int m = 0; m < 2; ++m)
+                        gh[l - 1][m] = mfma16<PREC>(buf[(own_m + m) * 256 + k * 64 + lane], bv, gh[l - 1][m]);
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const u32x4 av = buf[own_n * 256 + k * 64 + lane];
+#pragma unroll
+                    for (int j = 0; j < G::kOwnIn; ++j) {
+                        const int i = (wave >> 2) + 2 * j;
+                        if (i < G::kIn) g1[j] = mfma16<PREC>(av, sE[i * 256 + k * 64 + lane], g1[j]);
+                    }
                 }
             }
+            ++phase;
         }
-        __builtin_amdgcn_sched_barrier(0);
-        __syncthreads();
-        __builtin_amdgcn_sched_barrier(0);
     }
 
     // ---------------- write this block's partial gradient (every entry exactly once)
+    constexpr int IN = ENC == 0 ? kFeat : kHashIn;
+    auto store = [&](int i, float v) { out[i] = ENC == 1 && add ? out[i] + v : v; };
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const int input = wave + 4 * a;
-        if (input >= kInputs) break;
+    for (int j = 0; j < G::kOwnIn; ++j) {
+        const int i = (wave >> 2) + 2 * j;
+        if (i >= G::kIn) continue;
+        int c;   // canonical input of this lane's column, or -1
+        if constexpr (ENC == 0) {
+            c = 16 * (i < 7 ? surf_input(i) : i - 4) + col;
+        } else {
+            const int kb = i >> 1, pj = 4 * (i & 1) + (col & 3);
+            c = kb < 2 ? hash_surface_input(kb, col >> 2, pj) : hash_direction_input(col >> 2, pj);
+        }
+        if (c >= 0)
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                out[w_offset(W, 0) + (int64_t)(16 * mt + 4 * g + i) * kFeat + 16 * input + col] = g1[a][mt][i];
+            for (int r = 0; r < 4; ++r) store((16 * own_n + 4 * g + r) * IN + c, g1[j][r]);
     }
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+        for (int m = 0; m < 2; ++m)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                out[w_offset(W, 1 + a) + (int64_t)(16 * mt + 4 * g + i) * W + 16 * wave + col] = gh[a][mt][i];
-    if (g == 0) {
+            for (int r = 0; r < 4; ++r)
+                store(W * IN + a * W * W + (16 * (own_m + m) + 4 * g + r) * W + 16 * own_n + col, gh[a][m][r]);
+    if (wave < 4 && g == 0) {
 #pragma unroll
-        for (int i = 0; i < 3; ++i) out[w_offset(W, 4) + (int64_t)i * W + 16 * wave + col] = g5[i];
+        for (int r = 0; r < 3; ++r) store(W * IN + 3 * W * W + r * W + 16 * own_n + col, g5[r]);
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) loss_acc += __shfl_xor(loss_acc, d, 64);
@@ -360,20 +440,21 @@ __device__ __forceinline__ void grad16_block(const Points &pts, const Queries &q
     __syncthreads();
     if (threadIdx.x == 0) {
         float t = 0.0f;
-        for (int w = 0; w < kWaves16; ++w) t += sLoss[w];
-        *loss_out = t;
+        for (int w = 0; w < kWaves64; ++w) t += sLoss[w];
+        *loss_out = ENC == 1 && add ? *loss_out + t : t;
     }
     __syncthreads();
 }
 
-template <int W, int PREC, bool PLAIN = false>
-__global__ __launch_bounds__(kWaves16 * 64) void k_grad_h16(Points pts, Queries q, const uint16_t *__restrict__ packed,
+template <int PREC, bool PLAIN>
+__global__ __launch_bounds__(kWaves64 * 64) void k_grad_h16(Points pts, Queries q, const uint16_t *__restrict__ packed,
                                                             TrainArgs args, float *__restrict__ partials,
                                                             float *__restrict__ loss_partials) {
-    __shared__ u32x4 smem4[(Grad16Lds<W>::kTotal + 7) / 8];
-    __shared__ float sLoss[kWaves16];
-    grad16_block<W, PREC, PLAIN>(pts, q, packed, args, partials + (int64_t)blockIdx.x * n_params(W),
-                          loss_partials + blockIdx.x, blockIdx.x, gridDim.x, (uint16_t *)smem4, sLoss);
+    __shared__ u32x4 smem[Grad64<0>::kTotal4];
+    __shared__ float sLoss[kWaves64];
+    grad64_block<0, PREC, PLAIN>(pts, q, packed, args, nullptr, HashTrainBufs{}, GridAcc{}, false,
+                                 partials + (int64_t)blockIdx.x * n_params(64), loss_partials + blockIdx.x, blockIdx.x,
+                                 gridDim.x, smem, sLoss);
 }
 
 // The gradient step of several models at once (continuous batching of the streams' training
@@ -381,10 +462,10 @@ __global__ __launch_bounds__(kWaves16 * 64) void k_grad_h16(Points pts, Queries 
 // fixed grid walks the virtual blocks in order.  Virtual block b of a request computes exactly
 // what block b of k_grad_h16 computes for that request alone (same chunks, same order), so the
 // partials, and everything after them, are bit-identical.
-template <int W, int PREC>
-__global__ __launch_bounds__(kWaves16 * 64) void k_grad_h16_multi(const TrainDesc *__restrict__ desc) {
-    __shared__ u32x4 smem4[(Grad16Lds<W>::kTotal + 7) / 8];
-    __shared__ float sLoss[kWaves16];
+template <int PREC>
+__global__ __launch_bounds__(kWaves64 * 64) void k_grad_h16_multi(const TrainDesc *__restrict__ desc) {
+    __shared__ u32x4 smem[Grad64<0>::kTotal4];
+    __shared__ float sLoss[kWaves64];
     const int n = desc->n, total = desc->total_vb;
     for (int v = blockIdx.x; v < total; v += gridDim.x) {
         int r = 0;
@@ -394,8 +475,8 @@ __global__ __launch_bounds__(kWaves16 * 64) void k_grad_h16_multi(const TrainDes
         const Queries q{t.swx, t.swy, t.swz, t.sp, t.batch, t.bad};
         const TrainArgs a{t.stgt, nullptr, t.loss_eps, t.loss_scale * (float)t.batch, t.loss_kind, nullptr,
                           t.output == NIRC_OUTPUT_VISIBILITY, t.dyn_scale};
-        grad16_block<W, PREC>(t.pts, q, t.packed16, a, t.partials + (int64_t)b * n_params(W), t.lpart + b, b, t.nb,
-                              (uint16_t *)smem4, sLoss);
+        grad64_block<0, PREC, false>(t.pts, q, t.packed16, a, nullptr, HashTrainBufs{}, GridAcc{}, false,
+                                     t.partials + (int64_t)b * n_params(64), t.lpart + b, b, t.nb, smem, sLoss);
     }
 }
 
@@ -669,11 +750,15 @@ __global__ __launch_bounds__(kWaves16 * 64) void k_grad_h16_wide(Points pts, Que
     }
 }
 
-int train_blocks16(int64_t batch) {
-    int64_t chunks = (batch + kChunk16 - 1) / kChunk16;
+static int blocks_of(int64_t batch, int chunk) {
+    int64_t chunks = (batch + chunk - 1) / chunk;
     if (chunks > kMaxResidentBlocks) chunks = kMaxResidentBlocks;
     return (int)(chunks < 1 ? 1 : chunks);
 }
+
+int train_blocks16(int64_t batch) { return blocks_of(batch, kChunk16); }
+
+int grad_blocks16(int W, int64_t batch) { return blocks_of(batch, W == 64 ? kChunk64 : kChunk16); }
 
 hipError_t launch_grad_partials16(int W, int prec, const Points &pts, const Queries &q, const void *packed,
                                   TrainArgs a, float *partials, float *loss_partials, int nblocks, hipStream_t s) {
@@ -695,18 +780,15 @@ hipError_t launch_grad_partials16(int W, int prec, const Points &pts, const Quer
     }
     if (W != 64) return hipErrorInvalidValue;
     const bool plain = a.target && a.loss_kind == NIRC_LOSS_REL_L2 && !a.fr && !a.sig;
+    const dim3 grid(nblocks), block(kWaves64 * 64);
     if (prec == NIRC_BF16 && plain)
-        hipLaunchKernelGGL((k_grad_h16<64, NIRC_BF16, true>), dim3(nblocks), dim3(kWaves16 * 64), 0, s, pts, q, pk, a,
-                           partials, loss_partials);
+        hipLaunchKernelGGL((k_grad_h16<NIRC_BF16, true>), grid, block, 0, s, pts, q, pk, a, partials, loss_partials);
     else if (prec == NIRC_BF16)
-        hipLaunchKernelGGL((k_grad_h16<64, NIRC_BF16>), dim3(nblocks), dim3(kWaves16 * 64), 0, s, pts, q, pk, a,
-                           partials, loss_partials);
+        hipLaunchKernelGGL((k_grad_h16<NIRC_BF16, false>), grid, block, 0, s, pts, q, pk, a, partials, loss_partials);
     else if (plain)
-        hipLaunchKernelGGL((k_grad_h16<64, NIRC_FP16, true>), dim3(nblocks), dim3(kWaves16 * 64), 0, s, pts, q, pk, a,
-                           partials, loss_partials);
+        hipLaunchKernelGGL((k_grad_h16<NIRC_FP16, true>), grid, block, 0, s, pts, q, pk, a, partials, loss_partials);
     else
-        hipLaunchKernelGGL((k_grad_h16<64, NIRC_FP16>), dim3(nblocks), dim3(kWaves16 * 64), 0, s, pts, q, pk, a,
-                           partials, loss_partials);
+        hipLaunchKernelGGL((k_grad_h16<NIRC_FP16, false>), grid, block, 0, s, pts, q, pk, a, partials, loss_partials);
     return hipGetLastError();
 }
 
@@ -714,9 +796,9 @@ hipError_t launch_train_step_multi(const TrainDesc *desc, int prec, uint32_t ste
     hipError_t e = launch_train_batch_multi(desc, step, max_batch, s);
     if (e != hipSuccess) return e;
     if (prec == NIRC_BF16)
-        hipLaunchKernelGGL((k_grad_h16_multi<64, NIRC_BF16>), dim3(kMaxResidentBlocks), dim3(kWaves16 * 64), 0, s, desc);
+        hipLaunchKernelGGL((k_grad_h16_multi<NIRC_BF16>), dim3(kMaxResidentBlocks), dim3(kWaves64 * 64), 0, s, desc);
     else
-        hipLaunchKernelGGL((k_grad_h16_multi<64, NIRC_FP16>), dim3(kMaxResidentBlocks), dim3(kWaves16 * 64), 0, s, desc);
+        hipLaunchKernelGGL((k_grad_h16_multi<NIRC_FP16>), dim3(kMaxResidentBlocks), dim3(kWaves64 * 64), 0, s, desc);
     e = hipGetLastError();
     if (e == hipSuccess) e = launch_reduce_grad_multi(desc, 64, s);
     if (e == hipSuccess) e = launch_adam_pack16_multi(desc, 64, prec, s);
@@ -724,265 +806,23 @@ hipError_t launch_train_step_multi(const TrainDesc *desc, int prec, uint32_t ste
 }
 
 // ------------------------------------------------------------------------------------------
-// The hash-grid model (width 64): the same two phases as k_grad_h16 with the 64 grid / SH / phi
-// inputs, the grid values blended beforehand (bufs.vals).  In addition, after the first layer's
-// delta, each sample's gradient with respect to its 24 grid values (W1_grid^T delta1, from the TS
-// section) goes to bufs.dvals for the grid-entry sums.
-namespace {
-struct HashGrad16Lds {
-    static constexpr int kH = 4 * 64 * kRow16;
-    static constexpr int kD = 4 * 64 * kRow16;
-    static constexpr int kD5 = 4 * kRow16;
-    static constexpr int kE = kHashIn * kRow16;
-    static constexpr int kTotal = kH + kD + kD5 + kE;
-};
-}  // namespace
-
+// The hash-grid model: grad64_block with the 64 grid / SH / phi inputs, the grid values blended
+// beforehand (bufs.vals).  Each sample's gradient with respect to its 24 grid values (W1_grid^T
+// delta1, from the TS section) goes to bufs.dvals for the grid-entry sums.
 template <int PREC>
-__global__ __launch_bounds__(kWaves16 * 64) void k_hash_grad_h16(Queries q, const uint16_t *__restrict__ packed,
+__global__ __launch_bounds__(kWaves64 * 64) void k_hash_grad_h16(Queries q, const uint16_t *__restrict__ packed,
                                                                  HashGridArgs grid, TrainArgs args, HashTrainBufs bufs,
                                                                  float *__restrict__ partials,
-                                                                 float *__restrict__ loss_partials, GridAcc gacc, bool add) {
-    constexpr int MT = 4, KB = 2, W = 64;
-    using S = HashGrad16Lds;
-    __shared__ u32x4 smem4[(S::kTotal + 7) / 8];
-    __shared__ float sLoss[kWaves16];
+                                                                 float *__restrict__ loss_partials, GridAcc gacc,
+                                                                 bool add) {
+    __shared__ u32x4 smem[Grad64<1>::kTotal4];
+    __shared__ float sLoss[kWaves64];
     __shared__ HashLevel s_lv[kHashLevels];
-    uint16_t *smem = (uint16_t *)smem4;
-    uint16_t *sH = smem;
-    uint16_t *sD = sH + S::kH;
-    uint16_t *sD5 = sD + S::kD;
-    uint16_t *sE = sD5 + S::kD5;
     stage_levels(s_lv, grid);
     __syncthreads();
-
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
-    const int64_t B = q.count, stride = hash_level_stride(B);
-    const bool rel = args.loss_kind == NIRC_LOSS_REL_L2;
-    // the host passes loss_scale * B: k = 2 loss_scale / 3 per sample
-    const float kscale = 2.0f * args.loss_scale / (3.0f * (float)B);
-
-    f32x4 g1[MT], gh[3][MT], g5;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        g1[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int a = 0; a < 3; ++a) gh[a][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    g5 = f32x4{0.f, 0.f, 0.f, 0.f};
-    float loss_acc = 0.0f;
-
-    const int64_t n_chunks = (B + kChunk16 - 1) / kChunk16;
-    for (int64_t chunk = blockIdx.x; chunk < n_chunks; chunk += gridDim.x) {
-        {
-            const uint16_t *pk = opaque(packed);
-            const int s = 16 * wave + col;
-            const int64_t b = chunk * kChunk16 + s;
-            const bool valid = b < B;
-            const int64_t bi = valid ? b : B - 1;
-            const f32x4 xa = *(const f32x4 *)(bufs.attr + 8 * bi), xb = *(const f32x4 *)(bufs.attr + 8 * bi + 4);
-            const float xs[7] = {xa[0], xa[1], xa[2], xa[3], xb[0], xb[1], xb[2]};
-
-            // inputs: operands for the MFMAs and 16-bit rows [canonical input][sample] for dW1
-            u32x4 b0, b1;
-            float v[6];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const float2 t = bufs.vals[(3 * g + k) * stride + bi];
-                v[2 * k] = t.x;
-                v[2 * k + 1] = t.y;
-            }
-            hash_pack_surface<PREC>(xs, g, v, b0, b1);
-            float Y[25];
-            sh25(q.wx[bi], q.wy[bi], q.wz[bi], Y);
-            const u32x4 bd0 = sh_operand_of<PREC>(Y, g);
-            // the rows hold exactly the 16-bit operand values
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                sE[hash_surface_input(0, g, j) * kRow16 + s] = half_of(b0, j);
-                if (8 * g + j < 25) sE[(24 + 8 * g + j) * kRow16 + s] = half_of(bd0, j);
-            }
-            if (g == 0) {
-#pragma unroll
-                for (int j = 0; j < 7; ++j) sE[(57 + j) * kRow16 + s] = half_of(b1, j);
-            }
-
-            // forward
-            u32x4 hb[4][KB];
-            {
-                f32x4 h[MT];
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) h[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-                hash_layer1_surface<PREC>(h, pk + kHashSecS, b0, b1, lane);
-                const uint16_t *gD = pk + kHashSecD;
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) h[mt] = mfma16<PREC>(*(const u32x4 *)(gD + (mt * 64 + lane) * 8), bd0, h[mt]);
-#pragma unroll
-                for (int kb = 0; kb < KB; ++kb) hb[0][kb] = chain_operand<PREC>(h[2 * kb], h[2 * kb + 1]);
-            }
-#pragma unroll
-            for (int l = 1; l < 4; ++l) {
-                const uint16_t *sec = pk + hash_sec(SEC_H0 + (l - 1));
-                f32x4 h[MT];
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) h[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
-                        h[mt] = mfma16<PREC>(*(const u32x4 *)(sec + ((mt * KB + kb) * 64 + lane) * 8), hb[l - 1][kb],
-                                             h[mt]);
-#pragma unroll
-                for (int kb = 0; kb < KB; ++kb) hb[l][kb] = chain_operand<PREC>(h[2 * kb], h[2 * kb + 1]);
-            }
-            f32x4 z5 = f32x4{0.f, 0.f, 0.f, 0.f};
-            {
-                const uint16_t *sec = pk + hash_sec(SEC_O);
-#pragma unroll
-                for (int kb = 0; kb < KB; ++kb) z5 = mfma16<PREC>(*(const u32x4 *)(sec + (kb * 64 + lane) * 8), hb[3][kb], z5);
-            }
-#pragma unroll
-            for (int l = 0; l < 4; ++l) stage_chain<W>(sH + l * W * kRow16, hb[l], g, s);
-
-            float d5[3] = {0.f, 0.f, 0.f};
-            if (g == 0 && valid) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    float lt;
-                    d5[c] = out_grad16(z5[c], args.target[3 * b + c], 0.0f, true, args.loss_eps, kscale, rel, 0.0f,
-                                       false, lt);
-                    loss_acc += lt;
-                }
-            }
-            if (g == 0) {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) sD5[c * kRow16 + s] = to16<PREC>(c < 3 ? d5[c] : 0.0f);
-            }
-
-            // backward
-            f32x4 dl[MT];
-            u32x4 db1[KB];   // delta1 as chained B operands
-            {
-                const u32x4 bop = g == 0 ? u32x4{pack2<PREC>(d5[0], d5[1]), pack2<PREC>(d5[2], 0.0f), 0u, 0u}
-                                         : u32x4{0u, 0u, 0u, 0u};
-                const uint16_t *sec = pk + hash_sec(SEC_OT);
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    dl[mt] = mfma16<PREC>(*(const u32x4 *)(sec + (mt * 64 + lane) * 8), bop, f32x4{0.f, 0.f, 0.f, 0.f});
-            }
-#pragma unroll
-            for (int l = 3; l >= 0; --l) {
-                u32x4 db[KB];
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const uint16_t hv = half_of(hb[l][mt >> 1], 4 * (mt & 1) + i);
-                        if (hv == 0) dl[mt][i] = 0.0f;
-                    }
-#pragma unroll
-                for (int kb = 0; kb < KB; ++kb) db[kb] = chain_plain<PREC>(dl[2 * kb], dl[2 * kb + 1]);
-                stage_chain<W>(sD + l * W * kRow16, db, g, s);
-                if (l == 0) {
-                    db1[0] = db[0];
-                    db1[1] = db[1];
-                    break;
-                }
-                const uint16_t *sec = pk + hash_sec(SEC_T0 + (l - 1));
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) dl[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
-                        dl[mt] = mfma16<PREC>(*(const u32x4 *)(sec + ((mt * KB + kb) * 64 + lane) * 8), db[kb], dl[mt]);
-            }
-            // gradient of the grid values: rows 16 mt + 4 g + i of W1_grid^T delta1 for this
-            // sample (column col); rows 2 k and 2 k + 1 are the two values of level k
-            const uint16_t *sec = pk + kHashSecTS;
-            f32x4 de[2];
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt) {
-                de[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int kb = 0; kb < KB; ++kb)
-                    de[mt] = mfma16<PREC>(*(const u32x4 *)(sec + ((mt * KB + kb) * 64 + lane) * 8), db1[kb],
-                                          de[mt]);
-            }
-            // (lane (g, col): levels 8 mt + 2 g and 8 mt + 2 g + 1 of sample col)
-            if (valid) {
-#pragma unroll
-                for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-                    for (int k = 0; k < 2; ++k) {
-                        const int level = 8 * mt + 2 * g + k;
-                        if (level < kHashLevels) {
-                            const float d0 = de[mt][2 * k], d1 = de[mt][2 * k + 1];
-                            grid_grad_check(gacc, d0, xs[0], xs[1], xs[2], s_lv[level].res);
-                            grid_grad_check(gacc, d1, xs[0], xs[1], xs[2], s_lv[level].res);
-                            bufs.dvals[level * stride + b] = make_float2(d0, d1);
-                        }
-                    }
-            }
-        }
-        __syncthreads();
-        // phase 2: owned weight-gradient tiles (W1: inputs 16 wave .. 16 wave + 15)
-#pragma unroll
-        for (int kb = 0; kb < kChunk16 / 32; ++kb) {
-            const int s0 = 32 * kb + 8 * g;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                const u32x4 bv = *(const u32x4 *)(sH + (a * W + 16 * wave + col) * kRow16 + s0);
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    const u32x4 av = *(const u32x4 *)(sD + ((a + 1) * W + 16 * mt + col) * kRow16 + s0);
-                    gh[a][mt] = mfma16<PREC>(av, bv, gh[a][mt]);
-                }
-            }
-            {
-                const u32x4 bv = *(const u32x4 *)(sH + (3 * W + 16 * wave + col) * kRow16 + s0);
-                u32x4 av = u32x4{0u, 0u, 0u, 0u};
-                if (col < 3) av = *(const u32x4 *)(sD5 + col * kRow16 + s0);
-                g5 = mfma16<PREC>(av, bv, g5);
-            }
-            {
-                const u32x4 bv = *(const u32x4 *)(sE + (16 * wave + col) * kRow16 + s0);
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    const u32x4 av = *(const u32x4 *)(sD + (16 * mt + col) * kRow16 + s0);
-                    g1[mt] = mfma16<PREC>(av, bv, g1[mt]);
-                }
-            }
-        }
-        __syncthreads();
-    }
-
-    float *out = partials + (int64_t)blockIdx.x * kHashMlp;
-    auto put = [&](int64_t i, float v) { out[i] = add ? out[i] + v : v; };
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) put((int64_t)(16 * mt + 4 * g + i) * kHashIn + 16 * wave + col, g1[mt][i]);
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                put(W * kHashIn + a * W * W + (int64_t)(16 * mt + 4 * g + i) * W + 16 * wave + col, gh[a][mt][i]);
-    if (g == 0) {
-#pragma unroll
-        for (int i = 0; i < 3; ++i) put(W * kHashIn + 3 * W * W + (int64_t)i * W + 16 * wave + col, g5[i]);
-    }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) loss_acc += __shfl_xor(loss_acc, d, 64);
-    if (lane == 0) sLoss[wave] = loss_acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float t = 0.0f;
-        for (int w = 0; w < kWaves16; ++w) t += sLoss[w];
-        loss_partials[blockIdx.x] = add ? loss_partials[blockIdx.x] + t : t;
-    }
+    grad64_block<1, PREC, false>(Points{}, q, packed, args, s_lv, bufs, gacc, add,
+                                 partials + (int64_t)blockIdx.x * kHashMlp, loss_partials + blockIdx.x, blockIdx.x,
+                                 gridDim.x, smem, sLoss);
 }
 
 hipError_t launch_hash_grad(int prec, const Queries &q, const uint16_t *packed, const HashGridArgs &grid, TrainArgs a,
@@ -990,10 +830,10 @@ hipError_t launch_hash_grad(int prec, const Queries &q, const uint16_t *packed, 
                             int nblocks, bool add, hipStream_t s) {
     if (!a.target) return hipErrorInvalidValue;
     if (prec == NIRC_BF16)
-        hipLaunchKernelGGL((k_hash_grad_h16<NIRC_BF16>), dim3(nblocks), dim3(kWaves16 * 64), 0, s, q, packed, grid, a,
+        hipLaunchKernelGGL((k_hash_grad_h16<NIRC_BF16>), dim3(nblocks), dim3(kWaves64 * 64), 0, s, q, packed, grid, a,
                            bufs, partials, loss_partials, gacc, add);
     else if (prec == NIRC_FP16)
-        hipLaunchKernelGGL((k_hash_grad_h16<NIRC_FP16>), dim3(nblocks), dim3(kWaves16 * 64), 0, s, q, packed, grid, a,
+        hipLaunchKernelGGL((k_hash_grad_h16<NIRC_FP16>), dim3(nblocks), dim3(kWaves64 * 64), 0, s, q, packed, grid, a,
                            bufs, partials, loss_partials, gacc, add);
     else
         return hipErrorInvalidValue;
