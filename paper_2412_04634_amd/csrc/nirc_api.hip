@@ -382,12 +382,12 @@ nirc_status tlmc_reference_occluded(nirc_points points, const nirc_lobes *field,
 }
 
 // Gradient partials + reduction into `grad`/`loss`; the step's `bad` flag is raised on a
-// non-finite value.
+// non-finite value.  draw: the kernel draws its queries.count samples (16-bit models of width 64).
 static nirc_status grad_into(nirc_model *model, const nirc_points &points, const nirc_queries &queries,
                              const float *target, const float *d_rgb, float *grad, float *loss, uint32_t *err,
-                             char *ws, size_t ws_bytes, hipStream_t s) {
+                             char *ws, size_t ws_bytes, hipStream_t s, const TrainDraw *draw = nullptr) {
     nirc_status st = check_points(points);
-    if (st == NIRC_OK) st = check_queries(queries, points);
+    if (st == NIRC_OK && !draw) st = check_queries(queries, points);
     if (st != NIRC_OK) return st;
     if (queries.count < 1 || !grad) return NIRC_ERR_INVALID_ARG;
     const bool h16 = model->packed16 != nullptr;
@@ -415,7 +415,7 @@ static nirc_status grad_into(nirc_model *model, const nirc_points &points, const
         a.fr = fr;
     }
     hipError_t e = h16 ? launch_grad_partials16(model->W, model->cfg.precision, to_points(points),
-                                                to_queries(queries, err), model->packed16, a, partials, lpart, nb, s)
+                                                to_queries(queries, err), model->packed16, a, partials, lpart, nb, s, draw)
                        : launch_grad_partials(model->W, to_points(points), to_queries(queries, err), model->packed, a,
                                               partials, lpart, nb, s);
     if (e != hipSuccess) return NIRC_ERR_HIP;
@@ -457,14 +457,15 @@ nirc_status nirc_adam_step(nirc_model *model, const float *grad, void *stream) {
 
 // Gradient into the workspace `ws`, then Adam on it.
 static nirc_status train_step_on(nirc_model *model, const nirc_points &points, const nirc_queries &queries,
-                                 const float *target, float *loss, char *ws, size_t ws_bytes, hipStream_t s) {
-    if (!model || !target) return NIRC_ERR_INVALID_ARG;
+                                 const float *target, float *loss, char *ws, size_t ws_bytes, hipStream_t s,
+                                 const TrainDraw *draw = nullptr) {
+    if (!model || (!target && !draw)) return NIRC_ERR_INVALID_ARG;
     const WorkLayout wl(model->W, grad_blocks(model->cfg.precision, queries.count));
     if (!ws || ws_bytes < wl.total) return NIRC_ERR_WORKSPACE;
     float *grad = (float *)(ws + wl.grad);
     float *wloss = (float *)(ws + wl.loss);
     nirc_status st =
-        grad_into(model, points, queries, target, nullptr, grad, loss ? loss : wloss, model->bad, ws, ws_bytes, s);
+        grad_into(model, points, queries, target, nullptr, grad, loss ? loss : wloss, model->bad, ws, ws_bytes, s, draw);
     if (st != NIRC_OK) return st;
     hipError_t e = launch_adam(model->W, model->master, model->m, model->v, grad, model->step, model->flags,
                                model->bad, model->cfg.lr, model->cfg.beta1, model->cfg.beta2, model->cfg.adam_eps,
@@ -533,6 +534,18 @@ nirc_status nirc_train_frame(nirc_model *model, nirc_points points, const nirc_l
     const WorkLayout wl(model->W, grad_blocks(model->cfg.precision, batch), var_rows(model->cfg, batch), batch);
     if (!model->ws || model->ws_bytes < wl.total) return NIRC_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
+    // 16-bit models of width 64: the gradient kernel draws its samples (the residual-variance loss
+    // goes over the targets twice and keeps them in memory)
+    if (model->packed16 && model->W == 64 && model->cfg.loss != NIRC_LOSS_VAR) {
+        TrainDraw draw{{(uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)frame, 0, model->cfg.output}, *field};
+        const nirc_queries q{nullptr, nullptr, nullptr, nullptr, batch};
+        for (int32_t k = 0; k < steps && st == NIRC_OK; ++k) {
+            draw.keys.step = (uint32_t)k;
+            st = train_step_on(model, points, q, nullptr, k + 1 == steps ? loss : nullptr, model->ws, model->ws_bytes, s,
+                               &draw);
+        }
+        return st;
+    }
     // the samples of up to kFrameSampleSteps steps in one launch (they do not depend on the
     // weights), 7 values per sample and step: point, wx, wy, wz, target x 3
     const int64_t stride = 7 * batch;
@@ -672,12 +685,6 @@ nirc_status nirc_train_list_build(const nirc_train_request *requests, int32_t n,
         t.lpart = (float *)(m->ws + wl.loss_partials);
         t.grad = (float *)(m->ws + wl.grad);
         t.loss = (float *)(m->ws + wl.loss);
-        float *smp = (float *)(m->ws + wl.samples);
-        t.sp = (int32_t *)smp;
-        t.swx = smp + r.batch;
-        t.swy = t.swx + r.batch;
-        t.swz = t.swy + r.batch;
-        t.stgt = t.swz + r.batch;
         t.batch = r.batch;
         t.key0 = (uint32_t)r.seed;
         t.key1 = (uint32_t)(r.seed >> 32);
@@ -711,7 +718,7 @@ nirc_status nirc_train_frame_batch(const void *list, int32_t steps, int32_t prec
     if (precision != NIRC_BF16 && precision != NIRC_FP16) return NIRC_ERR_UNSUPPORTED;
     hipStream_t s = (hipStream_t)stream;
     for (int32_t k = 0; k < steps; ++k) {
-        const hipError_t e = launch_train_step_multi((const TrainDesc *)list, precision, (uint32_t)k, max_batch, s);
+        const hipError_t e = launch_train_step_multi((const TrainDesc *)list, precision, (uint32_t)k, s);
         if (e != hipSuccess) return NIRC_ERR_HIP;
     }
     return NIRC_OK;

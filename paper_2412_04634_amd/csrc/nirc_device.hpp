@@ -68,6 +68,12 @@ __host__ inline DivN make_divn(int n) {
 __device__ __forceinline__ uint32_t div_n(uint32_t q, DivN d) { return d.n == 1 ? q : __umulhi(q, d.magic); }
 
 // ------------------------------------------------------------------------------------------
+// What a step's training samples are drawn with (the Philox key and counter words, NIRC_OUTPUT_*).
+struct DrawKeys {
+    uint32_t key0, key1, frame, step;
+    int32_t mode;
+};
+
 // Philox4x32-10 (Salmon et al., SC'11): multiply-xor rounds on a 4x32 counter, key bumped by
 // the Weyl constants between rounds.
 struct Rand4 {
@@ -248,6 +254,26 @@ __device__ inline float visibility(const nirc_lobes &L, float x0, float wx, floa
 }
 
 __device__ inline float logistic(float z) { return 1.0f / (1.0f + expf(-z)); }
+
+// Training sample b of a step: its point, and the two numbers that choose its direction.
+__device__ __forceinline__ int64_t train_point(int64_t count, uint32_t b, const DrawKeys &k, float &u1, float &u2) {
+    const Rand4 r = philox(b, k.step, k.frame, (uint32_t)kStreamTrain, k.key0, k.key1);
+    u1 = u24(r.r[1]);
+    u2 = u24(r.r[2]);
+    return (int64_t)(((uint64_t)r.r[0] * (uint64_t)count) >> 32);
+}
+
+// Its target: the field, or in the occluded scene the visibility V (the visibility cache) or V L.
+__device__ __forceinline__ void train_target(const nirc_lobes &lobes, int mode, float x0, float x1, float x2, float wx,
+                                             float wy, float wz, float L[3]) {
+    field_eval(lobes, x0, x1, x2, wx, wy, wz, L);
+    if (mode != NIRC_OUTPUT_RADIANCE) {
+        const float V = visibility(lobes, x0, wx, wy, wz);
+        L[0] = mode == NIRC_OUTPUT_VISIBILITY ? V : V * L[0];
+        L[1] = mode == NIRC_OUTPUT_VISIBILITY ? V : V * L[1];
+        L[2] = mode == NIRC_OUTPUT_VISIBILITY ? V : V * L[2];
+    }
+}
 
 // ------------------------------------------------------------------------------------------
 // MFMA wrappers (wave64).  16x16x4 FP32: lane l holds A[row l%16][k l/16], B[k l/16][col l%16];

@@ -556,9 +556,14 @@ __device__ __forceinline__ void grid_grad_check(const GridAcc &ga, float d, floa
 
 // exact: the cells' fractions from the unrounded position product (hash_cell): FP32 models.  first:
 // the batch's first part (clears the non-finite flag).
+// Where drawn samples' directions and targets [B][3] go.
+struct HashDrawn {
+    float *wx, *wy, *wz, *target;
+};
 hipError_t launch_hash_prep(const Points &pts, const Queries &q, const float *table, const HashGridArgs &grid,
                             const HashScatterPlan &plan, bool sliced, bool exact, bool first,
-                            const HashTrainBufs &bufs, GridAcc gacc, hipStream_t s);
+                            const HashTrainBufs &bufs, GridAcc gacc, hipStream_t s, const TrainDraw *draw,
+                            const HashDrawn &drawn);
 // The grid gradient from bufs.dvals by slices: Adam on the grid and (from mlp_grad) the MLP
 // parameters, or (adam false) the grid gradient times scale into grad (the grid's first entry).
 hipError_t launch_hash_scatter(const HashGridArgs &grid, const HashScatterPlan &plan, const HashTrainBufs &bufs,

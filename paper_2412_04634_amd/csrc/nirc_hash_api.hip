@@ -284,7 +284,7 @@ static hipError_t hash_adam(nirc_hash_model *model, const float *grad, hipStream
 // the whole step (the grid's part of grad is then not written).
 static nirc_status hash_grad_into(nirc_hash_model *model, const nirc_points &points, const nirc_queries &queries,
                                   const float *target, float *grad, float *loss, uint32_t *err, bool adam,
-                                  hipStream_t s) {
+                                  hipStream_t s, const TrainDraw *draw = nullptr, const HashDrawn &drawn = HashDrawn{}) {
     nirc_status st = check_points_h(points);
     if (st == NIRC_OK) st = check_queries_h(queries, points);
     if (st != NIRC_OK) return st;
@@ -326,7 +326,8 @@ static nirc_status hash_grad_into(nirc_hash_model *model, const nirc_points &poi
         // 16-bit operands; the FP32 kernel takes the same convention); the reductions divide it out
         const TrainArgs a{target + 3 * b0, nullptr, model->cfg.loss_eps, model->cfg.loss_scale * (float)n,
                           model->cfg.loss, nullptr, 0};
-        e = launch_hash_prep(pts_of(pp), q, model->table(), model->grid, plan, sliced, exact, b0 == 0, bufs, ga, s);
+        e = launch_hash_prep(pts_of(pp), q, model->table(), model->grid, plan, sliced, exact, b0 == 0, bufs, ga, s,
+                             draw, drawn);
         if (e == hipSuccess)
             e = model->cfg.precision == NIRC_FP32
                     ? launch_hash_grad32(q, model->packed32(), model->grid, a, bufs, partials, lpart, ga, nb, b0 > 0, s)
@@ -361,15 +362,22 @@ nirc_status nirc_hash_adam_step(nirc_hash_model *model, const float *grad, void 
     return hip_st(e);
 }
 
-nirc_status nirc_hash_train_step(nirc_hash_model *model, nirc_points points, nirc_queries queries,
-                                 const float *target, float *loss, void *stream) {
-    if (!model) return NIRC_ERR_INVALID_ARG;
-    hipStream_t s = (hipStream_t)stream;
+// draw: the samples are drawn into `drawn` (which queries and target name) on the way.
+static nirc_status hash_train_step_on(nirc_hash_model *model, const nirc_points &points, const nirc_queries &queries,
+                                      const float *target, float *loss, hipStream_t s, const TrainDraw *draw,
+                                      const HashDrawn &drawn) {
     if (!model->ws) return NIRC_ERR_WORKSPACE;
     // the reduced gradient's place does not depend on how much of the batch fits
     const HashWork wl(model->np, train_blocks16(queries.count > 0 ? queries.count : 1), 0);
     if (model->ws_bytes < wl.samples) return NIRC_ERR_WORKSPACE;
-    return hash_grad_into(model, points, queries, target, (float *)(model->ws + wl.grad), loss, model->bad, true, s);
+    return hash_grad_into(model, points, queries, target, (float *)(model->ws + wl.grad), loss, model->bad, true, s,
+                          draw, drawn);
+}
+
+nirc_status nirc_hash_train_step(nirc_hash_model *model, nirc_points points, nirc_queries queries,
+                                 const float *target, float *loss, void *stream) {
+    if (!model) return NIRC_ERR_INVALID_ARG;
+    return hash_train_step_on(model, points, queries, target, loss, (hipStream_t)stream, nullptr, HashDrawn{});
 }
 
 nirc_status nirc_hash_train_frame(nirc_hash_model *model, nirc_points points, const nirc_lobes *field,
@@ -382,14 +390,14 @@ nirc_status nirc_hash_train_frame(nirc_hash_model *model, nirc_points points, co
     if (!model->ws || model->ws_bytes < wl.total) return NIRC_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     float *smp = (float *)(model->ws + wl.samples);
-    int32_t *pidx = (int32_t *)smp;
-    float *wx = smp + batch, *wy = wx + batch, *wz = wy + batch, *tgt = wz + batch;
+    const HashDrawn drawn{smp, smp + batch, smp + 2 * batch, smp + 3 * batch};
+    // the workspace holds the whole batch, so that a step runs in one part; points are drawn and
+    // gathered in one kernel, which reads no indices (the pointer only says that they are not 0, 1, ...)
+    const nirc_queries q{drawn.wx, drawn.wy, drawn.wz, (const int32_t *)smp, batch};
+    TrainDraw draw{{(uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)frame, 0, NIRC_OUTPUT_RADIANCE}, *field};
     for (int32_t k = 0; k < steps; ++k) {
-        if (launch_train_batch(pts_of(points), *field, batch, seed, frame, (uint32_t)k, NIRC_OUTPUT_RADIANCE, pidx,
-                               wx, wy, wz, tgt, s) != hipSuccess)
-            return NIRC_ERR_HIP;
-        const nirc_queries q{wx, wy, wz, pidx, batch};
-        st = nirc_hash_train_step(model, points, q, tgt, k + 1 == steps ? loss : nullptr, s);
+        draw.keys.step = (uint32_t)k;
+        st = hash_train_step_on(model, points, q, drawn.target, k + 1 == steps ? loss : nullptr, s, &draw, drawn);
         if (st != NIRC_OK) return st;
     }
     return NIRC_OK;

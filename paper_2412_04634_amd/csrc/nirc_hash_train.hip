@@ -9,9 +9,10 @@
 //                    adds: the same sums in any order) and applies Adam to the slice, or writes its
 //                    gradient: no accumulator in memory to clear, add to and read back;
 //   k_hash_merge     the same for the small levels, whose slices several workgroups share.
-// BF16, 65,536 samples, the default grid: 1.42 -> 0.63 ms per 4-step frame; per step the gather takes
-// 8 + 24 us, the gradient kernel 32 (280 with gather and atomics inside), the sums with Adam 61 + 10
-// (clearing the accumulators, converting them and a separate Adam pass alone took 47).
+// BF16, 65,536 samples, the default grid: 1.42 -> 0.57 ms per 4-step frame; per step the gather takes
+// 11 + 24 us (the samples drawn on the way; 7 + 8 + 24 with a kernel of their own), the gradient kernel
+// 24 (280 with gather and atomics inside), the sums with Adam 61 + 10 (clearing the accumulators,
+// converting them and a separate Adam pass alone took 47).
 // Sums by global 64-bit atomics (k_hash_scatter_atomic) serve the grids the slices do not suit: the
 // memory side performs them at 16 G cache-line operations/s whatever the occupancy or the placement
 // (65,536 samples x 12 levels: 192 us measured alone; 12.6 M adds).
@@ -85,17 +86,32 @@ bool hash_scatter_plan(const HashGridArgs &grid, int64_t B, HashScatterPlan *p) 
 }
 
 // The samples' point attributes attr[B][8] (position, normal, roughness, 0), gathered once by point
-// index; clears the merged levels' accumulators and the non-finite flag.
-__global__ __launch_bounds__(256) void k_hash_points(Points pts, Queries q, int64_t merged_elems, HashTrainBufs bufs,
-                                                     GridAcc gacc, bool first) {
+// index; clears the merged levels' accumulators and the non-finite flag.  DRAW: a training frame's
+// samples are drawn here, their directions and targets written for the gradient kernel.
+template <bool DRAW>
+__global__ __launch_bounds__(256) void k_hash_points(Points pts, Queries q, TrainDraw draw, HashDrawn drawn,
+                                                     int64_t merged_elems, HashTrainBufs bufs, GridAcc gacc,
+                                                     bool first) {
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, nt = (int64_t)gridDim.x * blockDim.x;
     if (first && tid == 0) *gacc.nonfinite = 0u;
     for (int64_t i = tid; i < merged_elems; i += nt) gacc.acc[i] = 0ull;
     if (tid >= q.count) return;
-    const int64_t p = query_point(q, pts, tid);
+    float u1 = 0.0f, u2 = 0.0f;
+    const int64_t p = DRAW ? train_point(pts.count, (uint32_t)tid, draw.keys, u1, u2) : query_point(q, pts, tid);
+    const float x0 = pts.px[p], x1 = pts.py[p], x2 = pts.pz[p], n0 = pts.nx[p], n1 = pts.ny[p], n2 = pts.nz[p];
     f32x4 *a = (f32x4 *)(bufs.attr + 8 * tid);
-    a[0] = f32x4{pts.px[p], pts.py[p], pts.pz[p], pts.nx[p]};
-    a[1] = f32x4{pts.ny[p], pts.nz[p], pts.rough[p], 0.0f};
+    a[0] = f32x4{x0, x1, x2, n0};
+    a[1] = f32x4{n1, n2, pts.rough[p], 0.0f};
+    if constexpr (DRAW) {
+        float x, y, z, L[3];
+        cosine_dir(n0, n1, n2, u1, u2, x, y, z);
+        train_target(draw.lobes, draw.keys.mode, x0, x1, x2, x, y, z, L);
+        drawn.wx[tid] = x;
+        drawn.wy[tid] = y;
+        drawn.wz[tid] = z;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) drawn.target[3 * tid + c] = L[c];
+    }
 }
 
 // Blended grid values vals[level][stride] and, per level, the slices of a cell's four (y, z) corner
@@ -414,10 +430,15 @@ __global__ __launch_bounds__(256) void k_hash_scatter_atomic(HashGridArgs grid, 
 
 hipError_t launch_hash_prep(const Points &pts, const Queries &q, const float *table, const HashGridArgs &grid,
                             const HashScatterPlan &plan, bool sliced, bool exact, bool first, const HashTrainBufs &bufs,
-                            GridAcc gacc, hipStream_t s) {
+                            GridAcc gacc, hipStream_t s, const TrainDraw *draw, const HashDrawn &drawn) {
     static_assert(kHashLevels == 12, "8 XCDs: 8 levels, and two workgroup sets on each of the other 4");
-    hipLaunchKernelGGL(k_hash_points, dim3((unsigned)((q.count + 255) / 256)), dim3(256), 0, s, pts, q,
-                       sliced ? plan.merged_elems : 0, bufs, gacc, first);
+    const dim3 pg((unsigned)((q.count + 255) / 256));
+    const int64_t merged = sliced ? plan.merged_elems : 0;
+    if (draw)
+        hipLaunchKernelGGL(k_hash_points<true>, pg, dim3(256), 0, s, pts, q, *draw, drawn, merged, bufs, gacc, first);
+    else
+        hipLaunchKernelGGL(k_hash_points<false>, pg, dim3(256), 0, s, pts, q, TrainDraw{}, drawn, merged, bufs, gacc,
+                           first);
     int64_t per = (q.count + 255) / 256;   // workgroups per XCD
     if (per > 128) per = 128;
     const dim3 nb((unsigned)(8 * per)), block(256);

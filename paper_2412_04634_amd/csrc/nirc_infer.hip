@@ -166,56 +166,26 @@ hipError_t launch_reference_occluded(const Points &pts, const nirc_lobes &lobes,
     return hipGetLastError();
 }
 
-// Training samples: one thread per sample.
-__device__ __forceinline__ void train_sample(const Points &pts, const nirc_lobes &lobes, uint32_t key0, uint32_t key1,
-                                             uint32_t frame, uint32_t step, int mode, int64_t b, int32_t *point,
-                                             float *wx, float *wy, float *wz, float *target) {
-    const Rand4 r = philox((uint32_t)b, step, frame, (uint32_t)kStreamTrain, key0, key1);
-    const int64_t p = (int64_t)(((uint64_t)r.r[0] * (uint64_t)pts.count) >> 32);
-    float x, y, z;
-    cosine_dir(pts.nx[p], pts.ny[p], pts.nz[p], u24(r.r[1]), u24(r.r[2]), x, y, z);
-    float L[3];
-    field_eval(lobes, pts.px[p], pts.py[p], pts.pz[p], x, y, z, L);
-    if (mode != NIRC_OUTPUT_RADIANCE) {   // occluded scene: the visibility cache learns V, the other V L
-        const float V = visibility(lobes, pts.px[p], x, y, z);
-        L[0] = mode == NIRC_OUTPUT_VISIBILITY ? V : V * L[0];
-        L[1] = mode == NIRC_OUTPUT_VISIBILITY ? V : V * L[1];
-        L[2] = mode == NIRC_OUTPUT_VISIBILITY ? V : V * L[2];
-    }
-    point[b] = (int32_t)p;
-    wx[b] = x;
-    wy[b] = y;
-    wz[b] = z;
-    target[3 * b + 0] = L[0];
-    target[3 * b + 1] = L[1];
-    target[3 * b + 2] = L[2];
-}
-
-// Step step + blockIdx.y into the buffers offset by blockIdx.y * stride.
-__global__ void k_train_batch(Points pts, nirc_lobes lobes, int64_t batch, uint32_t key0,
-                              uint32_t key1, uint32_t frame, uint32_t step, int mode, int32_t *point,
+// Training samples, one thread per sample: step keys.step + blockIdx.y into the buffers offset by
+// blockIdx.y * stride.
+__global__ void k_train_batch(Points pts, nirc_lobes lobes, int64_t batch, DrawKeys keys, int32_t *point,
                               float *wx, float *wy, float *wz, float *target, int64_t stride) {
     const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= batch) return;
-    const int64_t o = (int64_t)blockIdx.y * stride;
-    train_sample(pts, lobes, key0, key1, frame, step + blockIdx.y, mode, b, point + o, wx + o, wy + o, wz + o,
-                 target + o);
-}
-
-// The training samples of step `step` of every request of a training work list (request
-// blockIdx.y), into each request's sample buffers.
-__global__ void k_train_batch_multi(const TrainDesc *__restrict__ desc, uint32_t step) {
-    if ((int)blockIdx.y >= desc->n) return;
-    const TrainReq &t = desc->req[blockIdx.y];
-    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= t.batch) return;
-    train_sample(t.pts, t.lobes, t.key0, t.key1, t.frame, step, t.output, b, t.sp, t.swx, t.swy, t.swz, t.stgt);
-}
-
-hipError_t launch_train_batch_multi(const TrainDesc *desc, uint32_t step, int64_t max_batch, hipStream_t s) {
-    hipLaunchKernelGGL(k_train_batch_multi, dim3((unsigned)((max_batch + 255) / 256), kBatchMaxRequests), dim3(256), 0,
-                       s, desc, step);
-    return hipGetLastError();
+    keys.step += blockIdx.y;
+    const int64_t o = (int64_t)blockIdx.y * stride + b;
+    float u1, u2, x, y, z, L[3];
+    const int64_t p = train_point(pts.count, (uint32_t)b, keys, u1, u2);
+    cosine_dir(pts.nx[p], pts.ny[p], pts.nz[p], u1, u2, x, y, z);
+    train_target(lobes, keys.mode, pts.px[p], pts.py[p], pts.pz[p], x, y, z, L);
+    point[o] = (int32_t)p;
+    wx[o] = x;
+    wy[o] = y;
+    wz[o] = z;
+    float *t = target + (int64_t)blockIdx.y * stride + 3 * b;
+    t[0] = L[0];
+    t[1] = L[1];
+    t[2] = L[2];
 }
 
 // ------------------------------------------------------------------------------------------
@@ -704,8 +674,8 @@ hipError_t launch_train_batch(const Points &pts, const nirc_lobes &lobes, int64_
                               int64_t stride) {
     if (batch == 0 || nsteps < 1) return hipSuccess;
     hipLaunchKernelGGL(k_train_batch, dim3((unsigned)((batch + 255) / 256), (unsigned)nsteps), dim3(256), 0, s, pts,
-                       lobes, batch, (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)frame, step, mode,
-                       point, wx, wy, wz, target, stride);
+                       lobes, batch, DrawKeys{(uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)frame, step, mode}, point,
+                       wx, wy, wz, target, stride);
     return hipGetLastError();
 }
 

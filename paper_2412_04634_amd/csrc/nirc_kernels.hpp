@@ -408,8 +408,6 @@ struct TrainReq {
     int64_t *step;
     uint32_t *flags, *bad;
     float *partials, *lpart, *grad, *loss;   // the model's workspace (WorkLayout of its batch)
-    int32_t *sp;                         // samples: point [B], wx, wy, wz [B], target [B][3]
-    float *swx, *swy, *swz, *stgt;
     int64_t batch;
     uint32_t key0, key1, frame;
     int32_t nb;                          // gradient blocks of this request
@@ -494,6 +492,16 @@ size_t frame_stats_scratch_bytes();
 hipError_t launch_accumulate(const float *v, int64_t n, double *sum, double *sumsq, hipStream_t s);
 
 // Training (gradient partials, reduction, Adam).
+// The partial gradients' reduction: 16 waves of a workgroup add a sixteenth of the slabs each, in
+// eight running sums (slab i of a wave's share in sum i % 8); up to 128 slabs are one term per sum.
+constexpr int kReduceWaves = 16, kReduceSums = 8, kReduceSlots = kReduceWaves * kReduceSums;
+
+// A training frame's step draws its samples in the gradient kernel.
+struct TrainDraw {
+    DrawKeys keys;
+    nirc_lobes lobes;
+};
+
 struct TrainArgs {
     const float *target;   // [B][3] for the loss, or NULL
     const float *d_rgb;    // [B][3] upstream gradient for the VJP, or NULL
@@ -560,7 +568,8 @@ int train_blocks(int64_t batch);     // workgroups used by the FP32 gradient ker
 int train_blocks16(int64_t batch);   // partial slabs a 16-bit model's workspace holds for a batch
 int grad_blocks16(int W, int64_t batch);   // workgroups (slabs written) of the 16-bit gradient kernel
 hipError_t launch_grad_partials16(int W, int prec, const Points &pts, const Queries &q, const void *packed,
-                                  TrainArgs a, float *partials, float *loss_partials, int nblocks, hipStream_t s);
+                                  TrainArgs a, float *partials, float *loss_partials, int nblocks, hipStream_t s,
+                                  const TrainDraw *draw = nullptr);
 hipError_t launch_grad_partials(int W, const Points &pts, const Queries &q, const float *packed,
                                 TrainArgs a, float *partials, float *loss_partials, int nblocks,
                                 hipStream_t s);
@@ -588,8 +597,7 @@ hipError_t launch_adam(int W, float *master, float *m, float *v, const float *gr
 // of step `step`, gradient partials, reduction, Adam and the 16-bit repack with the step commit.
 // Launch shapes depend only on the list's capacity, so the sequence can be captured in a graph
 // and replayed over other lists.
-hipError_t launch_train_step_multi(const TrainDesc *desc, int prec, uint32_t step, int64_t max_batch, hipStream_t s);
-hipError_t launch_train_batch_multi(const TrainDesc *desc, uint32_t step, int64_t max_batch, hipStream_t s);
+hipError_t launch_train_step_multi(const TrainDesc *desc, int prec, uint32_t step, hipStream_t s);
 // The estimator with its fusions undone (stages 0..2; 16-bit, width 64), for measuring them.
 size_t ablation_workspace_bytes(int64_t P, int n_cache, int stage);
 hipError_t launch_ablation(int prec, int stage, const Points &pts, const nirc_lobes &lobes, const uint16_t *packed,

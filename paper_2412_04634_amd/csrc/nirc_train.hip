@@ -594,7 +594,6 @@ __global__ __launch_bounds__(kTrainWaves * 64) void k_grad_f32_wide(Points pts, 
 // (one per lane) with 16 waves; wave w sums the w-th sixteenth of the partials with eight running
 // sums, then the sixteen wave sums are added in a fixed tree.  Raises `bad` on a non-finite
 // entry.  Block 0 also reduces the loss.
-constexpr int kReduceWaves = 16;
 
 __device__ __forceinline__ void reduce_grad_block(const float *__restrict__ partials,
                                                   const float *__restrict__ loss_partials, int nblocks, int64_t np,
@@ -606,12 +605,13 @@ __device__ __forceinline__ void reduce_grad_block(const float *__restrict__ part
     const int64_t i = (int64_t)blk * 64 + lane;
     const int per = (nblocks + kReduceWaves - 1) / kReduceWaves;
     const int b0 = min(nblocks, wave * per), b1 = min(nblocks, b0 + per);
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    static_assert(kReduceSums == 8, "the tree below adds eight running sums");
+    float acc[kReduceSums] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (i < np) {
         int b = b0;
-        for (; b + 8 <= b1; b += 8)
+        for (; b + kReduceSums <= b1; b += kReduceSums)
 #pragma unroll
-            for (int u = 0; u < 8; ++u) acc[u] += partials[(int64_t)(b + u) * np + i];
+            for (int u = 0; u < kReduceSums; ++u) acc[u] += partials[(int64_t)(b + u) * np + i];
         for (int u = 0; b < b1; ++b, ++u) acc[u] += partials[(int64_t)b * np + i];
     }
     q[wave][lane] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));

@@ -10,9 +10,8 @@ namespace nirc {
 
 namespace {
 
-// Width 64: workgroups of 8 waves, rounds of 128 samples (four 32-sample K-blocks).
+// Width 64: workgroups of 8 waves, rounds of two chunks (four 32-sample K-blocks).
 constexpr int kWaves64 = 8;
-constexpr int kChunk64 = 16 * kWaves64;
 
 // Width 128: workgroups of 4 waves, rounds of 64 samples (two 32-sample K-blocks).
 constexpr int kWaves16 = 4;
@@ -92,6 +91,23 @@ __device__ __forceinline__ void load_point16(const Points &pts, const Queries &q
     o.x[3] = pts.nx[p], o.x[4] = pts.ny[p], o.x[5] = pts.nz[p], o.x[6] = pts.rough[p];
 }
 
+// A training frame's sample, drawn where it is used: the lanes of a wave draw 64 samples together,
+// lane (g, c) that of slot c in the workgroup's g-th next round, and each round takes its own lanes'.
+struct Drawn16 {
+    float x[7], u1, u2, w[3], t[3];
+};
+
+__device__ __forceinline__ void draw_point16(const Points &pts, const DrawKeys &keys, int64_t b, Drawn16 &o) {
+    const int64_t p = train_point(pts.count, (uint32_t)b, keys, o.u1, o.u2);
+    o.x[0] = pts.px[p], o.x[1] = pts.py[p], o.x[2] = pts.pz[p];
+    o.x[3] = pts.nx[p], o.x[4] = pts.ny[p], o.x[5] = pts.nz[p], o.x[6] = pts.rough[p];
+}
+
+__device__ __forceinline__ void draw_target16(const nirc_lobes &lobes, const DrawKeys &keys, Drawn16 &o) {
+    cosine_dir(o.x[3], o.x[4], o.x[5], o.u1, o.u2, o.w[0], o.w[1], o.w[2]);
+    train_target(lobes, keys.mode, o.x[0], o.x[1], o.x[2], o.w[0], o.w[1], o.w[2], o.t);
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------------------------------
@@ -99,18 +115,23 @@ __device__ __forceinline__ void load_point16(const Points &pts, const Queries &q
 // its operands hold a neuron per lane and samples in registers, while the layer chain holds a sample
 // per lane and neurons in registers.  The change of sides is an MFMA too: with the chained
 // activations as the A operand, the product with a 0/1 selection matrix leaves lane (g, c) with neuron
-// c of samples 4 g + i - exactly the value each 16-bit operand holds - and the rows of two waves (32
-// samples in the order 4 g + i, 16 + 4 g + i, the same for both factors) make one operand.
+// c of rows 4 g + i - exactly the value each 16-bit operand holds - and the rows of two waves make one
+// operand: the even wave's columns are samples 8 (c / 4) + c % 4 of the 32, the odd wave's 4 further, so
+// that operand position 8 g + j is sample 8 g + j.
 //
-// A workgroup of 8 waves takes rounds of 128 samples, 16 per wave, forward and back, layer by layer
-// from the last: each wave turns its delta_{l+1} and h_l and puts them in LDS (8-byte stores in
+// A workgroup of 8 waves takes rounds of two 64-sample chunks, 16 samples per wave, forward and back,
+// layer by layer from the last: each wave turns its delta_{l+1} and h_l and puts them in LDS (8-byte stores in
 // operand order), and after one barrier each wave adds its own tiles of dW_{l+1} over the round's four
 // K-blocks while it goes on to delta_l (two buffers, so that a layer needs one barrier).
 // The forward weights are in LDS (51 KB), the transposed ones (28 KB, one CU's L1) in global memory.
 // Bound by LDS and VALU work together: per wave and round 78 MFMAs forward and back, 43 to turn the
 // operands, 46 for the gradient, against ~600 VALU instructions.
+// Of a 65,536-sample BF16 gradient's 26 us (two rounds per workgroup, one workgroup per CU), 5 were the
+// weights' and samples' first reads, one after the other, 10.8 and 8.8 the rounds, 2 the partials; with
+// the reads side by side and the samples drawn here, a frame of 4 steps takes 158 us, 187 with samples
+// from a kernel before (7 us per step) read back here.
 // (Before, four waves staged every value by a two-byte store as [neuron][sample] rows and read all
-// weights from L2: 36 us for a 65,536-sample BF16 gradient.)
+// weights from L2: 36 us.)
 //
 // ENC 0: the frequency input (10 input tiles of 16 features).  ENC 1: the hash-grid model's 64 inputs
 // (6 tiles: two per K-block of its surface and direction operands; unused columns are not written).
@@ -140,6 +161,54 @@ __device__ __forceinline__ u32x4 select_operand(int half, float odd, int g, int 
     return v;
 }
 
+// The chunks (64 samples) of partial slab `blk` of `nblk`: blk, blk + nblk, ..., added in turn.  Up to
+// 256 chunks have a slab of one chunk each; beyond 128 a workgroup takes the two that the reduction
+// adds first (reduce_grad_block) and stores their sum, so that every batch size has the sums of one
+// chunk at a time, whatever a workgroup takes at once.
+__host__ __device__ constexpr bool slab_pairs(int64_t B) {
+    const int64_t chunks = (B + kChunk16 - 1) / kChunk16;
+    return chunks > kReduceSlots && chunks <= 2 * kReduceSlots;
+}
+
+template <bool PAIR>
+struct SlabChunks {
+    int64_t first, step;
+    int count;
+    __device__ __forceinline__ SlabChunks(int64_t B, int64_t blk, int64_t nblk) {
+        const int64_t chunks = (B + kChunk16 - 1) / kChunk16;
+        if constexpr (PAIR) {
+            const int64_t per = (chunks + kReduceWaves - 1) / kReduceWaves, w = blk / kReduceSums;
+            first = w * per + blk % kReduceSums;
+            step = kReduceSums;
+            const int64_t end = min(chunks, (w + 1) * per);
+            count = (first < end ? 1 : 0) + (first + step < end ? 1 : 0);
+        } else {
+            first = blk;
+            step = nblk;
+            count = blk < chunks ? (int)((chunks - blk + nblk - 1) / nblk) : 0;
+        }
+    }
+    __device__ __forceinline__ int64_t chunk(int k) const { return first + k * step; }
+};
+
+// acc[i] += sum_k a(i, k) b(i, k) over a round's K-blocks: 0, 1 of its first chunk, 2, 3 of its second
+// (all zero deltas if it has none), in turn.  PAIR: the second chunk's sum by itself, then added.
+template <int PREC, int N, bool PAIR, typename A, typename B>
+__device__ __forceinline__ void add_products(f32x4 *acc, const A &a, const B &b) {
+    f32x4 t[N];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            if (PAIR && k >= 2) t[i] = mfma16<PREC>(a(i, k), b(i, k), k == 2 ? f32x4{0.f, 0.f, 0.f, 0.f} : t[i]);
+            else acc[i] = mfma16<PREC>(a(i, k), b(i, k), acc[i]);
+        }
+    if constexpr (PAIR) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc[i] += t[i];
+    }
+}
+
 // Zeroes the 16-bit halves of d whose activation (a ReLU output, never negative) is +0.
 __device__ __forceinline__ uint32_t relu_mask2(uint32_t d, uint32_t h) {
     typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
@@ -153,10 +222,12 @@ __device__ __forceinline__ uint32_t relu_mask2(uint32_t d, uint32_t h) {
 // floats.  Ends after a workgroup barrier, so a caller may run the next block on the same LDS.
 // PLAIN: the caller guarantees the common case (targets given, relative L2 of eq. 12, no
 // residual-variance mean, exp outputs), so the general loss arithmetic is compiled out.
-template <int ENC, int PREC, bool PLAIN>
+// PAIR: slab_pairs of the batch.  DRAW: the samples are drawn here (keys, lobes) instead of read from the queries and targets.
+template <int ENC, int PREC, bool PLAIN, bool DRAW, bool PAIR>
 __device__ __forceinline__ void grad64_block(const Points &pts, const Queries &q, const uint16_t *packed,
                                              const TrainArgs &args, const HashLevel *s_lv, const HashTrainBufs &bufs,
-                                             const GridAcc &gacc, bool add, float *out, float *loss_out, int64_t blk,
+                                             const GridAcc &gacc, bool add, const DrawKeys &keys,
+                                             const nirc_lobes *lobes, float *out, float *loss_out, int64_t blk,
                                              int64_t nblk, u32x4 *smem, float *sLoss) {
     using G = Grad64<ENC>;
     constexpr int MT = 4, KB = 2, W = 64;
@@ -165,15 +236,44 @@ __device__ __forceinline__ void grad64_block(const Points &pts, const Queries &q
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int col = lane & 15, g = lane >> 4;
     const int64_t B = q.count, stride = hash_level_stride(B);
-    const bool use_loss = PLAIN || ENC == 1 || args.target != nullptr;
+    const bool use_loss = PLAIN || DRAW || ENC == 1 || args.target != nullptr;
     // the host passes loss_scale * B for 16-bit models (or the dynamic scale is taken times B):
     // k = 2 loss_scale / 3 per sample
     const float ls = args.dyn_scale ? *args.dyn_scale * (float)B : args.loss_scale;
     const float kscale = use_loss ? 2.0f * ls / (3.0f * (float)B) : ls;
 
-    {
+    const SlabChunks<PAIR> sc(B, blk, nblk);
+    const int n_rounds = (sc.count + 1) >> 1;
+    // this lane's sample of round r: waves 0..3 hold the round's first chunk, 4..7 its second (B: none);
+    // the turned rows of a K-block come out in the order of its samples
+    auto sample_of = [&](int r) {
+        const int k = 2 * r + (wave >> 2);
+        const int s = 32 * ((wave >> 1) & 1) + 8 * (col >> 2) + 4 * (wave & 1) + (col & 3);
+        const int64_t b = k < sc.count ? sc.chunk(k) * kChunk16 + s : B;
+        return b < B ? b : B;
+    };
+    Sample16 next;
+    Drawn16 drawn;
+    {   // the forward sections, all their loads in flight together, the first samples' beside them
+        constexpr int N = (G::kFwd4 + kWaves64 * 64 - 1) / (kWaves64 * 64);
         const u32x4 *src = (const u32x4 *)packed;
-        for (int i = threadIdx.x; i < G::kFwd4; i += kWaves64 * 64) sF[i] = src[i];
+        u32x4 t[N];
+        if (ENC == 0 && !DRAW) load_query16(q, args, sample_of(0), B, next);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int k = i * kWaves64 * 64 + (int)threadIdx.x;
+            t[i] = src[k < G::kFwd4 ? k : 0];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (ENC == 0 && DRAW) draw_point16(pts, keys, min(sample_of(g), B - 1), drawn);
+        if constexpr (ENC == 0 && !DRAW) load_point16(pts, q, next);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int k = i * kWaves64 * 64 + (int)threadIdx.x;
+            if (k < G::kFwd4) sF[k] = t[i];
+        }
+        if (ENC == 0 && DRAW) draw_target16(*lobes, keys, drawn);
     }
     // this wave's tiles: W2..W4 column tile wave % 4, row tiles 2 (wave / 4) and the next; W5 column
     // tile wave (waves 0..3); W1 row tile wave % 4, input tiles wave / 4 + 2 j
@@ -197,25 +297,38 @@ __device__ __forceinline__ void grad64_block(const Points &pts, const Queries &q
     // row slots 0..3 of a buffer: delta; 4..7: activations
     auto buffer = [&]() { return sB + (phase & 1) * G::kBuf4; };
 
-    const int64_t n_chunks = (B + kChunk64 - 1) / kChunk64;
-    const int s = 16 * wave + col;   // sample slot in the round
-    Sample16 next;
-    if (ENC == 0 && blk < n_chunks) {
-        load_query16(q, args, blk * kChunk64 + s, B, next);
-        load_point16(pts, q, next);
-    }
     __syncthreads();
-    for (int64_t chunk = blk; chunk < n_chunks; chunk += nblk) {
+    for (int round = 0; round < n_rounds; ++round) {
         const uint16_t *pk = opaque(packed);
-        const int64_t b = chunk * kChunk64 + s;
+        const int64_t b = sample_of(round);
         const bool valid = b < B;
         const int64_t bi = valid ? b : B - 1;
-        const bool more = chunk + nblk < n_chunks;
+        const bool more = round + 1 < n_rounds;
         float xs[7], tg[3];
         u32x4 e[G::kInKb];   // input operands
+        // FP16: the first layer's gradient takes features rounded once from FP32 (half of a rounded
+        // 2 cos may be subnormal and round again, and the second sine is a product, rounded as one)
+        constexpr bool kOwnRows = ENC == 0 && PREC == NIRC_FP16;
+        if (kOwnRows && round > 0) __syncthreads();   // every wave is done with the previous round's input rows
         if constexpr (ENC == 0) {
-            const Sample16 cur = next;
-            if (more) load_query16(q, args, (chunk + nblk) * kChunk64 + s, B, next);
+            Sample16 cur;
+            if constexpr (DRAW) {
+                if (round > 0 && (round & 3) == 0) {
+                    draw_point16(pts, keys, min(sample_of(round + g), B - 1), drawn);
+                    draw_target16(*lobes, keys, drawn);
+                }
+                const int src = 16 * (round & 3) + col;
+#pragma unroll
+                for (int i = 0; i < 7; ++i) cur.x[i] = __shfl(drawn.x[i], src, 64);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    cur.w[i] = __shfl(drawn.w[i], src, 64);
+                    cur.t[i] = __shfl(drawn.t[i], src, 64);
+                }
+            } else {
+                cur = next;
+                if (more) load_query16(q, args, sample_of(round + 1), B, next);
+            }
             // scheduling fences between the steps of a round keep their loads and LDS traffic apart
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -227,6 +340,13 @@ __device__ __forceinline__ void grad64_block(const Points &pts, const Queries &q
                 if (i0 + 1 < (kb < 4 ? 7 : 3)) enc_pair2_fast(v[i0 + 1], g, f[4], f[5], f[6], f[7]);
                 e[kb] = u32x4{pack2<PREC>(f[0], f[1]), pack2<PREC>(f[2], f[3]), pack2<PREC>(f[4], f[5]),
                               pack2<PREC>(f[6], f[7])};
+                if constexpr (kOwnRows) {
+                    const uint32_t s0 = to16<PREC>(f[0] * f[1]), s1 = to16<PREC>(f[4] * f[5]);
+                    const u32x4 r = {pack2<PREC>(f[0], 0.5f * f[1]), s0 | (uint32_t)to16<PREC>(0.5f * f[3]) << 16,
+                                     pack2<PREC>(f[4], 0.5f * f[5]), s1 | (uint32_t)to16<PREC>(0.5f * f[7]) << 16};
+                    put(sE + (kb < 4 ? i0 : 7 + i0) * 256, r, sel[0]);
+                    if (i0 + 1 < (kb < 4 ? 7 : 3)) put(sE + (kb < 4 ? i0 + 1 : 8 + i0) * 256, r, sel[1]);
+                }
             }
 #pragma unroll
             for (int c = 0; c < 3; ++c) tg[c] = cur.t[c];
@@ -282,7 +402,7 @@ __device__ __forceinline__ void grad64_block(const Points &pts, const Queries &q
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb)
             z5 = mfma16<PREC>(*(const u32x4 *)(fw + G::sec(SEC_O) + (kb * 64 + lane) * 8), hb[3][kb], z5);
-        if constexpr (ENC == 0) {
+        if constexpr (ENC == 0 && !DRAW) {
             __builtin_amdgcn_sched_barrier(0);
             if (more) load_point16(pts, q, next);
         }
@@ -313,16 +433,14 @@ __device__ __forceinline__ void grad64_block(const Points &pts, const Queries &q
 #pragma unroll
             for (int n = 0; n < 4; ++n) put(buf + (4 + n) * 256, hb[3][n >> 1], sel[n & 1]);
             __syncthreads();
-            if (wave < 4) {
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    g5 = mfma16<PREC>(buf[k * 64 + lane], buf[(4 + own_n) * 256 + k * 64 + lane], g5);
-            }
+            if (wave < 4)
+                add_products<PREC, 1, PAIR>(&g5, [&](int, int k) { return buf[k * 64 + lane]; },
+                                      [&](int, int k) { return buf[(4 + own_n) * 256 + k * 64 + lane]; });
             ++phase;
         }
         // the inputs' turned rows (every wave is past the previous round's last use of them)
 #pragma unroll
-        for (int i = 0; i < G::kIn; ++i) {
+        for (int i = 0; i < (kOwnRows ? 0 : G::kIn); ++i) {
             // ENC 0: surface inputs 0..6 in K-blocks 0..3, directions 0..2 in 4, 5
             const int kb = ENC == 1 ? i >> 1 : i < 7 ? i >> 1 : 4 + ((i - 7) >> 1);
             const int half = ENC == 1 ? i & 1 : i < 7 ? i & 1 : (i - 7) & 1;
@@ -382,25 +500,14 @@ __device__ __forceinline__ void grad64_block(const Points &pts, const Queries &q
                 }
             }
             __syncthreads();
-            if (l > 0) {
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const u32x4 bv = buf[(4 + own_n) * 256 + k * 64 + lane];
-#pragma unroll
-                    for (int m = 0; m < 2; ++m)
-                        gh[l - 1][m] = mfma16<PREC>(buf[(own_m + m) * 256 + k * 64 + lane], bv, gh[l - 1][m]);
-                }
-            } else {
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const u32x4 av = buf[own_n * 256 + k * 64 + lane];
-#pragma unroll
-                    for (int j = 0; j < G::kOwnIn; ++j) {
-                        const int i = (wave >> 2) + 2 * j;
-                        if (i < G::kIn) g1[j] = mfma16<PREC>(av, sE[i * 256 + k * 64 + lane], g1[j]);
-                    }
-                }
-            }
+            if (l > 0)
+                add_products<PREC, 2, PAIR>(gh[l > 0 ? l - 1 : 0],
+                                      [&](int m, int k) { return buf[(own_m + m) * 256 + k * 64 + lane]; },
+                                      [&](int, int k) { return buf[(4 + own_n) * 256 + k * 64 + lane]; });
+            else
+                add_products<PREC, G::kOwnIn, PAIR>(
+                    g1, [&](int, int k) { return buf[own_n * 256 + k * 64 + lane]; },
+                    [&](int j, int k) { return sE[((wave >> 2) + 2 * j) * 256 + k * 64 + lane]; });
             ++phase;
         }
     }
@@ -446,24 +553,38 @@ __device__ __forceinline__ void grad64_block(const Points &pts, const Queries &q
     __syncthreads();
 }
 
-template <int PREC, bool PLAIN>
+template <int PREC, bool PLAIN, bool PAIR>
 __global__ __launch_bounds__(kWaves64 * 64) void k_grad_h16(Points pts, Queries q, const uint16_t *__restrict__ packed,
                                                             TrainArgs args, float *__restrict__ partials,
                                                             float *__restrict__ loss_partials) {
     __shared__ u32x4 smem[Grad64<0>::kTotal4];
     __shared__ float sLoss[kWaves64];
-    grad64_block<0, PREC, PLAIN>(pts, q, packed, args, nullptr, HashTrainBufs{}, GridAcc{}, false,
-                                 partials + (int64_t)blockIdx.x * n_params(64), loss_partials + blockIdx.x, blockIdx.x,
-                                 gridDim.x, smem, sLoss);
+    grad64_block<0, PREC, PLAIN, false, PAIR>(pts, q, packed, args, nullptr, HashTrainBufs{}, GridAcc{}, false, DrawKeys{},
+                                        nullptr, partials + (int64_t)blockIdx.x * n_params(64),
+                                        loss_partials + blockIdx.x, blockIdx.x, gridDim.x, smem, sLoss);
+}
+
+// A training frame's step: the same over the `batch` samples it draws.
+template <int PREC, bool PLAIN, bool PAIR>
+__global__ __launch_bounds__(kWaves64 * 64) void k_grad_h16_draw(Points pts, int64_t batch, TrainDraw draw,
+                                                                 const uint16_t *__restrict__ packed, TrainArgs args,
+                                                                 float *__restrict__ partials,
+                                                                 float *__restrict__ loss_partials) {
+    __shared__ u32x4 smem[Grad64<0>::kTotal4];
+    __shared__ float sLoss[kWaves64];
+    const Queries q{nullptr, nullptr, nullptr, nullptr, batch, nullptr};
+    grad64_block<0, PREC, PLAIN, true, PAIR>(pts, q, packed, args, nullptr, HashTrainBufs{}, GridAcc{}, false, draw.keys,
+                                       &draw.lobes, partials + (int64_t)blockIdx.x * n_params(64),
+                                       loss_partials + blockIdx.x, blockIdx.x, gridDim.x, smem, sLoss);
 }
 
 // The gradient step of several models at once (continuous batching of the streams' training
 // passes): request r's workgroups are the virtual blocks vb0 .. vb0 + nb - 1 of the list, and a
 // fixed grid walks the virtual blocks in order.  Virtual block b of a request computes exactly
-// what block b of k_grad_h16 computes for that request alone (same chunks, same order), so the
+// what block b of k_grad_h16_draw computes for that request alone (same chunks, same order), so the
 // partials, and everything after them, are bit-identical.
 template <int PREC>
-__global__ __launch_bounds__(kWaves64 * 64) void k_grad_h16_multi(const TrainDesc *__restrict__ desc) {
+__global__ __launch_bounds__(kWaves64 * 64) void k_grad_h16_multi(const TrainDesc *__restrict__ desc, uint32_t step) {
     __shared__ u32x4 smem[Grad64<0>::kTotal4];
     __shared__ float sLoss[kWaves64];
     const int n = desc->n, total = desc->total_vb;
@@ -472,11 +593,15 @@ __global__ __launch_bounds__(kWaves64 * 64) void k_grad_h16_multi(const TrainDes
         while (r + 1 < n && desc->req[r + 1].vb0 <= v) ++r;
         const TrainReq &t = desc->req[r];
         const int b = v - t.vb0;
-        const Queries q{t.swx, t.swy, t.swz, t.sp, t.batch, t.bad};
-        const TrainArgs a{t.stgt, nullptr, t.loss_eps, t.loss_scale * (float)t.batch, t.loss_kind, nullptr,
+        const Queries q{nullptr, nullptr, nullptr, nullptr, t.batch, nullptr};
+        const TrainArgs a{nullptr, nullptr, t.loss_eps, t.loss_scale * (float)t.batch, t.loss_kind, nullptr,
                           t.output == NIRC_OUTPUT_VISIBILITY, t.dyn_scale};
-        grad64_block<0, PREC, false>(t.pts, q, t.packed16, a, nullptr, HashTrainBufs{}, GridAcc{}, false,
-                                     t.partials + (int64_t)b * n_params(64), t.lpart + b, b, t.nb, smem, sLoss);
+        if (slab_pairs(t.batch))
+            grad64_block<0, PREC, false, true, true>(t.pts, q, t.packed16, a, nullptr, HashTrainBufs{}, GridAcc{}, false,
+                                         DrawKeys{t.key0, t.key1, t.frame, step, t.output}, &t.lobes, t.partials + (int64_t)b * n_params(64), t.lpart + b, b, t.nb, smem, sLoss);
+        else
+            grad64_block<0, PREC, false, true, false>(t.pts, q, t.packed16, a, nullptr, HashTrainBufs{}, GridAcc{}, false,
+                                         DrawKeys{t.key0, t.key1, t.frame, step, t.output}, &t.lobes, t.partials + (int64_t)b * n_params(64), t.lpart + b, b, t.nb, smem, sLoss);
     }
 }
 
@@ -750,19 +875,21 @@ __global__ __launch_bounds__(kWaves16 * 64) void k_grad_h16_wide(Points pts, Que
     }
 }
 
-static int blocks_of(int64_t batch, int chunk) {
-    int64_t chunks = (batch + chunk - 1) / chunk;
+int train_blocks16(int64_t batch) {
+    int64_t chunks = (batch + kChunk16 - 1) / kChunk16;
     if (chunks > kMaxResidentBlocks) chunks = kMaxResidentBlocks;
     return (int)(chunks < 1 ? 1 : chunks);
 }
 
-int train_blocks16(int64_t batch) { return blocks_of(batch, kChunk16); }
-
-int grad_blocks16(int W, int64_t batch) { return blocks_of(batch, W == 64 ? kChunk64 : kChunk16); }
+int grad_blocks16(int W, int64_t batch) {
+    return W == 64 && slab_pairs(batch) ? kReduceSlots : train_blocks16(batch);
+}
 
 hipError_t launch_grad_partials16(int W, int prec, const Points &pts, const Queries &q, const void *packed,
-                                  TrainArgs a, float *partials, float *loss_partials, int nblocks, hipStream_t s) {
+                                  TrainArgs a, float *partials, float *loss_partials, int nblocks, hipStream_t s,
+                                  const TrainDraw *draw) {
     const uint16_t *pk = (const uint16_t *)packed;
+    if (draw && W != 64) return hipErrorInvalidValue;
     if (W == 128) {
         const dim3 grid(nblocks), block(kWaves16 * 64);
         if (prec == NIRC_BF16) {
@@ -779,27 +906,35 @@ hipError_t launch_grad_partials16(int W, int prec, const Points &pts, const Quer
         return hipGetLastError();
     }
     if (W != 64) return hipErrorInvalidValue;
-    const bool plain = a.target && a.loss_kind == NIRC_LOSS_REL_L2 && !a.fr && !a.sig;
-    const dim3 grid(nblocks), block(kWaves64 * 64);
-    if (prec == NIRC_BF16 && plain)
-        hipLaunchKernelGGL((k_grad_h16<NIRC_BF16, true>), grid, block, 0, s, pts, q, pk, a, partials, loss_partials);
-    else if (prec == NIRC_BF16)
-        hipLaunchKernelGGL((k_grad_h16<NIRC_BF16, false>), grid, block, 0, s, pts, q, pk, a, partials, loss_partials);
-    else if (plain)
-        hipLaunchKernelGGL((k_grad_h16<NIRC_FP16, true>), grid, block, 0, s, pts, q, pk, a, partials, loss_partials);
-    else
-        hipLaunchKernelGGL((k_grad_h16<NIRC_FP16, false>), grid, block, 0, s, pts, q, pk, a, partials, loss_partials);
+    const bool plain = (draw || a.target) && a.loss_kind == NIRC_LOSS_REL_L2 && !a.fr && !a.sig;
+    auto go = [&](auto P, auto plainc, auto pairc) {
+        constexpr int PR = decltype(P)::value;
+        constexpr bool PL = decltype(plainc)::value, PA = decltype(pairc)::value;
+        const dim3 grid(nblocks), block(kWaves64 * 64);
+        if (draw)
+            hipLaunchKernelGGL((k_grad_h16_draw<PR, PL, PA>), grid, block, 0, s, pts, q.count, *draw, pk, a, partials,
+                               loss_partials);
+        else
+            hipLaunchKernelGGL((k_grad_h16<PR, PL, PA>), grid, block, 0, s, pts, q, pk, a, partials, loss_partials);
+    };
+    const bool pair = slab_pairs(q.count);
+    auto with_prec = [&](auto P) {
+        if (plain && pair) go(P, std::true_type{}, std::true_type{});
+        else if (plain) go(P, std::true_type{}, std::false_type{});
+        else if (pair) go(P, std::false_type{}, std::true_type{});
+        else go(P, std::false_type{}, std::false_type{});
+    };
+    if (prec == NIRC_BF16) with_prec(std::integral_constant<int, NIRC_BF16>{});
+    else with_prec(std::integral_constant<int, NIRC_FP16>{});
     return hipGetLastError();
 }
 
-hipError_t launch_train_step_multi(const TrainDesc *desc, int prec, uint32_t step, int64_t max_batch, hipStream_t s) {
-    hipError_t e = launch_train_batch_multi(desc, step, max_batch, s);
-    if (e != hipSuccess) return e;
+hipError_t launch_train_step_multi(const TrainDesc *desc, int prec, uint32_t step, hipStream_t s) {
     if (prec == NIRC_BF16)
-        hipLaunchKernelGGL((k_grad_h16_multi<NIRC_BF16>), dim3(kMaxResidentBlocks), dim3(kWaves64 * 64), 0, s, desc);
+        hipLaunchKernelGGL((k_grad_h16_multi<NIRC_BF16>), dim3(kMaxResidentBlocks), dim3(kWaves64 * 64), 0, s, desc, step);
     else
-        hipLaunchKernelGGL((k_grad_h16_multi<NIRC_FP16>), dim3(kMaxResidentBlocks), dim3(kWaves64 * 64), 0, s, desc);
-    e = hipGetLastError();
+        hipLaunchKernelGGL((k_grad_h16_multi<NIRC_FP16>), dim3(kMaxResidentBlocks), dim3(kWaves64 * 64), 0, s, desc, step);
+    hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = launch_reduce_grad_multi(desc, 64, s);
     if (e == hipSuccess) e = launch_adam_pack16_multi(desc, 64, prec, s);
     return e;
@@ -809,7 +944,7 @@ hipError_t launch_train_step_multi(const TrainDesc *desc, int prec, uint32_t ste
 // The hash-grid model: grad64_block with the 64 grid / SH / phi inputs, the grid values blended
 // beforehand (bufs.vals).  Each sample's gradient with respect to its 24 grid values (W1_grid^T
 // delta1, from the TS section) goes to bufs.dvals for the grid-entry sums.
-template <int PREC>
+template <int PREC, bool PAIR>
 __global__ __launch_bounds__(kWaves64 * 64) void k_hash_grad_h16(Queries q, const uint16_t *__restrict__ packed,
                                                                  HashGridArgs grid, TrainArgs args, HashTrainBufs bufs,
                                                                  float *__restrict__ partials,
@@ -820,23 +955,25 @@ __global__ __launch_bounds__(kWaves64 * 64) void k_hash_grad_h16(Queries q, cons
     __shared__ HashLevel s_lv[kHashLevels];
     stage_levels(s_lv, grid);
     __syncthreads();
-    grad64_block<1, PREC, false>(Points{}, q, packed, args, s_lv, bufs, gacc, add,
-                                 partials + (int64_t)blockIdx.x * kHashMlp, loss_partials + blockIdx.x, blockIdx.x,
-                                 gridDim.x, smem, sLoss);
+    grad64_block<1, PREC, false, false, PAIR>(Points{}, q, packed, args, s_lv, bufs, gacc, add, DrawKeys{}, nullptr,
+                                        partials + (int64_t)blockIdx.x * kHashMlp, loss_partials + blockIdx.x,
+                                        blockIdx.x, gridDim.x, smem, sLoss);
 }
 
 hipError_t launch_hash_grad(int prec, const Queries &q, const uint16_t *packed, const HashGridArgs &grid, TrainArgs a,
                             const HashTrainBufs &bufs, float *partials, float *loss_partials, GridAcc gacc,
                             int nblocks, bool add, hipStream_t s) {
     if (!a.target) return hipErrorInvalidValue;
-    if (prec == NIRC_BF16)
-        hipLaunchKernelGGL((k_hash_grad_h16<NIRC_BF16>), dim3(nblocks), dim3(kWaves64 * 64), 0, s, q, packed, grid, a,
-                           bufs, partials, loss_partials, gacc, add);
-    else if (prec == NIRC_FP16)
-        hipLaunchKernelGGL((k_hash_grad_h16<NIRC_FP16>), dim3(nblocks), dim3(kWaves64 * 64), 0, s, q, packed, grid, a,
-                           bufs, partials, loss_partials, gacc, add);
-    else
-        return hipErrorInvalidValue;
+    if (prec != NIRC_BF16 && prec != NIRC_FP16) return hipErrorInvalidValue;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(kWaves64 * 64), 0, s, q, packed, grid, a, bufs, partials,
+                           loss_partials, gacc, add);
+    };
+    const bool pair = slab_pairs(q.count);
+    if (prec == NIRC_BF16 && pair) go(k_hash_grad_h16<NIRC_BF16, true>);
+    else if (prec == NIRC_BF16) go(k_hash_grad_h16<NIRC_BF16, false>);
+    else if (pair) go(k_hash_grad_h16<NIRC_FP16, true>);
+    else go(k_hash_grad_h16<NIRC_FP16, false>);
     return hipGetLastError();
 }
 
