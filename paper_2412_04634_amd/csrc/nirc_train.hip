@@ -590,40 +590,56 @@ __global__ __launch_bounds__(kTrainWaves * 64) void k_grad_f32_wide(Points pts, 
     }
 }
 
-// grad[i] = inv_scale * sum_blk partials[blk][i] in a fixed order: a block handles 64 parameters
-// (one per lane) with 16 waves; wave w sums the w-th sixteenth of the partials with eight running
-// sums, then the sixteen wave sums are added in a fixed tree.  Raises `bad` on a non-finite
-// entry.  Block 0 also reduces the loss.
+// grad[i] = inv_scale * sum_blk partials[blk][i] in a fixed order: a workgroup handles 64 V parameters
+// (V consecutive ones per lane) with 16 waves; wave w sums the w-th sixteenth of the partials with
+// eight running sums, then the sixteen wave sums are added in a fixed tree.  Raises `bad` on a
+// non-finite entry.  Workgroup 0 also reduces the loss.
+template <int V>
+struct ReduceVec {
+    typedef float T __attribute__((ext_vector_type(V)));
+};
+template <>
+struct ReduceVec<1> {
+    typedef float T;
+};
 
+template <int V>
 __device__ __forceinline__ void reduce_grad_block(const float *__restrict__ partials,
                                                   const float *__restrict__ loss_partials, int nblocks, int64_t np,
                                                   float inv_scale, float loss_norm, float *__restrict__ grad,
                                                   float *__restrict__ loss, uint32_t *bad, int blk,
-                                                  float (*q)[64], const float *dyn_scale, float dyn_batch) {
+                                                  typename ReduceVec<V>::T (*q)[64], const float *dyn_scale,
+                                                  float dyn_batch) {
+    using T = typename ReduceVec<V>::T;
     if (dyn_scale) inv_scale = 1.0f / (*dyn_scale * dyn_batch);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t i = (int64_t)blk * 64 + lane;
+    const int64_t i = ((int64_t)blk * 64 + lane) * V;
     const int per = (nblocks + kReduceWaves - 1) / kReduceWaves;
     const int b0 = min(nblocks, wave * per), b1 = min(nblocks, b0 + per);
     static_assert(kReduceSums == 8, "the tree below adds eight running sums");
-    float acc[kReduceSums] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    T acc[kReduceSums] = {};
     if (i < np) {
         int b = b0;
         for (; b + kReduceSums <= b1; b += kReduceSums)
 #pragma unroll
-            for (int u = 0; u < kReduceSums; ++u) acc[u] += partials[(int64_t)(b + u) * np + i];
-        for (int u = 0; b < b1; ++b, ++u) acc[u] += partials[(int64_t)b * np + i];
+            for (int u = 0; u < kReduceSums; ++u) acc[u] += *(const T *)(partials + (int64_t)(b + u) * np + i);
+        for (int u = 0; b < b1; ++b, ++u) acc[u] += *(const T *)(partials + (int64_t)b * np + i);
     }
     q[wave][lane] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
     __syncthreads();
     if (wave == 0 && i < np) {
-        float t[kReduceWaves / 2];
+        T t[kReduceWaves / 2];
 #pragma unroll
         for (int k = 0; k < kReduceWaves / 2; ++k) t[k] = q[2 * k][lane] + q[2 * k + 1][lane];
-        const float sum = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
-        const float gi = sum * inv_scale;
-        grad[i] = gi;
-        if (bad && !isfinite(gi)) atomicOr(bad, NIRC_FLAG_NONFINITE_GRAD);
+        const T gi = (((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]))) * inv_scale;
+        *(T *)(grad + i) = gi;
+        bool finite = true;
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            const float *e = (const float *)&gi;
+            finite = finite && isfinite(e[k]);
+        }
+        if (bad && !finite) atomicOr(bad, NIRC_FLAG_NONFINITE_GRAD);
     }
     // the loss: lane-strided sums of the partials, then a fixed shuffle tree (one wave, so the
     // loads are in flight together rather than one dependent load per partial)
@@ -647,21 +663,30 @@ __global__ __launch_bounds__(kReduceWaves * 64) void k_reduce_grad(const float *
                                                                    float *__restrict__ loss, uint32_t *bad,
                                                                    const float *dyn_scale, float dyn_batch) {
     __shared__ float q[kReduceWaves][64];
-    reduce_grad_block(partials, loss_partials, nblocks, np, inv_scale, loss_norm, grad, loss, bad, blockIdx.x, q,
-                      dyn_scale, dyn_batch);
+    reduce_grad_block<1>(partials, loss_partials, nblocks, np, inv_scale, loss_norm, grad, loss, bad, blockIdx.x, q,
+                         dyn_scale, dyn_batch);
 }
 
-// The reduction of every request of a training work list (request blockIdx.y), with the scale
-// factors each request's own step uses (16-bit models: loss_scale * B).
+// The reduction of every request of a training work list, with the scale factors each request's own
+// step uses (16-bit models: loss_scale * B).  A fixed grid walks the requests' workgroups one after
+// the other, whatever the list's length (a grid row for each request that a list may hold: 20,590 of
+// 22,720 workgroups of a 6-request list had nothing to do), four parameters per lane.
+// 6 x 16,384 samples: 30.4 -> 15.5 us (70 MB).
+constexpr int kReduceMultiVec = 4;
+
 __global__ __launch_bounds__(kReduceWaves * 64) void k_reduce_grad_multi(const TrainDesc *__restrict__ desc) {
-    __shared__ float q[kReduceWaves][64];
-    if ((int)blockIdx.y >= desc->n) return;
-    const TrainReq &t = desc->req[blockIdx.y];
-    const int64_t np = n_params(desc->width);
-    if ((int64_t)blockIdx.x * 64 >= np) return;
-    const float scale = t.loss_scale * (float)t.batch;
-    reduce_grad_block(t.partials, t.lpart, t.nb, np, 1.0f / scale, 1.0f / (3.0f * (float)t.batch), t.grad, t.loss,
-                      t.bad, blockIdx.x, q, t.dyn_scale, (float)t.batch);
+    constexpr int64_t np = n_params(64);
+    constexpr int V = kReduceMultiVec, per = (int)((np + 64 * V - 1) / (64 * V));
+    static_assert(np % V == 0, "a lane's parameters are all there or none");
+    __shared__ ReduceVec<V>::T q[kReduceWaves][64];
+    const int total = desc->n * per;
+    for (int item = blockIdx.x; item < total; item += gridDim.x) {
+        const TrainReq &t = desc->req[item / per];
+        const float scale = t.loss_scale * (float)t.batch;
+        reduce_grad_block<V>(t.partials, t.lpart, t.nb, np, 1.0f / scale, 1.0f / (3.0f * (float)t.batch), t.grad, t.loss,
+                             t.bad, item % per, q, t.dyn_scale, (float)t.batch);
+        __syncthreads();
+    }
 }
 
 __global__ void k_check_finite(const float *__restrict__ grad, int64_t np, uint32_t *bad) {
@@ -702,11 +727,13 @@ __global__ __launch_bounds__(kAdamThreads) void k_adam_pack32(float *__restrict_
                                                      float eps) {
     constexpr int64_t np = n_params(W);
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < np && *bad == 0u) {
-        const float t = (float)(*step + 1);
+    const bool on = i < np;
+    const int64_t j = on ? i : 0;
+    float mi = m[j], vi = v[j];
+    const float w0 = w[j], gi = grad[j], t = (float)(*step + 1);   // read beside `bad`, not after it
+    if (on && *bad == 0u) {
         const float c1 = 1.0f - powf(b1, t), c2 = 1.0f - powf(b2, t);
-        float mi = m[i], vi = v[i];
-        const float wi = adam_update(w[i], mi, vi, grad[i], c1, c2, lr, b1, b2, eps);
+        const float wi = adam_update(w0, mi, vi, gi, c1, c2, lr, b1, b2, eps);
         m[i] = mi;
         v[i] = vi;
         w[i] = wi;
@@ -714,11 +741,10 @@ __global__ __launch_bounds__(kAdamThreads) void k_adam_pack32(float *__restrict_
         const int n = f32_packed_targets(W, i, e);
         for (int k = 0; k < n; ++k) packed[e[k]] = wi;
     }
+    // no fence beyond the workgroup's: see adam_pack16_block
     __syncthreads();
     if (threadIdx.x == 0) {
-        __threadfence();
         if (atomicAdd(done, 1u) == gridDim.x - 1u) {
-            __threadfence();
             commit_step(step, flags, bad, nullptr, nullptr);
             *done = 0u;
         }
@@ -838,9 +864,8 @@ hipError_t launch_adam(int W, float *master, float *m, float *v, const float *gr
 }
 
 hipError_t launch_reduce_grad_multi(const TrainDesc *desc, int W, hipStream_t s) {
-    const int64_t np = n_params(W);
-    hipLaunchKernelGGL(k_reduce_grad_multi, dim3((unsigned)((np + 63) / 64), kBatchMaxRequests),
-                       dim3(kReduceWaves * 64), 0, s, desc);
+    if (W != 64) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_reduce_grad_multi, dim3(2 * kMaxResidentBlocks), dim3(kReduceWaves * 64), 0, s, desc);
     return hipGetLastError();
 }
 
