@@ -382,7 +382,7 @@ nirc_status tlmc_reference_occluded(nirc_points points, const nirc_lobes *field,
 }
 
 // Gradient partials + reduction into `grad`/`loss`; the step's `bad` flag is raised on a
-// non-finite value.  draw: the kernel draws its queries.count samples (16-bit models of width 64).
+// non-finite value.  draw: the kernel draws its queries.count samples (width 64).
 static nirc_status grad_into(nirc_model *model, const nirc_points &points, const nirc_queries &queries,
                              const float *target, const float *d_rgb, float *grad, float *loss, uint32_t *err,
                              char *ws, size_t ws_bytes, hipStream_t s, const TrainDraw *draw = nullptr) {
@@ -392,7 +392,7 @@ static nirc_status grad_into(nirc_model *model, const nirc_points &points, const
     if (queries.count < 1 || !grad) return NIRC_ERR_INVALID_ARG;
     const bool h16 = model->packed16 != nullptr;
     const int slabs = grad_blocks(model->cfg.precision, queries.count);
-    const int nb = h16 ? grad_blocks16(model->W, queries.count) : slabs;
+    const int nb = h16 ? grad_blocks16(model->W, queries.count) : grad_blocks32(model->W, queries.count, target || draw);
     const bool var = target && model->cfg.loss == NIRC_LOSS_VAR;
     const WorkLayout wl(model->W, slabs, var ? queries.count : 0);
     if (!ws || ws_bytes < wl.total) return NIRC_ERR_WORKSPACE;
@@ -417,7 +417,7 @@ static nirc_status grad_into(nirc_model *model, const nirc_points &points, const
     hipError_t e = h16 ? launch_grad_partials16(model->W, model->cfg.precision, to_points(points),
                                                 to_queries(queries, err), model->packed16, a, partials, lpart, nb, s, draw)
                        : launch_grad_partials(model->W, to_points(points), to_queries(queries, err), model->packed, a,
-                                              partials, lpart, nb, s);
+                                              partials, lpart, nb, s, draw);
     if (e != hipSuccess) return NIRC_ERR_HIP;
     const float loss_norm = 1.0f / (3.0f * (float)queries.count);
     e = launch_reduce_grad(model->W, partials, lpart, nb, 1.0f / scale, loss_norm, grad, loss, model->bad, s,
@@ -534,9 +534,9 @@ nirc_status nirc_train_frame(nirc_model *model, nirc_points points, const nirc_l
     const WorkLayout wl(model->W, grad_blocks(model->cfg.precision, batch), var_rows(model->cfg, batch), batch);
     if (!model->ws || model->ws_bytes < wl.total) return NIRC_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
-    // 16-bit models of width 64: the gradient kernel draws its samples (the residual-variance loss
-    // goes over the targets twice and keeps them in memory)
-    if (model->packed16 && model->W == 64 && model->cfg.loss != NIRC_LOSS_VAR) {
+    // width 64: the gradient kernel draws its samples (the residual-variance loss goes over the
+    // targets twice and keeps them in memory)
+    if (model->W == 64 && model->cfg.loss != NIRC_LOSS_VAR) {
         TrainDraw draw{{(uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)frame, 0, model->cfg.output}, *field};
         const nirc_queries q{nullptr, nullptr, nullptr, nullptr, batch};
         for (int32_t k = 0; k < steps && st == NIRC_OK; ++k) {

@@ -564,7 +564,8 @@ __device__ inline void commit_step(int64_t *step, uint32_t *flags, uint32_t *bad
 // summed in a fixed order; part holds kFrBlocks x 3 floats.
 constexpr int kFrBlocks = 256;
 hipError_t launch_residual_mean(const float *y, const float *t, int64_t B, float *part, float *fr, hipStream_t s);
-int train_blocks(int64_t batch);     // workgroups used by the FP32 gradient kernel for a batch
+int train_blocks(int64_t batch);     // partial slabs an FP32 model's workspace holds for a batch
+int grad_blocks32(int W, int64_t batch, bool loss);   // ... that it launches (slabs written); loss: targets given
 int train_blocks16(int64_t batch);   // partial slabs a 16-bit model's workspace holds for a batch
 int grad_blocks16(int W, int64_t batch);   // workgroups (slabs written) of the 16-bit gradient kernel
 hipError_t launch_grad_partials16(int W, int prec, const Points &pts, const Queries &q, const void *packed,
@@ -572,7 +573,7 @@ hipError_t launch_grad_partials16(int W, int prec, const Points &pts, const Quer
                                   const TrainDraw *draw = nullptr);
 hipError_t launch_grad_partials(int W, const Points &pts, const Queries &q, const float *packed,
                                 TrainArgs a, float *partials, float *loss_partials, int nblocks,
-                                hipStream_t s);
+                                hipStream_t s, const TrainDraw *draw = nullptr);
 // dyn_scale (nullable): the gradient is divided by dyn_scale * dyn_batch instead of multiplied by
 // inv_scale.
 hipError_t launch_reduce_grad(int W, const float *partials, const float *loss_partials, int nblocks,

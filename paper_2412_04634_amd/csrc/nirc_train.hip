@@ -1,6 +1,7 @@
 // Training kernels: fused forward + relative-L2 loss + backward to per-workgroup weight-gradient
 // partials, a fixed-order reduction, and Adam with a refresh of the packed weights.
-#include "nirc_hash.hpp"
+#include "nirc_grad.hpp"
+#include "nirc_split.hpp"
 
 namespace nirc {
 
@@ -16,9 +17,11 @@ struct GradLds {
     static constexpr int kD = 4 * W * kStride;     // delta1..delta4
     static constexpr int kD5 = 4 * kStride;        // output-layer delta, rows 0..3
     static constexpr int kX = kChunk * kInputs;    // raw inputs [sample][10]
-    static constexpr int kLoss = kTrainWaves;
-    static constexpr int kTotal = kH + kD + kD5 + kX + kLoss;
+    static constexpr int kTotal = kH + kD + kD5 + kX;
 };
+
+// Samples of a workgroup's round in k_grad_split.
+__host__ __device__ constexpr int split_round(int64_t batch) { return batch <= 64 * kMaxResidentBlocks ? 64 : 128; }
 
 // Output-pre-activation gradient and loss term of one channel.
 // rel: the relative loss (denominator y^2 + eps held constant), else den = 1; fr: the F_r shift of
@@ -45,10 +48,9 @@ __device__ inline float out_grad(float z, float t, float dr, bool use_loss, floa
 // LDS as [neuron][sample].  Phase 2: each wave owns a fixed set of 16x16 weight-gradient tiles
 // (a quarter of every layer's column tiles) held in registers across rounds, and adds the
 // round's 64 samples with MFMAs whose K dimension is the sample index.  At the end every tile is
-// written once into this workgroup's partial gradient (canonical layout).
-// PLAIN: targets given, relative L2 of eq. 12, no residual-variance mean, exp outputs (the general
-// loss arithmetic compiled out).
-template <int W, bool PLAIN = false>
+// written once into this workgroup's partial gradient (canonical layout).  For upstream gradients of
+// any range (nirc_backward); loss gradients take k_grad_split.
+template <int W>
 __global__ __launch_bounds__(kTrainWaves * 64) void k_grad_f32(Points pts, Queries q,
                                                                const float *__restrict__ packed,
                                                                TrainArgs args, float *__restrict__ partials,
@@ -63,12 +65,10 @@ __global__ __launch_bounds__(kTrainWaves * 64) void k_grad_f32(Points pts, Queri
     float *sD = sH + S::kH;
     float *sD5 = sD + S::kD;
     float *sX = sD5 + S::kD5;
-    float *sLoss = sX + S::kX;
 
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
     const int64_t B = q.count;
-    const bool use_loss = PLAIN || args.target != nullptr;
-    const float kscale = use_loss ? 2.0f * args.loss_scale / (3.0f * (float)B) : args.loss_scale;
+    const float kscale = args.loss_scale;
 
     // owned gradient tiles: first layer input columns {wave, wave+4, wave+8} (< 10), column tile
     // `wave` of W2..W4 and of W5
@@ -81,7 +81,6 @@ __global__ __launch_bounds__(kTrainWaves * 64) void k_grad_f32(Points pts, Queri
             gh[a][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
     g5 = f32x4{0.f, 0.f, 0.f, 0.f};
-    float loss_acc = 0.0f;
 
     const int64_t n_chunks = (B + kChunk - 1) / kChunk;
     for (int64_t chunk = blockIdx.x; chunk < n_chunks; chunk += gridDim.x) {
@@ -149,14 +148,9 @@ __global__ __launch_bounds__(kTrainWaves * 64) void k_grad_f32(Points pts, Queri
             if (g == 0 && valid) {
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
-                    const float t = use_loss ? args.target[3 * b + c] : 0.0f;
-                    const float dr = use_loss ? 0.0f : args.d_rgb[3 * b + c];
                     float lt;
-                    d5[c] = PLAIN ? out_grad(z5[c], t, 0.0f, true, args.loss_eps, kscale, true, 0.0f, false, lt)
-                                  : out_grad(z5[c], t, dr, use_loss, args.loss_eps, kscale,
-                                             args.loss_kind == NIRC_LOSS_REL_L2, args.fr ? args.fr[c] : 0.0f,
-                                             args.sig != 0, lt);
-                    loss_acc += lt;
+                    d5[c] = out_grad(z5[c], 0.0f, args.d_rgb[3 * b + c], false, args.loss_eps, kscale, false, 0.0f,
+                                     args.sig != 0, lt);
                 }
             }
             if (g == 0) {
@@ -285,14 +279,446 @@ __global__ __launch_bounds__(kTrainWaves * 64) void k_grad_f32(Points pts, Queri
 #pragma unroll
         for (int i = 0; i < 3; ++i) out[w_offset(W, 4) + (int64_t)i * W + 16 * wave + col] = g5[i];
     }
-    // loss partial: fixed-order wave sum, then waves in order
+    if (threadIdx.x == 0) loss_partials[blockIdx.x] = 0.0f;
+}
+
+// ------------------------------------------------------------------------------------------
+// Loss gradients of FP32 models.  The forward pass and the deltas keep the FP32 MFMA chain (operation
+// for operation: a ReLU decision that rounding moved would change a sample's gradient by more than
+// rounding does, and an FP16 MFMA cuts the smaller products of a group at 2^-24 of the largest, which
+// every sample's deltas would share).  The weight gradients' sums over the samples take two-term FP16
+// operands (x s = h + l; h h + h l + l h in three 16x16x32 MFMAs of 16 cycles instead of eight FP32 ones
+// of 32): their errors are the samples' own and average out.
+//
+// Scales: every operand set is scaled by an exact power of two that puts the largest magnitude the
+// workgroup has met in it (a layer's activations, a layer's deltas) in [2^14, 2^15), so that a value's
+// error is at most 2^-39 of that largest, and 22 bits are kept of a value within 2^-16 of it.  The maxima
+// only grow; when one does, the sums held in registers are rescaled (exactly).  An upstream gradient of
+// the caller's may span any range and stays with k_grad_f32.
+//
+// The weight gradient's operands hold a neuron per lane and samples in registers: each term is turned by
+// an MFMA with a 0/1 selection matrix, as in the 16-bit kernels.  A workgroup of 8 waves takes rounds of
+// 128 samples, 16 per wave (64 samples, a wave per SIMD, while one round of those covers the batch).
+// LDS, 160 KB: the first layer's weights; the hidden layers', whose room takes the transposed ones once
+// the forward pass is through and, with the activations' room, the turned inputs at the end; one layer's
+// turned activations and deltas.
+// 65,536 samples: 116 us (FP32 MFMA throughout, four waves, weights from L2, and 7 more for a kernel that
+// drew the samples) -> 86, of which 9 are the samples' gather, 2 x 36 the rounds (17 of MFMA each).
+struct GradSplit {
+    static constexpr int kW1 = 0, kHT = 2560, kAct = kHT + 3072, kDel = kAct + 2048, kX = kDel + 2048, kW5 = kX + 320,
+                         kD5 = kW5 + 48, kMax = kD5 + 96, kLoss = kMax + 18, kTotal = kLoss + 2;   // u32x4
+    static constexpr int kRows = 512;   // a turned tile: [K-block][term][lane]
+    // kMax: each wave's largest magnitudes of activations h1..h4, the output delta, deltas 1..4
+    static constexpr int mH = 0, mD5 = 4, mD = 5, mCount = 9;
+};
+constexpr int kSplitGradWaves = 8;
+
+// The workgroup's exponent of a magnitude from its waves' (FP32 bits), within the range that scales can
+// follow.
+__device__ __forceinline__ int exp_of(const u32x4 *waves) {
+    const u32x4 a = waves[0], b = waves[1];
+    const uint32_t m = max(max(max(a[0], a[1]), max(a[2], a[3])), max(max(b[0], b[1]), max(b[2], b[3])));
+    const int e = (int)(__builtin_amdgcn_readfirstlane(m) >> 23) - 127;
+    return e < -100 ? -100 : e;
+}
+// Largest of a wave's values.
+__device__ __forceinline__ uint32_t wave_max(uint32_t m) {
+#define NIRC_DPP_MAX(ctrl) m = max(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, ctrl, 0xF, 0xF, false))
+    NIRC_DPP_MAX(0xB1);    // lanes 1 apart
+    NIRC_DPP_MAX(0x4E);    // 2 apart
+    NIRC_DPP_MAX(0x141);   // mirrored in 8
+    NIRC_DPP_MAX(0x140);   // mirrored in 16
+#undef NIRC_DPP_MAX
+    const auto a = __builtin_amdgcn_permlane16_swap(m, m, false, false);
+    m = max((uint32_t)a[0], (uint32_t)a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+    return max((uint32_t)b[0], (uint32_t)b[1]);
+}
+__device__ __forceinline__ float pow2f(int e) { return __builtin_bit_cast(float, (uint32_t)(127 + e) << 23); }
+__device__ __forceinline__ uint32_t mag_bits(float x) { return __builtin_bit_cast(uint32_t, x) & 0x7FFFFFFFu; }
+
+// acc += a b over `kb` K-blocks of turned tiles, both operands in two terms.
+template <int N, typename A, typename B>
+__device__ __forceinline__ void add_split(f32x4 *acc, bool four, const A &a, const B &b) {
+    auto block = [&](int k) {
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) loss_acc += __shfl_xor(loss_acc, d, 64);
+        for (int i = 0; i < N; ++i) acc[i] = mfma16<NIRC_FP16>(a(i, k, 1), b(i, k, 0), acc[i]);
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc[i] = mfma16<NIRC_FP16>(a(i, k, 0), b(i, k, 1), acc[i]);
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc[i] = mfma16<NIRC_FP16>(a(i, k, 0), b(i, k, 0), acc[i]);
+    };
+    block(0);
+    block(1);
+    if (!four) return;
+    block(2);
+    block(3);
+}
+
+template <bool PLAIN, bool DRAW>
+__global__ __launch_bounds__(kSplitGradWaves * 64) void k_grad_split(Points pts, Queries q, TrainDraw draw,
+                                                                     const float *__restrict__ packed, TrainArgs args,
+                                                                     float *__restrict__ partials,
+                                                                     float *__restrict__ loss_partials) {
+    using G = GradSplit;
+    constexpr F32Layout L{64};
+    constexpr int W = 64, MT = 4, KQ = 4, NT = kSplitGradWaves * 64;
+    static_assert(L.offset(SEC_S) == 0 && L.offset(SEC_D) + L.size(SEC_D) == 4 * G::kHT &&
+                      L.offset(SEC_H0) == 4 * G::kHT && L.offset(SEC_H2) + L.size(SEC_H2) == 4 * G::kAct,
+                  "the forward sections are one run");
+    static_assert(sizeof(u32x4) * G::kTotal <= 163840, "fits the LDS");
+    __shared__ u32x4 smem[G::kTotal];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int col = lane & 15, g = lane >> 4;
+    const int64_t B = q.count;
+    uint32_t *sMax = (uint32_t *)(smem + G::kMax);
+    const bool use_loss = PLAIN || DRAW || args.target != nullptr;
+    const float kscale = use_loss ? 2.0f * args.loss_scale / (3.0f * (float)B) : args.loss_scale;
+    const int round_samples = split_round(B);
+    const bool four = round_samples == 128, active = four || wave < 4;
+    const int64_t n_chunks = (B + round_samples - 1) / round_samples, nblk = gridDim.x;
+    auto sample_of = [&](int64_t chunk) {
+        const int64_t b = chunk * round_samples + 16 * wave + col;
+        return b < B ? b : B;
+    };
+
+    // ---------------- prologue: forward weights to LDS, the transposed weights' range, first samples
+    TrainSample next;
+    DrawnSample drawn;
+    if (threadIdx.x < G::mCount * kSplitGradWaves) sMax[threadIdx.x] = 0u;   // (waves without samples leave theirs)
+    if constexpr (!DRAW) load_query(q, args, sample_of(blockIdx.x), B, next);
+    {
+        constexpr int N = G::kAct / NT;
+        static_assert(G::kAct % NT == 0, "whole turns");
+        u32x4 t[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) t[i] = ((const u32x4 *)packed)[i * NT + threadIdx.x];
+        f32x4 w5 = f32x4{0.f, 0.f, 0.f, 0.f};   // (channel c, K-quad kq, lane group gg): W5[c][16 kq + 4 gg ..]
+        const int c5 = (int)threadIdx.x / 16, n5 = threadIdx.x & 15;
+        if (threadIdx.x < 48) w5 = *(const f32x4 *)(packed + L.offset(SEC_O) + ((n5 >> 2) * 64 + 16 * (n5 & 3) + c5) * 4);
+        if constexpr (DRAW)
+            draw_point(pts, draw.keys, min(sample_of(blockIdx.x + g * nblk), B - 1), drawn);
+        else
+            load_point(pts, q, next);
+#pragma unroll
+        for (int i = 0; i < N; ++i) smem[i * NT + threadIdx.x] = t[i];
+        if (threadIdx.x < 48) ((f32x4 *)(smem + G::kW5))[c5 * 16 + n5] = w5;
+        if constexpr (DRAW) draw_target(draw.lobes, draw.keys, drawn);
+    }
+    __syncthreads();
+    // this wave's tiles: W2..W4 column tile wave % 4, row tiles 2 (wave / 4) and the next; W5 column
+    // tile wave (waves 0..3); W1 row tile wave % 4, inputs wave / 4 + 2 j
+    const int own_n = wave & 3, own_m = 2 * (wave >> 2);
+    f32x4 gh[3][2], g1[5], g5 = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) gh[a][0] = gh[a][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 5; ++j) g1[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // the largest exponents met: activations, output delta, deltas
+    int eH[4] = {-100, -100, -100, -100}, eD5 = -100, eD[4] = {-100, -100, -100, -100};
+    // exponents of the operands in the sums: W1, W2, W3, W4, W5
+    int eg[5] = {-1000, -1000, -1000, -1000, -1000};
+    auto rescale = [&](int k, int e, f32x4 *acc, int n) {
+        if (e == eg[k]) return;
+        if (eg[k] != -1000)
+#pragma unroll
+            for (int i = 0; i < n; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[i][r] = ldexpf(acc[i][r], eg[k] - e);
+        eg[k] = e;
+    };
+    float loss_acc = 0.0f;
+    const u32x4 sel[2] = {select_operand<NIRC_FP16>(0, 1.0f, g, col), select_operand<NIRC_FP16>(1, 1.0f, g, col)};
+    // both terms of this wave's samples, turned: half an operand of K-block wave / 2
+    auto put = [&](u32x4 *tile, const u32x4 &h, const u32x4 &l, const u32x4 &sl) {
+        const f32x4 th = mfma16<NIRC_FP16>(h, sl, f32x4{0.f, 0.f, 0.f, 0.f});
+        const f32x4 tl = mfma16<NIRC_FP16>(l, sl, f32x4{0.f, 0.f, 0.f, 0.f});
+        uint2 *d = (uint2 *)(tile + (wave >> 1) * 128 + lane) + (wave & 1);
+        d[0] = make_uint2(pack2<NIRC_FP16>(th[0], th[1]), pack2<NIRC_FP16>(th[2], th[3]));
+        d[128] = make_uint2(pack2<NIRC_FP16>(tl[0], tl[1]), pack2<NIRC_FP16>(tl[2], tl[3]));
+    };
+    auto put_layer = [&](u32x4 *tiles, const f32x4 (&v)[MT], float scale) {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            const float x[8] = {v[2 * kb][0],     v[2 * kb][1],     v[2 * kb][2],     v[2 * kb][3],
+                                v[2 * kb + 1][0], v[2 * kb + 1][1], v[2 * kb + 1][2], v[2 * kb + 1][3]};
+            u32x4 vh, vl;
+            split8(x, scale, vh, vl);
+            put(tiles + (2 * kb) * G::kRows, vh, vl, sel[0]);
+            put(tiles + (2 * kb + 1) * G::kRows, vh, vl, sel[1]);
+        }
+    };
+    auto note_max = [&](int word, uint32_t m) {
+        m = wave_max(m);
+        if (lane == 0) sMax[word * kSplitGradWaves + wave] = m;
+    };
+    auto take_max = [&](int &e, int word) { e = max(e, exp_of((const u32x4 *)(sMax + word * kSplitGradWaves))); };
+    auto layer_max = [&](const f32x4 (&v)[MT]) {
+        uint32_t m = 0u;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int i = 0; i < 4; i += 2) {
+                const float x = v[mt][i], y = v[mt][i + 1];
+                m = max(max(m, mag_bits(x)), mag_bits(y));
+            }
+        return m;
+    };
+    u32x4 *sAct = smem + G::kAct, *sDel = smem + G::kDel, *sE = smem + G::kHT;
+    float *sX = (float *)(smem + G::kX);
+    const f32x4 *sW5 = (const f32x4 *)(smem + G::kW5);
+    uint16_t *sD5 = (uint16_t *)(smem + G::kD5);   // [K-block][term][lane group][channel][8]
+
+    int round = 0;
+    for (int64_t chunk = blockIdx.x; chunk < n_chunks; chunk += nblk, ++round) {
+        const float *pk = opaque(packed);
+        const int64_t b = sample_of(chunk);
+        const bool valid = b < B, more = chunk + nblk < n_chunks;
+        if (round > 0) {   // the hidden layers' weights again, where the turned inputs were
+            constexpr int N = (G::kAct - G::kHT) / NT;
+            u32x4 t[N];
+#pragma unroll
+            for (int i = 0; i < N; ++i) t[i] = ((const u32x4 *)pk)[G::kHT + i * NT + threadIdx.x];
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < N; ++i) smem[G::kHT + i * NT + threadIdx.x] = t[i];
+            __syncthreads();
+        }
+        f32x4 h[4][MT], d[MT];   // h1..h4; a layer's delta
+        float d5[3] = {0.f, 0.f, 0.f};
+        if (active) {
+            float xs[7], ws[3], tg[3];
+            if constexpr (DRAW) {
+                if (round > 0 && (round & 3) == 0) {
+                    draw_point(pts, draw.keys, min(sample_of(chunk + g * nblk), B - 1), drawn);
+                    draw_target(draw.lobes, draw.keys, drawn);
+                }
+                const int src = 16 * (round & 3) + col;
+#pragma unroll
+                for (int i = 0; i < 7; ++i) xs[i] = __shfl(drawn.x[i], src, 64);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    ws[i] = __shfl(drawn.w[i], src, 64);
+                    tg[i] = __shfl(drawn.t[i], src, 64);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 7; ++i) xs[i] = next.x[i];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) ws[i] = next.w[i], tg[i] = next.t[i];
+                if (more) load_query(q, args, sample_of(chunk + nblk), B, next);
+            }
+            if (g == 0) {
+                float *x = sX + (16 * wave + col) * kInputs;
+#pragma unroll
+                for (int i = 0; i < 7; ++i) x[i] = xs[i];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) x[7 + i] = ws[i];
+            }
+            // ---------------- forward (the operations of grad_f32_block)
+            const float *sw = (const float *)smem;
+            {
+                f32x4 a1[1][MT];
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) a1[0][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+                layer1_surface<W>(a1[0], sw + L.offset(SEC_S), xs, lane, g);
+                const float dx[1] = {ws[0]}, dy[1] = {ws[1]}, dz[1] = {ws[2]};
+                layer1_direction<W, 1>(a1, sw + L.offset(SEC_D), dx, dy, dz, lane, g);
+                relu_all<W, 1>(a1);
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) h[0][mt] = a1[0][mt];
+            }
+            uint32_t mh[4];
+            mh[0] = layer_max(h[0]);
+#pragma unroll
+            for (int l = 1; l < 4; ++l) {
+                const float *sec = sw + L.offset(SEC_H0 + (l - 1));
+                f32x4 o[MT];
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) o[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int kq = 0; kq < KQ; ++kq) {
+                    f32x4 a[MT];
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) a[mt] = *(const f32x4 *)(sec + ((mt * KQ + kq) * 64 + lane) * 4);
+#pragma unroll
+                    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt) o[mt] = mfma4(a[mt][kk], h[l - 1][kq][kk], o[mt]);
+                }
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) h[l][mt][i] = relu_f32(o[mt][i]);
+                mh[l] = layer_max(h[l]);
+            }
+            if constexpr (!DRAW)
+                if (more) load_point(pts, q, next);
+            // output layer and the last layer's delta on the vector units: every lane group has its own
+            // 16 neurons of the sample
+            f32x4 w5[3][MT];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                float z = 0.0f;
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    w5[c][mt] = sW5[c * 16 + 4 * mt + g];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) z = fmaf(w5[c][mt][i], h[3][mt][i], z);
+                }
+                z += __shfl_xor(z, 16);
+                z += __shfl_xor(z, 32);
+                const float t = use_loss ? tg[c] : 0.0f, dr = use_loss ? 0.0f : tg[c];
+                float lt;
+                d5[c] = PLAIN ? out_grad(z, t, 0.0f, true, args.loss_eps, kscale, true, 0.0f, false, lt)
+                              : out_grad(z, t, dr, use_loss, args.loss_eps, kscale, args.loss_kind == NIRC_LOSS_REL_L2,
+                                         args.fr ? args.fr[c] : 0.0f, args.sig != 0, lt);
+                if (!valid) d5[c] = 0.0f;
+                if (g == 0 && valid) loss_acc += lt;
+            }
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float v = fmaf(w5[2][mt][i], d5[2], fmaf(w5[1][mt][i], d5[1], w5[0][mt][i] * d5[0]));
+                    d[mt][i] = h[3][mt][i] > 0.0f ? v : 0.0f;
+                }
+#pragma unroll
+            for (int l = 0; l < 4; ++l) note_max(G::mH + l, mh[l]);
+            note_max(G::mD5, max(max(mag_bits(d5[0]), mag_bits(d5[1])), mag_bits(d5[2])));
+            note_max(G::mD + 3, layer_max(d));
+            __syncthreads();   // the maxima; every wave is through its forward pass
+        } else {
+            __syncthreads();
+        }
+        // the transposed weights where the hidden layers' were
+#pragma unroll
+        for (int i = 0; i < (G::kAct - G::kHT) / NT; ++i) smem[G::kHT + i * NT + threadIdx.x] = ((const u32x4 *)(pk + L.offset(SEC_T0)))[i * NT + threadIdx.x];
+#pragma unroll
+        for (int l = 0; l < 4; ++l) take_max(eH[l], G::mH + l);
+        take_max(eD5, G::mD5);
+        take_max(eD[3], G::mD + 3);
+        if (active) {
+            if (g == 0) {
+                const float f = pow2f(14 - eD5);
+                uint16_t *o = sD5 + ((wave >> 1) * 24 + (col >> 2) * 3) * 8 + 4 * (wave & 1) + (col & 3);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    uint32_t hh, ll;
+                    split2(d5[c], 0.0f, f, hh, ll);
+                    o[c * 8] = (uint16_t)hh;
+                    o[96 + c * 8] = (uint16_t)ll;
+                }
+            }
+            put_layer(sAct, h[3], pow2f(14 - eH[3]));
+        }
+        __syncthreads();
+        // ---------------- W5
+        if (wave < 4) {
+            rescale(4, eD5 + eH[3], &g5, 1);
+            add_split<1>(&g5, four,
+                         [&](int, int k, int t) {
+                             const u32x4 v = *(const u32x4 *)(sD5 + ((2 * k + t) * 12 + g * 3 + (col < 3 ? col : 0)) * 8);
+                             return col < 3 ? v : u32x4{0u, 0u, 0u, 0u};
+                         },
+                         [&](int, int k, int t) { return sAct[own_n * G::kRows + k * 128 + t * 64 + lane]; });
+        }
+        __syncthreads();
+        // ---------------- layers 4 .. 1: delta_{l+1} in d
+#pragma unroll
+        for (int l = 3; l >= 0; --l) {
+            if (l < 3) take_max(eD[l], G::mD + l);
+            if (active) {
+                put_layer(sDel, d, pow2f(14 - eD[l]));
+                if (l > 0) {
+                    put_layer(sAct, h[l > 0 ? l - 1 : 0], pow2f(14 - eH[l > 0 ? l - 1 : 0]));
+                } else {
+                    // the input features once more, turned (the transposed weights and the activations
+                    // are done with)
+                    const float *x = sX + (16 * wave + col) * kInputs;
+#pragma unroll
+                    for (int i = 0; i < 10; i += 2) {
+                        float e[8];
+                        enc_pair2(x[i], 2 * g, e[0], e[1], e[2], e[3]);
+                        enc_pair2(x[i + 1], 2 * g, e[4], e[5], e[6], e[7]);
+                        u32x4 eh, el;
+                        split8(e, kSplitFeat, eh, el);
+                        put(sE + i * G::kRows, eh, el, sel[0]);
+                        put(sE + (i + 1) * G::kRows, eh, el, sel[1]);
+                    }
+                }
+            }
+            __syncthreads();
+            if (l > 0) {
+                const int k = l > 0 ? l : 1;
+                f32x4 o[MT];
+                if (active) {
+                    const float *sec = (const float *)(smem + G::kHT) + (k - 1) * L.size(SEC_T0);
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) o[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int kq = 0; kq < KQ; ++kq) {
+                        f32x4 a[MT];
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt) a[mt] = *(const f32x4 *)(sec + ((mt * KQ + kq) * 64 + lane) * 4);
+#pragma unroll
+                        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+                            for (int mt = 0; mt < MT; ++mt) o[mt] = mfma4(a[mt][kk], d[kq][kk], o[mt]);
+                    }
+                }
+                rescale(k, eD[k] + eH[k - 1], gh[k - 1], 2);
+                add_split<2>(gh[k - 1], four,
+                             [&](int m, int kb, int t) { return sDel[(own_m + m) * G::kRows + kb * 128 + t * 64 + lane]; },
+                             [&](int, int kb, int t) { return sAct[own_n * G::kRows + kb * 128 + t * 64 + lane]; });
+                if (active) {
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) d[mt][i] = h[k - 1][mt][i] > 0.0f ? o[mt][i] : 0.0f;
+                    note_max(G::mD + k - 1, layer_max(d));
+                }
+                __syncthreads();
+            } else {
+                rescale(0, eD[0], g1, 5);
+                add_split<5>(g1, four,
+                             [&](int, int kb, int t) { return sDel[own_n * G::kRows + kb * 128 + t * 64 + lane]; },
+                             [&](int j, int kb, int t) {
+                                 return sE[((wave >> 2) + 2 * j) * G::kRows + kb * 128 + t * 64 + lane];
+                             });
+            }
+        }
+    }
+
+    // ---------------- this workgroup's partial gradient (every entry exactly once)
+    float *out = partials + (int64_t)blockIdx.x * n_params(W);
+#pragma unroll
+    for (int j = 0; j < 5; ++j) {
+        const int i = (wave >> 2) + 2 * j, input = i < 7 ? surf_input(i) : i - 4;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            out[(16 * own_n + 4 * g + r) * kFeat + 16 * input + col] = ldexpf(g1[j][r], eg[0] - 28);
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                out[w_offset(W, 1 + a) + (16 * (own_m + m) + 4 * g + r) * W + 16 * own_n + col] =
+                    ldexpf(gh[a][m][r], eg[1 + a] - 28);
+    if (wave < 4 && g == 0) {
+#pragma unroll
+        for (int r = 0; r < 3; ++r) out[w_offset(W, 4) + r * W + 16 * own_n + col] = ldexpf(g5[r], eg[4] - 28);
+    }
+#pragma unroll
+    for (int dd = 32; dd >= 1; dd >>= 1) loss_acc += __shfl_xor(loss_acc, dd, 64);
+    float *sLoss = (float *)(smem + G::kLoss);
     if (lane == 0) sLoss[wave] = loss_acc;
     __syncthreads();
     if (threadIdx.x == 0) {
         float t = 0.0f;
-        for (int w = 0; w < kTrainWaves; ++w) t += sLoss[w];
+        for (int w = 0; w < kSplitGradWaves; ++w) t += sLoss[w];
         loss_partials[blockIdx.x] = t;
     }
 }
@@ -802,6 +1228,12 @@ hipError_t launch_residual_mean(const float *y, const float *t, int64_t B, float
     return hipGetLastError();
 }
 
+int grad_blocks32(int W, int64_t batch, bool loss) {
+    if (W != 64 || !loss) return train_blocks(batch);
+    const int64_t chunks = (batch + split_round(batch) - 1) / split_round(batch);
+    return (int)(chunks < 1 ? 1 : chunks > kMaxResidentBlocks ? kMaxResidentBlocks : chunks);
+}
+
 int train_blocks(int64_t batch) {
     int64_t chunks = (batch + kChunk - 1) / kChunk;
     if (chunks > kMaxResidentBlocks) chunks = kMaxResidentBlocks;
@@ -810,7 +1242,8 @@ int train_blocks(int64_t batch) {
 
 hipError_t launch_grad_partials(int W, const Points &pts, const Queries &q, const float *packed,
                                 TrainArgs a, float *partials, float *loss_partials, int nblocks,
-                                hipStream_t s) {
+                                hipStream_t s, const TrainDraw *draw) {
+    if (draw && W != 64) return hipErrorInvalidValue;
     if (W == 128) {
         const dim3 grid(nblocks), block(kTrainWaves * 64);
         hipLaunchKernelGGL((k_grad_f32_wide<128, 0>), grid, block, 0, s, pts, q, packed, a, partials, loss_partials);
@@ -819,12 +1252,21 @@ hipError_t launch_grad_partials(int W, const Points &pts, const Queries &q, cons
         return hipGetLastError();
     }
     if (W != 64) return hipErrorInvalidValue;
-    if (a.target && a.loss_kind == NIRC_LOSS_REL_L2 && !a.fr && !a.sig)
-        hipLaunchKernelGGL((k_grad_f32<64, true>), dim3(nblocks), dim3(kTrainWaves * 64), 0, s, pts, q, packed, a,
-                           partials, loss_partials);
-    else
-        hipLaunchKernelGGL((k_grad_f32<64>), dim3(nblocks), dim3(kTrainWaves * 64), 0, s, pts, q, packed, a,
-                           partials, loss_partials);
+    // an upstream gradient may span any range: its products stay in FP32
+    if (!a.target && !draw) {
+        hipLaunchKernelGGL(k_grad_f32<64>, dim3(nblocks), dim3(kTrainWaves * 64), 0, s, pts, q, packed, a, partials,
+                           loss_partials);
+        return hipGetLastError();
+    }
+    const bool plain = a.loss_kind == NIRC_LOSS_REL_L2 && !a.fr && !a.sig;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(kSplitGradWaves * 64), 0, s, pts, q, draw ? *draw : TrainDraw{},
+                           packed, a, partials, loss_partials);
+    };
+    if (draw && plain) go(k_grad_split<true, true>);
+    else if (draw) go(k_grad_split<false, true>);
+    else if (plain) go(k_grad_split<true, false>);
+    else go(k_grad_split<false, false>);
     return hipGetLastError();
 }
 

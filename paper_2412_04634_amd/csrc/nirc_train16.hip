@@ -4,7 +4,7 @@
 // are shared.  The per-sample output gradient is not divided by the batch size inside the
 // kernel (the host folds 1/B into the loss scale), which keeps every 16-bit delta near unit
 // magnitude whatever the batch; the reduction divides the scale out again.
-#include "nirc_hash.hpp"
+#include "nirc_grad.hpp"
 
 namespace nirc {
 
@@ -21,13 +21,6 @@ constexpr int kRow16 = kChunk16 + 8;      // LDS row stride in 16-bit elements (
 template <int PREC>
 __device__ __forceinline__ uint16_t to16(float x) {
     return (uint16_t)(pack2<PREC>(x, 0.0f) & 0xFFFFu);
-}
-
-// Packs two result tiles into a chained B operand without ReLU (backward deltas).
-template <int PREC>
-__device__ __forceinline__ u32x4 chain_plain(const f32x4 &lo, const f32x4 &hi) {
-    return u32x4{pack2<PREC>(lo[0], lo[1]), pack2<PREC>(lo[2], lo[3]), pack2<PREC>(hi[0], hi[1]),
-                 pack2<PREC>(hi[2], hi[3])};
 }
 
 // 16-bit element e of an operand (8 values in 4 dwords).
@@ -56,56 +49,6 @@ __device__ inline float out_grad16(float z, float t, float dr, bool use_loss, fl
     }
     loss_term = 0.0f;
     return k * dr * dydz;
-}
-
-// One sample's inputs to a training round: its point's attributes, its direction and its
-// target (or output gradient).  Loaded ahead of use in two steps, so that neither the point
-// index nor the attributes that depend on it are waited for: the query's own values one round
-// ahead (load_query16), the point's attributes half a round ahead (load_point16).
-struct Sample16 {
-    float x[7], w[3], t[3];
-    int64_t bi;   // the query (the batch's last one for the slots past its end)
-    int64_t j;    // its point index as given (bi itself when the queries carry none)
-    bool valid;
-};
-
-__device__ __forceinline__ void load_query16(const Queries &q, const TrainArgs &args, int64_t b, int64_t B,
-                                             Sample16 &o) {
-    o.valid = b < B;
-    o.bi = o.valid ? b : B - 1;
-    o.j = q.point ? (int64_t)q.point[o.bi] : o.bi;
-    o.w[0] = q.wx[o.bi], o.w[1] = q.wy[o.bi], o.w[2] = q.wz[o.bi];
-    const float *t = args.target ? args.target : args.d_rgb;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) o.t[c] = t[3 * o.bi + c];
-}
-
-__device__ __forceinline__ void load_point16(const Points &pts, const Queries &q, Sample16 &o) {
-    // the checks of query_point on the index loaded before
-    int64_t p = o.j;
-    if (p < 0 || p >= pts.count) {
-        if (q.err) atomicOr(q.err, NIRC_FLAG_BAD_POINT_INDEX);
-        p = p < 0 ? 0 : pts.count - 1;
-    }
-    o.x[0] = pts.px[p], o.x[1] = pts.py[p], o.x[2] = pts.pz[p];
-    o.x[3] = pts.nx[p], o.x[4] = pts.ny[p], o.x[5] = pts.nz[p], o.x[6] = pts.rough[p];
-}
-
-// A training frame's sample, drawn where it is used: the lanes of a wave draw 64 samples together,
-// lane (g, c) that of slot c in the workgroup's g-th next round, and each round takes its own lanes'.
-struct Drawn16 {
-    float x[7], u1, u2, w[3], t[3];
-};
-
-__device__ __forceinline__ void draw_point16(const Points &pts, const DrawKeys &keys, int64_t b, Drawn16 &o) {
-    const int64_t p = train_point(pts.count, (uint32_t)b, keys, o.u1, o.u2);
-    o.x[0] = pts.px[p], o.x[1] = pts.py[p], o.x[2] = pts.pz[p];
-    o.x[3] = pts.nx[p], o.x[4] = pts.ny[p], o.x[5] = pts.nz[p], o.x[6] = pts.rough[p];
-}
-
-__device__ __forceinline__ void draw_target16(const nirc_lobes &lobes, const DrawKeys &keys, Drawn16 &o) {
-    cosine_dir(o.x[3], o.x[4], o.x[5], o.u1, o.u2, o.w[0], o.w[1], o.w[2]);
-    train_target(lobes, keys.mode, o.x[0], o.x[1], o.x[2], o.w[0], o.w[1], o.w[2], o.t);
 }
 
 }  // namespace
@@ -146,20 +89,6 @@ struct Grad64 {
     static constexpr int kTotal4 = kFwd4 + kE4 + 2 * kBuf4;
     __host__ __device__ static constexpr int sec(int s) { return ENC == 0 ? H16Layout{64}.offset(s) : hash_sec(s); }
 };
-
-// Selection operands (B: lane (g, c) holds K positions 8 g + j of column c): column c takes K position
-// 8 (c / 4) + c % 4 + 4 half, times `odd` where c is odd.
-template <int PREC>
-__device__ __forceinline__ u32x4 select_operand(int half, float odd, int g, int col) {
-    u32x4 v = u32x4{0u, 0u, 0u, 0u};
-    const uint32_t one = pack2<PREC>((col & 1) ? odd : 1.0f, 0.0f) & 0xFFFFu;
-    const uint32_t w = (col & 1) ? one << 16 : one;
-    if (g == (col >> 2)) {
-        const int d = 2 * half + ((col & 3) >> 1);
-        v = u32x4{d == 0 ? w : 0u, d == 1 ? w : 0u, d == 2 ? w : 0u, d == 3 ? w : 0u};
-    }
-    return v;
-}
 
 // The chunks (64 samples) of partial slab `blk` of `nblk`: blk, blk + nblk, ..., added in turn.  Up to
 // 256 chunks have a slab of one chunk each; beyond 128 a workgroup takes the two that the reduction
@@ -252,28 +181,28 @@ __device__ __forceinline__ void grad64_block(const Points &pts, const Queries &q
         const int64_t b = k < sc.count ? sc.chunk(k) * kChunk16 + s : B;
         return b < B ? b : B;
     };
-    Sample16 next;
-    Drawn16 drawn;
+    TrainSample next;
+    DrawnSample drawn;
     {   // the forward sections, all their loads in flight together, the first samples' beside them
         constexpr int N = (G::kFwd4 + kWaves64 * 64 - 1) / (kWaves64 * 64);
         const u32x4 *src = (const u32x4 *)packed;
         u32x4 t[N];
-        if (ENC == 0 && !DRAW) load_query16(q, args, sample_of(0), B, next);
+        if (ENC == 0 && !DRAW) load_query(q, args, sample_of(0), B, next);
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const int k = i * kWaves64 * 64 + (int)threadIdx.x;
             t[i] = src[k < G::kFwd4 ? k : 0];
         }
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (ENC == 0 && DRAW) draw_point16(pts, keys, min(sample_of(g), B - 1), drawn);
-        if constexpr (ENC == 0 && !DRAW) load_point16(pts, q, next);
+        if constexpr (ENC == 0 && DRAW) draw_point(pts, keys, min(sample_of(g), B - 1), drawn);
+        if constexpr (ENC == 0 && !DRAW) load_point(pts, q, next);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const int k = i * kWaves64 * 64 + (int)threadIdx.x;
             if (k < G::kFwd4) sF[k] = t[i];
         }
-        if (ENC == 0 && DRAW) draw_target16(*lobes, keys, drawn);
+        if (ENC == 0 && DRAW) draw_target(*lobes, keys, drawn);
     }
     // this wave's tiles: W2..W4 column tile wave % 4, row tiles 2 (wave / 4) and the next; W5 column
     // tile wave (waves 0..3); W1 row tile wave % 4, input tiles wave / 4 + 2 j
@@ -311,11 +240,11 @@ __device__ __forceinline__ void grad64_block(const Points &pts, const Queries &q
         constexpr bool kOwnRows = ENC == 0 && PREC == NIRC_FP16;
         if (kOwnRows && round > 0) __syncthreads();   // every wave is done with the previous round's input rows
         if constexpr (ENC == 0) {
-            Sample16 cur;
+            TrainSample cur;
             if constexpr (DRAW) {
                 if (round > 0 && (round & 3) == 0) {
-                    draw_point16(pts, keys, min(sample_of(round + g), B - 1), drawn);
-                    draw_target16(*lobes, keys, drawn);
+                    draw_point(pts, keys, min(sample_of(round + g), B - 1), drawn);
+                    draw_target(*lobes, keys, drawn);
                 }
                 const int src = 16 * (round & 3) + col;
 #pragma unroll
@@ -327,7 +256,7 @@ __device__ __forceinline__ void grad64_block(const Points &pts, const Queries &q
                 }
             } else {
                 cur = next;
-                if (more) load_query16(q, args, sample_of(round + 1), B, next);
+                if (more) load_query(q, args, sample_of(round + 1), B, next);
             }
             // scheduling fences between the steps of a round keep their loads and LDS traffic apart
             __builtin_amdgcn_sched_barrier(0);
@@ -404,7 +333,7 @@ __device__ __forceinline__ void grad64_block(const Points &pts, const Queries &q
             z5 = mfma16<PREC>(*(const u32x4 *)(fw + G::sec(SEC_O) + (kb * 64 + lane) * 8), hb[3][kb], z5);
         if constexpr (ENC == 0 && !DRAW) {
             __builtin_amdgcn_sched_barrier(0);
-            if (more) load_point16(pts, q, next);
+            if (more) load_point(pts, q, next);
         }
 
         // output delta (channels 0..2 in lane group 0)
