@@ -253,9 +253,14 @@ __device__ __forceinline__ void direction_operands(float dx, float dy, float dz,
 
 // Layer 1 (direction part, accumulating onto h) + ReLU, then layers 2..4, for T tiles; leaves
 // the hidden activations of layer 4 as chained B operands hb[tt][kb].  Each layer's weight
-// fragments are fetched from LDS while the previous layer's MFMAs drain and its epilogue runs
-// (software prefetch), so LDS latency does not sit between the layers.  `next` receives the
-// output layer's fragments (4 shifted copies x KB) for output16_packed.
+// fragments are fetched from LDS a layer ahead, so LDS latency does not sit between the layers.
+// `aout` receives the output layer's fragments (4 shifted copies x KB) for output16_packed.
+// A layer runs tile by tile, and a tile's ReLU and packing (16 vector instructions) are scheduled two by
+// two between the next tile's MFMAs: two 4-cycle instructions are free in the shadow of a 16-cycle MFMA,
+// while a third is not, and a run of them from the SIMD's other wave mostly waits (measured on one CU:
+// 37.7 cycles per pair of MFMAs alone, 41.5 with 2 instructions each, 56.6 with 3).  BF16, 1080p,
+// N = 16: 1182 us with a layer's MFMAs in one run and the packing after it, 1105 so (timed one by one,
+// 1170: 1201 without the scheduling groups, 1239 and 1228 with one and three instructions per MFMA).
 // The direction-layer fragments (`dfrag`, [kb][mt], from load_dir_fragments) stay in registers
 // across passes.
 // DKB: K-blocks of the direction section (2 for the frequency input, 1 for spherical harmonics).
@@ -275,37 +280,14 @@ __device__ __forceinline__ void mlp16(f32x4 (&h)[T][W / 16], u32x4 (&hb)[T][W / 
                                       u32x4 (&aout)[4 * (W / 32)]) {
     constexpr int MT = W / 16, KB = W / 32;
     static_assert(KB == 2, "fragment buffer sized for KB = 2");
-    u32x4 a[MT * 2];   // fragments of the hidden layer being computed: [kb][mt]
-#pragma unroll
-    for (int layer = 0; layer < 4; ++layer) {
-        __builtin_amdgcn_sched_barrier(0);
-        const u32x4(&bin)[T][2] = layer == 0 ? bd : hb;
-        const u32x4(&af)[MT * 2] = layer == 0 ? dfrag : a;
-        if (layer > 0) {
-#pragma unroll
-            for (int tt = 0; tt < T; ++tt)
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) h[tt][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-        // the wave's MFMA run at raised issue priority: the SIMD's other wave fills the gaps
-        // with its VALU work (measured: 1.5 % shorter estimates)
-        __builtin_amdgcn_s_setprio(1);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int kb = 0; kb < (layer == 0 ? DKB : 2); ++kb)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int tt = 0; tt < T; ++tt) h[tt][mt] = mfma16<PREC>(af[kb * MT + mt], bin[tt][kb], h[tt][mt]);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_setprio(0);
-        // prefetch the next layer's fragments (hidden layer `layer`, or the output copies)
+    u32x4 a[2][MT * 2];   // fragments of the hidden layer being computed and of the next: [kb][mt]
+    auto fetch = [&](int layer) {   // hidden layer `layer`'s fragments, or the output copies
         if (layer < 3) {
             const uint16_t *sec = sH + layer * (MT * KB * 512);
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) a[kb * MT + mt] = *(const u32x4 *)(sec + ((mt * KB + kb) * 64 + lane) * 8);
+                for (int mt = 0; mt < MT; ++mt) a[layer & 1][kb * MT + mt] = *(const u32x4 *)(sec + ((mt * KB + kb) * 64 + lane) * 8);
         } else {
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)
@@ -313,11 +295,37 @@ __device__ __forceinline__ void mlp16(f32x4 (&h)[T][W / 16], u32x4 (&hb)[T][W / 
                 for (int t4 = 0; t4 < 4; ++t4)
                     aout[kb * 4 + t4] = *(const u32x4 *)(sOS + ((t4 * KB + kb) * 64 + lane) * 8);
         }
+    };
+    fetch(0);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-        for (int tt = 0; tt < T; ++tt)
+    for (int layer = 0; layer < 4; ++layer) {
+        if (layer > 0) fetch(layer);
+        const u32x4(&af)[MT * 2] = layer == 0 ? dfrag : a[(layer - 1) & 1];
+#pragma unroll
+        for (int tt = 0; tt < T; ++tt) {
+            u32x4 bin[2];
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) bin[kb] = layer == 0 ? bd[tt][kb] : hb[tt][kb];
+            if (layer > 0)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) h[tt][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kb = 0; kb < (layer == 0 ? DKB : 2); ++kb)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) h[tt][mt] = mfma16<PREC>(af[kb * MT + mt], bin[kb], h[tt][mt]);
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) hb[tt][kb] = chain_operand<PREC>(h[tt][2 * kb], h[tt][2 * kb + 1]);
+        }
     }
+#pragma unroll
+    for (int i = 0; i < T * (MT * DKB + 3 * MT * KB); ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // an MFMA, then
+        __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);   // two vector instructions in its shadow
+    }
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // The same chain for widths above 64, whose weights stay in global memory: fragments are loaded
@@ -416,10 +424,12 @@ __device__ __forceinline__ void mlp16_hl(f32x4 (&h)[T][W / 16], u32x4 (&hb)[T][W
             for (int mt = 0; mt < MT; ++mt)
                 a[(i + 1) & 1][mt] = *(const u32x4 *)(sH + l1 * SEC + ((mt * KB + kb1) * 64 + lane) * 8);
         }
+        // tile by tile, so that a tile's packing can start before the others' MFMAs end (0.9 % shorter
+        // estimates than row by row at 720p, N = 8)
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+        for (int tt = 0; tt < T; ++tt)
 #pragma unroll
-            for (int tt = 0; tt < T; ++tt) h[tt][mt] = mfma16<PREC>(a[i & 1][mt], hb[tt][kb], h[tt][mt]);
+            for (int mt = 0; mt < MT; ++mt) h[tt][mt] = mfma16<PREC>(a[i & 1][mt], hb[tt][kb], h[tt][mt]);
         if (kb == KB - 1) {
 #pragma unroll
             for (int tt = 0; tt < T; ++tt)

@@ -126,8 +126,8 @@ __device__ __forceinline__ void tlmc_sums(const f32x4 &z, int T0, int s0, int n_
             // two points (4 <= N + 1), so it leaves one sum per point in the slab; then one lane per
             // (point, channel) adds the quads of its point: at most one that it enters in the middle
             // and the ones that start in it.  Bound by LDS latency: independent reads, one update
-            // per point and pass (FP16, 230,399 points, N = 5: 86 us; 110 us with one lane per channel
-            // adding query by query onto the slab, a dependent read and write each)
+            // per point and pass (FP16, 230,399 points, N = 5: 110 us with one lane per channel adding
+            // query by query onto the slab, a dependent read and write each; 86 so)
             const int nq = 4 * min(T, n_cache - T0);   // cache quads of this pass (may be <= 0)
             const int base = 16 * T0;                  // its first query
             {
