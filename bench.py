@@ -25,10 +25,25 @@ METRIC = "NIRC queries/s + ms/frame at 1080p N=16; BF16 vs FP32 at equal MRSE"
 PEAK_FP32_MFMA = 157.3e12      # MI355X dense FP32 matrix peak, FLOP/s
 PEAK_BF16_MFMA = 2.5e15        # MI355X dense BF16/FP16 matrix peak, FLOP/s
 PEAK_HBM = 8.0e12              # bytes/s
-# HBM bytes per launch of k_tlmc_f32 in the frame configuration (1080p, N = 16, F_tl + F_c + F_r
+
+
+def estimate_peak(prec: int, W: int) -> float:
+    """Matrix peak of the estimator's products, FLOP/s: FP32 models of width 64 form each product as
+    three FP16 ones with FP32 accumulation (two-term operands), wider ones on the FP32 units."""
+    if prec != 0:
+        return PEAK_BF16_MFMA
+    return PEAK_BF16_MFMA / 3 if W == 64 else PEAK_FP32_MFMA
+
+
+def measured_peak(probe: dict, name: str, W: int) -> float:
+    """The same from the probe's rates, TFLOP/s."""
+    return probe["fp16"]["tflops"] / 3 if name == "fp32" and W == 64 else probe[name]["tflops"]
+
+
+# HBM bytes per launch of k_tlmc_split in the frame configuration (1080p, N = 16, F_tl + F_c + F_r
 # written), from FETCH_SIZE x 2.0 + WRITE_SIZE (factors from a plain 512 MiB copy); recorded in
 # profiles/k_tlmc_hbm_counters_1080p_n16.md and to be measured again whenever the kernel changes.
-TRAFFIC_K_TLMC_F32 = 134192896
+TRAFFIC_K_TLMC_SPLIT = 134192896
 
 
 def algorithmic_flops_estimate(P: int, N: int, W: int) -> float:
@@ -186,7 +201,7 @@ def precision_compare(nirc, model32, dp, lobes_for, table, fs, P, N, W, seed, fr
         t = ev[0].elapsed_time(ev[1]) * 1e-3 / reps
         mrse = float(nirc.tlmc_frame_stats(dp, lob, table, tl, fs=fs)[4].item())
         flops = algorithmic_flops_estimate(P, N, W)
-        peak = PEAK_FP32_MFMA if prec == 0 else PEAK_BF16_MFMA
+        peak = estimate_peak(prec, W)
         mt = nirc.Model(w, cfg=nirc.make_config(precision=prec), max_batch=B)
         nirc.nirc_train_frame(mt, dp, lob, B, S, seed, frame)
         torch.cuda.synchronize()
@@ -245,7 +260,7 @@ def precision_form(nirc, w64, dp, lob_packed, table, fs, P, seed, frame, reps=3)
                 if ref is None:
                     ref = tl.clone()
                 flops = algorithmic_flops_estimate(P, N, W)
-                peak = PEAK_FP32_MFMA if prec == 0 else PEAK_BF16_MFMA
+                peak = estimate_peak(prec, W)
                 rows.append({"width": W, "n_cache": N, "precision": name, "ms_estimate": t * 1e3,
                              "queries_per_s": P * (N + 1) / t, "mfma_frac": flops / t / peak, "mrse": mrse,
                              "rel_l2_vs_fp32": float((tl - ref).norm() / ref.norm())})
@@ -900,9 +915,9 @@ def main():
                                f"MLP 4x{W} ReLU, {S} Adam steps of {B} samples per frame",
                    "points": P, "n_cache": N, "width": W, "train_batch": B, "train_steps_per_frame": S,
                    "precision": "fp32"},
-        "roofline": {"bound": "mfma", "kernel": "k_tlmc_f32", "achieved": achieved / 1e12,
-                     "peak": PEAK_FP32_MFMA / 1e12, "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_MFMA,
-                     "traffic": TRAFFIC_K_TLMC_F32 if cfgw is wl.WORKLOADS["1080p_n16"] else None,
+        "roofline": {"bound": "mfma", "kernel": "k_tlmc_split", "achieved": achieved / 1e12,
+                     "peak": estimate_peak(0, W) / 1e12, "unit": "TFLOP/s", "frac": achieved / estimate_peak(0, W),
+                     "traffic": TRAFFIC_K_TLMC_SPLIT if cfgw is wl.WORKLOADS["1080p_n16"] else None,
                      "traffic_unit": "bytes per launch", "flops_per_launch": flops,
                      "avg_launch_ms": t_est_avg * 1e3},
         "estimate_queries_per_s": queries / t_est_avg,
@@ -919,8 +934,8 @@ def main():
     }
     probe = mfma_probe(nirc)
     result["mfma_probe"] = probe
-    result["roofline"]["peak_measured"] = probe["fp32"]["tflops"]
-    result["roofline"]["frac_measured"] = achieved / 1e12 / probe["fp32"]["tflops"]
+    result["roofline"]["peak_measured"] = measured_peak(probe, "fp32", W)
+    result["roofline"]["frac_measured"] = achieved / 1e12 / measured_peak(probe, "fp32", W)
     if result["roofline"]["traffic"] is not None:   # the HBM side of the same launch (far from its bound)
         result["roofline"]["hbm_gbps"] = result["roofline"]["traffic"] / t_est_avg / 1e9
         result["roofline"]["hbm_frac"] = result["roofline"]["traffic"] / t_est_avg / PEAK_HBM
@@ -928,8 +943,8 @@ def main():
         result["precision_compare"] = precision_compare(nirc, model, dp, lobes_for, table, fs, P, N, W, seed,
                                                         args.warmup + args.steps, args.steps, B, S)
         for name, v in result["precision_compare"].items():
-            v["roofline"]["peak_measured"] = probe[name]["tflops"]
-            v["roofline"]["frac_measured"] = v["roofline"]["achieved"] / probe[name]["tflops"]
+            v["roofline"]["peak_measured"] = measured_peak(probe, name, W)
+            v["roofline"]["frac_measured"] = v["roofline"]["achieved"] / measured_peak(probe, name, W)
         result["biased_bth"] = biased_compare(nirc, model, dp, lobes_for, table, fs, P, N, seed,
                                               args.warmup + args.steps, min(args.steps, 20))
         result["precision_trained"] = precision_trained(nirc, w0, dp, lobes_for, table, fs, P, N, seed, 100, B, S)

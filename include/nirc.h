@@ -151,8 +151,8 @@ size_t nirc_state_bytes(const nirc_config *cfg /* host */);
 
 /* Bytes of workspace needed by training calls on batches of up to max_batch queries
  * (per-workgroup gradient partials, reduced gradient, loss, and the sample buffers of
- * nirc_train_frame, which makes the samples of up to 4 steps in one launch).  Inference needs
- * none. */
+ * nirc_train_frame for the models whose samples are not drawn in the gradient kernel: width 128
+ * and the residual-variance loss).  Inference needs none. */
 size_t nirc_workspace_bytes(const nirc_config *cfg /* host */, int64_t max_batch);
 
 /* Create a model over caller-owned device buffers.  `state` must hold nirc_state_bytes and be
@@ -364,7 +364,8 @@ nirc_status tlmc_train_batch(nirc_points points, const nirc_lobes *field /* host
  *   loss = (1/(3B)) sum_{b,c} (y - t)^2 / (sg(y)^2 + loss_eps)
  * w.r.t. the weights, written to grad [n_params] (canonical FP32); loss (device float, may be
  * NULL) receives the loss.  Needs the workspace.  Deterministic (fixed reduction order).
- * FP32 models run FP32 MFMA; BF16 / FP16 models run the forward and backward with 16-bit
+ * FP32 models run FP32 MFMA (width 64: the weight gradients' sums over the samples on two-term FP16
+ * operands with FP32 accumulation, errors at FP32's own level); BF16 / FP16 models run the forward and backward with 16-bit
  * operands and FP32 accumulation, with the output gradient scaled by loss_scale * B before the
  * backward and the gradient unscaled after the reduction.  Width 128 sweeps the batch several
  * times (each sweep owns a disjoint part of the gradient). */

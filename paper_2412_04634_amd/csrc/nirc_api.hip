@@ -381,11 +381,11 @@ nirc_status tlmc_reference_occluded(nirc_points points, const nirc_lobes *field,
     return hip_status(launch_reference_occluded(to_points(points), *field, q, F, (hipStream_t)stream));
 }
 
-// Gradient partials + reduction into `grad`/`loss`; the step's `bad` flag is raised on a
-// non-finite value.  draw: the kernel draws its queries.count samples (width 64).
+// Gradient partials + reduction into `grad`/`loss`; `bad` (a step's; NULL for a standalone gradient,
+// which starts none and so raises and clears nothing) is raised on a non-finite value.  draw: the kernel draws its queries.count samples (width 64).
 static nirc_status grad_into(nirc_model *model, const nirc_points &points, const nirc_queries &queries,
                              const float *target, const float *d_rgb, float *grad, float *loss, uint32_t *err,
-                             char *ws, size_t ws_bytes, hipStream_t s, const TrainDraw *draw = nullptr) {
+                             uint32_t *bad, char *ws, size_t ws_bytes, hipStream_t s, const TrainDraw *draw = nullptr) {
     nirc_status st = check_points(points);
     if (st == NIRC_OK && !draw) st = check_queries(queries, points);
     if (st != NIRC_OK) return st;
@@ -420,7 +420,7 @@ static nirc_status grad_into(nirc_model *model, const nirc_points &points, const
                                               partials, lpart, nb, s, draw);
     if (e != hipSuccess) return NIRC_ERR_HIP;
     const float loss_norm = 1.0f / (3.0f * (float)queries.count);
-    e = launch_reduce_grad(model->W, partials, lpart, nb, 1.0f / scale, loss_norm, grad, loss, model->bad, s,
+    e = launch_reduce_grad(model->W, partials, lpart, nb, 1.0f / scale, loss_norm, grad, loss, bad, s,
                            model->dyn(), (float)queries.count);
     return hip_status(e);
 }
@@ -429,19 +429,16 @@ nirc_status nirc_loss_grad(nirc_model *model, nirc_points points, nirc_queries q
                            float *grad, float *loss, void *stream) {
     if (!model || !target) return NIRC_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
-    nirc_status st = grad_into(model, points, queries, target, nullptr, grad, loss, model->flags, model->ws, model->ws_bytes, s);
-    if (st != NIRC_OK) return st;
-    // a standalone gradient does not start a step: clear the step's flag again
-    return hip_status(launch_fill_u32(model->bad, 1, 0u, s));
+    return grad_into(model, points, queries, target, nullptr, grad, loss, model->flags, nullptr, model->ws,
+                     model->ws_bytes, s);
 }
 
 nirc_status nirc_backward(nirc_model *model, nirc_points points, nirc_queries queries, const float *d_rgb,
                           float *grad, void *stream) {
     if (!model || !d_rgb) return NIRC_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
-    nirc_status st = grad_into(model, points, queries, nullptr, d_rgb, grad, nullptr, model->flags, model->ws, model->ws_bytes, s);
-    if (st != NIRC_OK) return st;
-    return hip_status(launch_fill_u32(model->bad, 1, 0u, s));
+    return grad_into(model, points, queries, nullptr, d_rgb, grad, nullptr, model->flags, nullptr, model->ws,
+                     model->ws_bytes, s);
 }
 
 nirc_status nirc_adam_step(nirc_model *model, const float *grad, void *stream) {
@@ -465,7 +462,8 @@ static nirc_status train_step_on(nirc_model *model, const nirc_points &points, c
     float *grad = (float *)(ws + wl.grad);
     float *wloss = (float *)(ws + wl.loss);
     nirc_status st =
-        grad_into(model, points, queries, target, nullptr, grad, loss ? loss : wloss, model->bad, ws, ws_bytes, s, draw);
+        grad_into(model, points, queries, target, nullptr, grad, loss ? loss : wloss, model->bad, model->bad, ws, ws_bytes,
+                  s, draw);
     if (st != NIRC_OK) return st;
     hipError_t e = launch_adam(model->W, model->master, model->m, model->v, grad, model->step, model->flags,
                                model->bad, model->cfg.lr, model->cfg.beta1, model->cfg.beta2, model->cfg.adam_eps,

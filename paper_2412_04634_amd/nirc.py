@@ -522,7 +522,7 @@ def tlmc_accumulate(values: torch.Tensor, s: torch.Tensor, s2: torch.Tensor):
 
 def nirc_train_frame(model: Model, points: Points, lobes, batch: int, steps: int, seed: int, frame: int,
                      loss: torch.Tensor | None = None):
-    """steps x (training samples + train step) in one native call; samples live in the workspace."""
+    """steps x (training samples + train step) in one native call; the samples are drawn on the GPU."""
     L = lobes if isinstance(lobes, Lobes) else lobes_struct(lobes)
     _check(lib().nirc_train_frame(model.handle, points.c(), ctypes.byref(L), batch, steps, seed, frame, _ptr(loss),
                                   _stream()), "nirc_train_frame")
