@@ -43,7 +43,7 @@ def measured_peak(probe: dict, name: str, W: int) -> float:
 # HBM bytes per launch of k_tlmc_split in the frame configuration (1080p, N = 16, F_tl + F_c + F_r
 # written), from FETCH_SIZE x 2.0 + WRITE_SIZE (factors from a plain 512 MiB copy); recorded in
 # profiles/k_tlmc_hbm_counters_1080p_n16.md and to be measured again whenever the kernel changes.
-TRAFFIC_K_TLMC_SPLIT = 134192896
+TRAFFIC_K_TLMC_SPLIT = 135595648
 
 
 def algorithmic_flops_estimate(P: int, N: int, W: int) -> float:

@@ -229,7 +229,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_infer_f32(Points pts, Queries q,
     static_assert(!lds_weights(W), "width 64 takes k_infer_split");
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
     const int64_t n_tiles = (q.count + 15) >> 4;
-    for (int64_t tile = (int64_t)blockIdx.x * WAVES + wave; tile < n_tiles; tile += (int64_t)gridDim.x * WAVES)
+    for (int64_t tile = first_unit<WAVES>(n_tiles, wave); tile < n_tiles; tile += (int64_t)gridDim.x * WAVES)
         infer_tile_f32<W>(pts, q, packed, nullptr, rgb, sig, tile, lane, g, col);
 }
 
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_infer_split(Points pts, Queries 
     __syncthreads();
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
     const int64_t Q = q.count, n_tiles = (Q + 15) >> 4;
-    const int64_t first = T * ((int64_t)blockIdx.x * WAVES + wave), stride = T * (int64_t)gridDim.x * WAVES;
+    const int64_t first = T * first_unit<WAVES>((n_tiles + T - 1) / T, wave), stride = T * (int64_t)gridDim.x * WAVES;
     if (!split) {
         for (int64_t t0 = first; t0 < n_tiles; t0 += stride)
             for (int64_t t = t0; t < min(t0 + T, n_tiles); ++t)
@@ -536,13 +536,13 @@ __global__ __launch_bounds__(WAVES * 64) void k_tlmc_split(Points pts, nirc_lobe
     const int64_t n_groups = (pts.count + 15) >> 4, stride = (int64_t)gridDim.x * WAVES;
     if (split) {
         const GroupSlab gs = group_slab(slab, 64);
-        for (int64_t grp = (int64_t)blockIdx.x * WAVES + wave; grp < n_groups; grp += stride)
+        for (int64_t grp = first_unit<WAVES>(n_groups, wave); grp < n_groups; grp += stride)
             tlmc_group_split<OCC, N16>(pts, grp << 4, n_cache, dn, key0, key1, frame, mode, rrad, out_tl, out_c, out_r,
                                        s_lobes, wsm, sc, gs, lane, g, col);
     } else {
         constexpr F32Layout L{64};
         const float *sD = (const float *)wsm, *sH = sD + L.size(SEC_D), *sO = sH + 3 * L.size(SEC_H0);
-        for (int64_t grp = (int64_t)blockIdx.x * WAVES + wave; grp < n_groups; grp += stride)
+        for (int64_t grp = first_unit<WAVES>(n_groups, wave); grp < n_groups; grp += stride)
             tlmc_group_f32<64, OCC>(pts, grp << 4, n_cache, dn, key0, key1, frame, mode, rrad, out_tl, out_c, out_r,
                                     s_lobes, packed + L.offset(SEC_S), sD, sH, sO, slab, slab + 16 * 64, lane, g, col);
     }
@@ -571,7 +571,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_tlmc_f32(Points pts, nirc_lobes 
     float *hs = (float *)smem4 + wave * SLAB;   // [16 points][W]
     float *db = hs + 16 * W;                    // directions, SoA [3][kDirSlots]
     const int64_t n_groups = (pts.count + 15) >> 4;
-    for (int64_t grp = (int64_t)blockIdx.x * WAVES + wave; grp < n_groups; grp += (int64_t)gridDim.x * WAVES)
+    for (int64_t grp = first_unit<WAVES>(n_groups, wave); grp < n_groups; grp += (int64_t)gridDim.x * WAVES)
         tlmc_group_f32<W, OCC>(pts, grp << 4, n_cache, dn, key0, key1, frame, mode, rrad, out_tl, out_c, out_r, s_lobes,
                                gS, sD, sH, sO, hs, db, lane, g, col);
 }
@@ -680,7 +680,10 @@ hipError_t launch_train_batch(const Points &pts, const nirc_lobes &lobes, int64_
 }
 
 unsigned grid_for(int64_t units_per_wave_total, int waves, int max_blocks) {
-    int64_t b = (units_per_wave_total + waves - 1) / waves;
+    // few units: a workgroup per CU as far as they go, with fewer of its waves at work (first_unit)
+    int64_t b = units_per_wave_total <= (int64_t)kMaxResidentBlocks * waves
+                    ? std::min<int64_t>(units_per_wave_total, kMaxResidentBlocks)
+                    : (units_per_wave_total + waves - 1) / waves;
     if (b > max_blocks) b = max_blocks;
     if (b < 1) b = 1;
     return (unsigned)b;
@@ -801,7 +804,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_hash_tlmc_f32(Points pts, nirc_l
     float *hs = smem + NW + wave * SLAB;
     float *db = hs + 16 * 64;
     const int64_t n_groups = (pts.count + 15) >> 4;
-    for (int64_t grp = (int64_t)blockIdx.x * WAVES + wave; grp < n_groups; grp += (int64_t)gridDim.x * WAVES)
+    for (int64_t grp = first_unit<WAVES>(n_groups, wave); grp < n_groups; grp += (int64_t)gridDim.x * WAVES)
         tlmc_group_f32<64, false, 1>(pts, grp << 4, n_cache, dn, key0, key1, frame, NIRC_OUTPUT_RADIANCE, rrad, out_tl,
                                      out_c, out_r, s_lobes, packed, sD, sH, sO, hs, db, lane, g, col, s_lv, grid.tmask,
                                      table);
@@ -826,7 +829,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_hash_infer_f32(Points pts, Queri
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
     const int64_t Q = q.count;
     const int64_t n_tiles = (Q + 15) >> 4;
-    for (int64_t tile = (int64_t)blockIdx.x * WAVES + wave; tile < n_tiles; tile += (int64_t)gridDim.x * WAVES) {
+    for (int64_t tile = first_unit<WAVES>(n_tiles, wave); tile < n_tiles; tile += (int64_t)gridDim.x * WAVES) {
         const int64_t qi = min((tile << 4) + col, Q - 1);
         const int64_t p = query_point(q, pts, qi);
         const float xs[7] = {pts.px[p], pts.py[p], pts.pz[p], pts.nx[p], pts.ny[p], pts.nz[p], pts.rough[p]};

@@ -142,7 +142,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_infer_h16(Points pts, Queries q,
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
     const int64_t Q = q.count;
     const int64_t n_tiles = (Q + 15) >> 4;
-    for (int64_t tile = (int64_t)blockIdx.x * WAVES + wave; tile < n_tiles; tile += (int64_t)gridDim.x * WAVES) {
+    for (int64_t tile = first_unit<WAVES>(n_tiles, wave); tile < n_tiles; tile += (int64_t)gridDim.x * WAVES) {
         const uint16_t *sD = kLds ? (const uint16_t *)smem4 : opaque(packed) + L.offset(SEC_D);
         const uint16_t *sH = sD + L.size(SEC_D);
         const uint16_t *sO = sH + 3 * L.size(SEC_H0);
@@ -363,7 +363,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_tlmc_h16(Points pts, nirc_lobes 
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
     const GroupSlab gs = group_slab((float *)slab4 + wave * SLAB, W);
     const int64_t n_groups = (pts.count + 15) >> 4;
-    for (int64_t grp = (int64_t)blockIdx.x * WAVES + wave; grp < n_groups; grp += (int64_t)gridDim.x * WAVES)
+    for (int64_t grp = first_unit<WAVES>(n_groups, wave); grp < n_groups; grp += (int64_t)gridDim.x * WAVES)
         tlmc_group_h16<W, PREC, (W <= 64 || WAVES <= 4) ? 4 : 2, OCC, 0, kHidLds, N16>(
             pts, grp << 4, n_cache, dn, key0, key1, frame, mode, rrad, out_tl, out_c, out_r, s_lobes, gS, sD, sH, sOS,
             gs, lane, g, col);
@@ -562,7 +562,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_hash_infer_h16(Points pts, Queri
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
     const int64_t Q = q.count;
     const int64_t n_tiles = (Q + 15) >> 4;
-    for (int64_t tile = (int64_t)blockIdx.x * WAVES + wave; tile < n_tiles; tile += (int64_t)gridDim.x * WAVES) {
+    for (int64_t tile = first_unit<WAVES>(n_tiles, wave); tile < n_tiles; tile += (int64_t)gridDim.x * WAVES) {
         const int64_t qi = min((tile << 4) + col, Q - 1);
         const int64_t p = query_point(q, pts, qi);
         const float xs[7] = {pts.px[p], pts.py[p], pts.pz[p], pts.nx[p], pts.ny[p], pts.nz[p], pts.rough[p]};
@@ -624,7 +624,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_hash_tlmc_h16(Points pts, nirc_l
     // group's last queries run through the MLP (the next index is clamped to the last point, so
     // the final group's fetch stays in bounds and is simply unused)
     float2 nxt[24];
-    int64_t grp = (int64_t)blockIdx.x * WAVES + __builtin_amdgcn_readfirstlane(wave);
+    int64_t grp = first_unit<WAVES>(n_groups, __builtin_amdgcn_readfirstlane(wave));
     {
         const int64_t pc = min((grp << 4) + col, pts.count - 1);
         hash_fetch24(s_lv, grid.tmask, table, pts.px[pc], pts.py[pc], pts.pz[pc], g, nxt);

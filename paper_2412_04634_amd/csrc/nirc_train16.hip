@@ -71,8 +71,8 @@ __device__ inline float out_grad16(float z, float t, float dr, bool use_loss, fl
 // operands, 46 for the gradient, against ~600 VALU instructions.
 // Of a 65,536-sample BF16 gradient's 26 us (two rounds per workgroup, one workgroup per CU), 5 were the
 // weights' and samples' first reads, one after the other, 10.8 and 8.8 the rounds, 2 the partials; with
-// the reads side by side and the samples drawn here, a frame of 4 steps takes 158 us, 187 with samples
-// from a kernel before (7 us per step) read back here.
+// the reads side by side and the samples drawn here, a step's kernel takes 29.4 us, 28.6 and 7 with
+// samples from a kernel before read back here.
 // (Before, four waves staged every value by a two-byte store as [neuron][sample] rows and read all
 // weights from L2: 36 us.)
 //
