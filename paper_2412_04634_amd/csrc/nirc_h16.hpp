@@ -287,7 +287,8 @@ __device__ __forceinline__ void mlp16(f32x4 (&h)[T][W / 16], u32x4 (&hb)[T][W / 
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) a[layer & 1][kb * MT + mt] = *(const u32x4 *)(sec + ((mt * KB + kb) * 64 + lane) * 8);
+                for (int mt = 0; mt < MT; ++mt)
+                    a[layer & 1][kb * MT + mt] = *(const u32x4 *)(sec + ((mt * KB + kb) * 64 + lane) * 8);
         } else {
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)

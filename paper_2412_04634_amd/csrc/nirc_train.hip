@@ -593,7 +593,8 @@ __global__ __launch_bounds__(kSplitGradWaves * 64) void k_grad_split(Points pts,
         }
         // the transposed weights where the hidden layers' were
 #pragma unroll
-        for (int i = 0; i < (G::kAct - G::kHT) / NT; ++i) smem[G::kHT + i * NT + threadIdx.x] = ((const u32x4 *)(pk + L.offset(SEC_T0)))[i * NT + threadIdx.x];
+        for (int i = 0; i < (G::kAct - G::kHT) / NT; ++i)
+            smem[G::kHT + i * NT + threadIdx.x] = ((const u32x4 *)(pk + L.offset(SEC_T0)))[i * NT + threadIdx.x];
 #pragma unroll
         for (int l = 0; l < 4; ++l) take_max(eH[l], G::mH + l);
         take_max(eD5, G::mD5);

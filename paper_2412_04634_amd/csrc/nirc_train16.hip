@@ -151,7 +151,8 @@ __device__ __forceinline__ uint32_t relu_mask2(uint32_t d, uint32_t h) {
 // floats.  Ends after a workgroup barrier, so a caller may run the next block on the same LDS.
 // PLAIN: the caller guarantees the common case (targets given, relative L2 of eq. 12, no
 // residual-variance mean, exp outputs), so the general loss arithmetic is compiled out.
-// PAIR: slab_pairs of the batch.  DRAW: the samples are drawn here (keys, lobes) instead of read from the queries and targets.
+// PAIR: slab_pairs of the batch.  DRAW: the samples are drawn here (keys, lobes) instead of read from
+// the queries and targets.
 template <int ENC, int PREC, bool PLAIN, bool DRAW, bool PAIR>
 __device__ __forceinline__ void grad64_block(const Points &pts, const Queries &q, const uint16_t *packed,
                                              const TrainArgs &args, const HashLevel *s_lv, const HashTrainBufs &bufs,
@@ -525,12 +526,14 @@ __global__ __launch_bounds__(kWaves64 * 64) void k_grad_h16_multi(const TrainDes
         const Queries q{nullptr, nullptr, nullptr, nullptr, t.batch, nullptr};
         const TrainArgs a{nullptr, nullptr, t.loss_eps, t.loss_scale * (float)t.batch, t.loss_kind, nullptr,
                           t.output == NIRC_OUTPUT_VISIBILITY, t.dyn_scale};
+        const DrawKeys keys{t.key0, t.key1, t.frame, step, t.output};
+        float *out = t.partials + (int64_t)b * n_params(64);
         if (slab_pairs(t.batch))
             grad64_block<0, PREC, false, true, true>(t.pts, q, t.packed16, a, nullptr, HashTrainBufs{}, GridAcc{}, false,
-                                         DrawKeys{t.key0, t.key1, t.frame, step, t.output}, &t.lobes, t.partials + (int64_t)b * n_params(64), t.lpart + b, b, t.nb, smem, sLoss);
+                                                     keys, &t.lobes, out, t.lpart + b, b, t.nb, smem, sLoss);
         else
             grad64_block<0, PREC, false, true, false>(t.pts, q, t.packed16, a, nullptr, HashTrainBufs{}, GridAcc{}, false,
-                                         DrawKeys{t.key0, t.key1, t.frame, step, t.output}, &t.lobes, t.partials + (int64_t)b * n_params(64), t.lpart + b, b, t.nb, smem, sLoss);
+                                                      keys, &t.lobes, out, t.lpart + b, b, t.nb, smem, sLoss);
     }
 }
 
