@@ -247,9 +247,9 @@ template <int T, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void k_infer_split(Points pts, Queries q, const float *__restrict__ packed,
                                                             float *__restrict__ rgb, int sig) {
     __shared__ u32x4 wsm[kSplitWeights];
-    __shared__ SplitNorms s_norms;
+    __shared__ SplitPrep s_prep;
     SplitScale sc;
-    const bool split = split_stage<WAVES>(packed, wsm, &s_norms, sc);
+    const bool split = split_stage<WAVES>(packed, wsm, &s_prep, sc);
     if (!split) stage_f32<WAVES>((f32x4 *)wsm, packed);
     __syncthreads();
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
@@ -525,10 +525,10 @@ __global__ __launch_bounds__(WAVES * 64) void k_tlmc_split(Points pts, nirc_lobe
     __shared__ u32x4 wsm[kSplitWeights];
     __shared__ f32x4 slab4[WAVES * kSplitSlab / 4];
     __shared__ nirc_lobes s_lobes;
-    __shared__ SplitNorms s_norms;
+    __shared__ SplitPrep s_prep;
     if (threadIdx.x == 0) s_lobes = lobes;
     SplitScale sc;
-    const bool split = split_stage<WAVES>(packed, wsm, &s_norms, sc);
+    const bool split = split_stage<WAVES>(packed, wsm, &s_prep, sc);
     if (!split) stage_f32<WAVES>((f32x4 *)wsm, packed);
     __syncthreads();
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
@@ -584,7 +584,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_tlmc_multi_split(const BatchDesc
     __shared__ u32x4 wsm[kSplitWeights];
     __shared__ f32x4 slab4[WAVES * kSplitSlab / 4];
     __shared__ BatchRequest s_req;
-    __shared__ SplitNorms s_norms;
+    __shared__ SplitPrep s_prep;
     const float *sD = (const float *)wsm, *sH = sD + L.size(SEC_D), *sO = sH + 3 * L.size(SEC_H0);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
     float *slab = (float *)slab4 + wave * kSplitSlab;
@@ -602,7 +602,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_tlmc_multi_split(const BatchDesc
             __syncthreads();   // every wave is done with the previous request's weights
             if (threadIdx.x == 0) s_req = desc->req[r];
             __syncthreads();
-            split = split_stage<WAVES>((const float *)s_req.packed, wsm, &s_norms, sc);
+            split = split_stage<WAVES>((const float *)s_req.packed, wsm, &s_prep, sc);
             if (!split) stage_f32<WAVES>((f32x4 *)wsm, (const float *)s_req.packed);
             __syncthreads();
             cur = r;

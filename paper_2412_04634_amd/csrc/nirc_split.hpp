@@ -10,14 +10,24 @@
 // estimate 8.96 -> 3.52 ms, 500,009 explicit queries 212 -> 92 us.
 // The FP16 unit's range is met by exact powers of two:
 //   - a layer's weights are scaled so that the largest is in [2^13, 2^14);
-//   - activations of layer l are scaled by 2^ea_l with B_l 2^ea_l < 2^15, where B_l bounds every
-//     activation whatever the inputs: B_0 = 1 (sines and cosines), B_l = B_{l-1} times the largest
-//     row sum of the positive weights (of all weights' magnitudes in the first layer; ReLU
-//     activations are never negative).  Nothing can overflow, and the second term's resolution,
-//     2^-24 of a scale whose typical activation is 2^2..2^9, stays below FP32 rounding.
-// The scales are found once per workgroup from the packed FP32 weights while they are staged.
-// Models the scales do not suit (a weight that is not finite, layer norms beyond 2^+-30, a nonzero
-// weight row more than 2^12 below its layer's largest weight) take the FP32 MFMA chain instead.
+//   - activations of layer l are scaled by 2^ea_l so that no unit's bound b_k reaches 2^15.  b_k holds
+//     whatever the inputs: the positive weights of the unit's row times the bounds of the layer before
+//     (ReLU activations are never negative; of the first layer all weights' magnitudes, for sines and
+//     cosines).  Nothing can overflow.
+// What the range costs is bounded as well.  A second term resolves 2^-24 of a scaled value, so that a held
+// activation errs by at most 2^-25 2^-ea_l beyond its own 2^-22, and a weight of less than 2^-2 as staged by
+// 2^-25 as staged.  e_k carries these errors from layer to layer, times the magnitudes of the weights;
+// what arrives at z is an error of the prediction, relative to it, that no input can exceed.  A model for
+// which it exceeds kSplitFloor takes the FP32 MFMA chain instead: units of a layer far apart, sums that
+// cancel, large units that are hardly ever on, layers that have grown in long training; also one with a
+// weight that is not finite.  The bound takes all roundings the same way and every unit at its worst; where it
+// is 2^-17, independent roundings come to 2^-25, less than FP32's own.  Restated in 64 bits (bound; error of the
+// predictions, plain FP32's): Glorot weights 2^-23.2, 0.6e-7, 1.0e-7; after 3,000, 30,000 and 150,000 training
+// steps at a learning rate of 1e-3 2^-23.0, 2^-21.1 and 2^-19.5, 2.0e-7, 1.2e-7 and 1.1e-7 against 3.3e-7, 2.7e-7 and
+// 2.3e-7; at 1e-2 2^-22.2, 2^-15.8 and 2^-11.4, the last two on the FP32 chain.  (Scales from products of the
+// layers' largest row sums, without the bound on the error, left models of the last kind 10 times plain
+// FP32's error, and one with a unit 2^9 larger than the others in each of two layers 3,000 times.)
+// All this is found once per workgroup, from the packed FP32 weights while they are staged.
 #pragma once
 
 #include "nirc_tlmc.hpp"
@@ -30,20 +40,24 @@ constexpr int kSplitS = 0, kSplitD = 16, kSplitH = 24, kSplitO = 48, kSplitFrags
 constexpr int kSplitWeights = kSplitFrags * 2 * 64;   // u32x4
 constexpr int kSplitSlab = TlmcLds<64>::kSlab + 32 + 48;   // floats per wave (GroupSlab without fa, fb)
 
-// Weight norms gathered by the workgroup (FP32 bits; magnitudes order like their bits).
-struct SplitNorms {
-    uint32_t wmax[5];   // largest magnitude of a layer
-    uint32_t rmin[5];   // smallest nonzero row maximum of a layer
-    uint32_t row[4];    // largest row sum
+// What the workgroup finds about the model while it stages (LDS; a wave's share by row tile).
+struct SplitPrep {
+    u32x4 wmax[5];     // largest magnitude of a layer's weights, FP32 bits (of the output layer's: [0])
+    u32x4 least[5];    // smallest nonzero one, 2 (bits - 1)
+    f32x4 bmax[4];     // largest bound of a layer's activations
+    float b[4][64];    // a unit's bound
+    float e[4][64];    // ... and its activation's error by the format's range
+    float ez;          // the outputs' error
 };
 
 struct SplitScale {
-    int ew[5];    // weights of layer l + 1 carry 2^ew[l]
     float f[4];   // layer l + 1's accumulator times f[l] is its activations' scale
     int ez;       // output accumulator times 2^ez = z
 };
 
 constexpr float kSplitFeat = 16384.0f;   // scale of the input features (2^14)
+
+constexpr float kSplitFloor = 0x1p-17f;
 
 // (a f, b f) as packed FP16 pairs h (nearest) and l (nearest of the rest): four v_fma_mix.  The
 // empty asm statements keep h one register, so that l reads the same rounding that the matrix
@@ -69,118 +83,227 @@ __device__ __forceinline__ void split8(const float *x, float f, u32x4 &h, u32x4 
     }
 }
 
-// Scales from the norms; false when the model has to take the FP32 chain.  Uniform.
-__device__ __forceinline__ bool split_scales(const SplitNorms &n, SplitScale &sc) {
-    bool ok = true;
-    float B = 1.0f;
-    int ea = 14;
+// Sum over the four lanes of a row (16 apart), and the largest of a wave's 16 rows.
+__device__ __forceinline__ float rows_sum(float x) {
+    const uint32_t v = __builtin_bit_cast(uint32_t, x);
+    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    const uint32_t a0 = a[0], a1 = a[1];
+    const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, a0) + __builtin_bit_cast(float, a1));
+    const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    const uint32_t b0 = b[0], b1 = b[1];
+    return __builtin_bit_cast(float, b0) + __builtin_bit_cast(float, b1);
+}
+__device__ __forceinline__ uint32_t row_max(uint32_t m) {   // (the same in the four lanes of a row)
 #pragma unroll
-    for (int l = 0; l < 5; ++l) {
-        const uint32_t wm = __builtin_amdgcn_readfirstlane(n.wmax[l]);
-        const uint32_t rm = __builtin_amdgcn_readfirstlane(n.rmin[l]);
-        const int e = wm ? (int)(wm >> 23) - 127 : 0;
-        ok = ok && wm < 0x7F800000u && e >= -30 && e <= 30 && (rm == ~0u || rm >= wm - (12u << 23));
-        sc.ew[l] = 13 - e;
-        if (l < 4) {
-            B *= 1.001f * __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(n.row[l]));
-            const int eb = B > 0.0f ? (int)(__builtin_bit_cast(uint32_t, B) >> 23) - 127 : 0;
-            ok = ok && eb >= -30 && eb <= 30;
-            sc.f[l] = ldexpf(1.0f, (14 - eb) - ea - sc.ew[l]);
-            ea = 14 - eb;
-        }
+    for (int st = 0; st < 4; ++st) {
+        const int v = (int)m;
+        const int o = st == 0   ? __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false)     // lanes 1 apart
+                      : st == 1 ? __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false)     // 2 apart
+                      : st == 2 ? __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, false)    // mirrored in 8
+                                : __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, false);   // mirrored in 16
+        m = max(m, (uint32_t)o);
     }
-    sc.ez = -(ea + sc.ew[4]);
-    return ok;
+    return m;
+}
+__device__ __forceinline__ float row_max(float x) {   // x >= 0
+    return __builtin_bit_cast(float, row_max(__builtin_bit_cast(uint32_t, x)));
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t m) {
+    m = row_max(m);
+    const auto a = __builtin_amdgcn_permlane16_swap(m, m, false, false);
+    m = max((uint32_t)a[0], (uint32_t)a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+    return max((uint32_t)b[0], (uint32_t)b[1]);
+}
+
+// The waves' largest, uniform.
+__device__ __forceinline__ uint32_t largest(const u32x4 &v) {
+    return __builtin_amdgcn_readfirstlane(max(max(v[0], v[1]), max(v[2], v[3])));
+}
+__device__ __forceinline__ float largest(const f32x4 &v) {   // (none negative)
+    return __builtin_bit_cast(float, largest(__builtin_bit_cast(u32x4, v)));
 }
 
 // Stages the split weights of a packed FP32 model (F32Layout{64}) into dst and returns true, or
-// returns false (dst unwritten) when the model needs the FP32 chain.  Called by the whole
-// workgroup; barriers inside, none at the end.
+// returns false when the model needs the FP32 chain (dst is then to be written over).  Called by the whole
+// workgroup; ends with a barrier.
+// Bounds come layer by layer, so waves 0..3 (a row tile each; lane: row lane % 16, a quarter of its columns)
+// go through the layers while waves 4..7 split the weights; every wave has all its reads in flight at once.
 template <int WAVES>
-__device__ __forceinline__ bool split_stage(const float *packed, u32x4 *dst, SplitNorms *norms, SplitScale &sc) {
+__device__ __forceinline__ bool split_stage(const float *packed, u32x4 *dst, SplitPrep *prep, SplitScale &sc) {
+    static_assert(WAVES == 8, "four waves for the bounds, four for the terms");
     constexpr F32Layout L{64};
     constexpr int oS = L.offset(SEC_S), oD = L.offset(SEC_D), oH = L.offset(SEC_H0), oO = L.offset(SEC_O);
     constexpr int szH = L.size(SEC_H0);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (threadIdx.x < 5) {
-        norms->wmax[threadIdx.x] = 0u;
-        norms->rmin[threadIdx.x] = ~0u;
-        if (threadIdx.x < 4) norms->row[threadIdx.x] = 0u;
-    }
-    __syncthreads();
-    // a wave takes whole row tiles (lane: row lane % 16, a quarter of its columns)
-    for (int c = wave; c < 17; c += WAVES) {
-        const int layer = c < 4 ? 0 : c < 16 ? 1 + ((c - 4) >> 2) : 4, mt = c < 16 ? c & 3 : 0;
-        uint32_t mx = 0u;
-        float row = 0.0f;
-        auto take = [&](int o, bool first) {
-            const f32x4 a = *(const f32x4 *)(packed + o + 4 * lane);
+    const int g = lane >> 4, mt = wave & 3, row = 16 * mt + (lane & 15);
+    const bool bounds = wave < 4;
+    // quads of 16 columns: the first layer's 7 + 3 (waves 4..7), the hidden layers' 4 each, the output's
+    // (waves 0 and 4)
+    f32x4 u1[10], uh[3][4], uo[4];
+    if (!bounds) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const float v = a[k];   // (a bit cast of the vector's element itself reads element 0)
-                mx = max(mx, __builtin_bit_cast(uint32_t, v) & 0x7FFFFFFFu);
-                row += first ? fabsf(v) : fmaxf(v, 0.0f);
+        for (int q = 0; q < 10; ++q)
+            u1[q] = *(const f32x4 *)(packed + (q < 7 ? oS + (mt * 7 + q) * 256 : oD + (mt * 3 + q - 7) * 256) + 4 * lane);
+    }
+#pragma unroll
+    for (int l = 0; l < 3; ++l)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) uh[l][q] = *(const f32x4 *)(packed + oH + l * szH + (mt * 4 + q) * 256 + 4 * lane);
+    if (mt == 0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) uo[q] = *(const f32x4 *)(packed + oO + q * 256 + 4 * lane);
+    }
+    float rsum[5];   // a row's sum of magnitudes
+    auto look = [&](int l, const f32x4 *u, int nq) {
+        uint32_t mx = 0u, mn = ~0u;
+        float sum = 0.0f;
+#pragma unroll
+        for (int q = 0; q < nq; ++q)
+#pragma unroll
+            for (int i = 0; i < 4; i += 2) {
+                const float x = u[q][i], y = u[q][i + 1];   // (a bit cast of a vector's element reads element 0)
+                const uint32_t a = __builtin_bit_cast(uint32_t, x), b = __builtin_bit_cast(uint32_t, y);
+                mx = max(max(mx, a & 0x7FFFFFFFu), b & 0x7FFFFFFFu);
+                mn = min(min(mn, (a - 1u) << 1), (b - 1u) << 1);   // (zeros come out largest)
+                sum += fabsf(x);
+                sum += fabsf(y);
             }
-        };
-        if (layer == 0) {
-#pragma unroll
-            for (int q = 0; q < 7; ++q) take(oS + (mt * 7 + q) * 256, true);
-#pragma unroll
-            for (int q = 0; q < 3; ++q) take(oD + (mt * 3 + q) * 256, true);
-        } else {
-            const int base = layer < 4 ? oH + (layer - 1) * szH : oO;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) take(base + (mt * 4 + q) * 256, false);
-        }
-#pragma unroll
-        for (int d = 16; d <= 32; d <<= 1) {
-            mx = max(mx, (uint32_t)__shfl_xor((int)mx, d));
-            row += __shfl_xor(row, d);
-        }
-        uint32_t mn = mx ? mx : ~0u;
-#pragma unroll
-        for (int d = 1; d <= 8; d <<= 1) {
-            mx = max(mx, (uint32_t)__shfl_xor((int)mx, d));
-            mn = min(mn, (uint32_t)__shfl_xor((int)mn, d));
-            row = fmaxf(row, __shfl_xor(row, d));
-        }
+        rsum[l] = rows_sum(sum);
+        mx = wave_max(mx);
+        mn = ~wave_max(~mn);
         if (lane == 0) {
-            atomicMax(&norms->wmax[layer], mx);
-            atomicMin(&norms->rmin[layer], mn);
-            if (layer < 4) atomicMax(&norms->row[layer], __builtin_bit_cast(uint32_t, row));
+            ((uint32_t *)&prep->wmax[l])[mt] = mx;
+            ((uint32_t *)&prep->least[l])[mt] = mn;
         }
+    };
+    if (bounds) {
+#pragma unroll
+        for (int l = 1; l < 4; ++l) look(l, uh[l - 1], 4);
+        if (mt == 0) look(4, uo, 4);
+    } else {
+        look(0, u1, 10);
+        const float n = row_max(rsum[0]);
+        if (g == 0) {
+            prep->b[0][row] = rsum[0];
+            prep->e[0][row] = rsum[0] * (0x1p-25f / kSplitFeat);
+        }
+        if (lane == 0) ((float *)&prep->bmax[0])[mt] = n;
     }
     __syncthreads();
-    if (!split_scales(*norms, sc)) return false;
-    for (int i = wave; i < kSplitFrags; i += WAVES) {
-        int o, layer;
-        bool pair = true;   // the K-block's second quad exists (else zero padding)
-        if (i < kSplitD) {
-            o = oS + ((i >> 2) * 7 + 2 * (i & 3)) * 256;
-            pair = (i & 3) < 3;
-            layer = 0;
-        } else if (i < kSplitH) {
-            o = oD + (((i - kSplitD) >> 1) * 3 + 2 * (i & 1)) * 256;
-            pair = (i & 1) == 0;
-            layer = 0;
-        } else if (i < kSplitO) {
-            const int h = i - kSplitH;
-            o = oH + (h >> 3) * szH + (((h >> 1) & 3) * 4 + 2 * (h & 1)) * 256;
-            layer = 1 + (h >> 3);
-        } else {
-            o = oO + 2 * (i - kSplitO) * 256;
-            layer = 4;
-        }
-        const f32x4 a = *(const f32x4 *)(packed + o + 4 * lane);
-        const f32x4 b = pair ? *(const f32x4 *)(packed + o + 256 + 4 * lane) : f32x4{0.f, 0.f, 0.f, 0.f};
-        const int ew = layer == 0 ? sc.ew[0] : layer == 1 ? sc.ew[1] : layer == 2 ? sc.ew[2] : layer == 3 ? sc.ew[3] : sc.ew[4];
-        const float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-        u32x4 h, l;
-        split8(x, ldexpf(1.0f, ew), h, l);
-        dst[(2 * i) * 64 + lane] = h;
-        dst[(2 * i + 1) * 64 + lane] = l;
+    bool ok = true;
+    int ew[5], ea[5];
+    float bmax[5];
+#pragma unroll
+    for (int l = 0; l < 5; ++l) {
+        const uint32_t wm = l < 4 ? largest(prep->wmax[l]) : __builtin_amdgcn_readfirstlane(prep->wmax[4][0]);
+        const int e = wm ? (int)(wm >> 23) - 127 : 0;
+        ok = ok && wm < 0x7F800000u && e >= -30 && e <= 30;
+        ew[l] = 13 - e;
     }
-    return true;
+    ea[0] = 14;
+    bmax[0] = 1.0f;
+    auto take_bmax = [&](int l) {   // activations of layer l + 1
+        bmax[l + 1] = 1.001f * largest(prep->bmax[l]);
+        const int eb = bmax[l + 1] > 0.0f ? (int)(__builtin_bit_cast(uint32_t, bmax[l + 1]) >> 23) - 127 : 0;
+        ok = ok && eb >= -30 && eb <= 30;
+        ea[l + 1] = 14 - eb;
+        sc.f[l] = ldexpf(1.0f, ea[l + 1] - ea[l] - ew[l]);
+    };
+    auto put = [&](int frag, const f32x4 &a, const f32x4 &b, float f) {
+        const float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+        u32x4 h, lo;
+        split8(x, f, h, lo);
+        dst[(2 * frag) * 64 + lane] = h;
+        dst[(2 * frag + 1) * 64 + lane] = lo;
+    };
+    // the magnitude below which layer l's weights are held by their last bits, if it has any (else 0)
+    auto small_below = [&](int l) {
+        const uint32_t mn = l < 4 ? ~largest(~prep->least[l]) : __builtin_amdgcn_readfirstlane(prep->least[4][0]);
+        const float t = ldexpf(0.25f, -ew[l]);
+        return (mn >> 1) + 1u < __builtin_bit_cast(uint32_t, t) ? t : 0.0f;
+    };
+    if (const float t = small_below(0); t > 0.0f) {   // (uniform)
+        if (!bounds) {
+            float c = 0.0f;
+#pragma unroll
+            for (int q = 0; q < 10; ++q)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) c += u1[q][i] != 0.0f && fabsf(u1[q][i]) < t ? 1.0f : 0.0f;
+            c = rows_sum(c);
+            if (g == 0) prep->e[0][row] = fmaf(c, ldexpf(0x1p-25f, -ew[0]), rsum[0] * (0x1p-25f / kSplitFeat));
+        }
+        __syncthreads();
+    }
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int l = 1; l < 5; ++l) {
+        take_bmax(l - 1);
+        if (bounds) {
+            if (l < 4 || mt == 0) {
+                const float floor = ldexpf(0x1p-25f, -ea[l]);
+                float p = 0.0f, e = 0.0f;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 bi = *(const f32x4 *)(prep->b[l - 1] + 16 * q + 4 * g);
+                    const f32x4 ei = *(const f32x4 *)(prep->e[l - 1] + 16 * q + 4 * g);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float w = l < 4 ? uh[l < 4 ? l - 1 : 0][q][i] : uo[q][i];
+                        p = fmaf(fmaxf(w, 0.0f), bi[i], p);
+                        e = fmaf(fabsf(w), ei[i], e);
+                    }
+                }
+                const float t = small_below(l);
+                if (t > 0.0f) {
+                    float c = 0.0f;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4 bi = *(const f32x4 *)(prep->b[l - 1] + 16 * q + 4 * g);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const float m = fabsf(l < 4 ? uh[l < 4 ? l - 1 : 0][q][i] : uo[q][i]);
+                            c += m > 0.0f && m < t ? bi[i] : 0.0f;
+                        }
+                    }
+                    e = fmaf(c, ldexpf(0x1p-25f, -ew[l]), e);
+                }
+                e = fmaf(floor, rsum[l], rows_sum(e));
+                if (l < 4) {
+                    p = rows_sum(p);
+                    if (g == 0) {
+                        prep->b[l < 4 ? l : 0][row] = p;
+                        prep->e[l < 4 ? l : 0][row] = e;
+                    }
+                    p = row_max(p);
+                    if (lane == 0) ((float *)&prep->bmax[l < 4 ? l : 0])[mt] = p;
+                } else {
+                    e = row_max(e);
+                    if (lane == 0) prep->ez = e;
+                }
+            }
+        } else {
+            const float f = ldexpf(1.0f, ew[l - 1]);
+            if (l == 1) {
+#pragma unroll
+                for (int kb = 0; kb < 4; ++kb) put(kSplitS + mt * 4 + kb, u1[2 * kb], kb < 3 ? u1[2 * kb + 1] : zero, f);
+                put(kSplitD + mt * 2, u1[7], u1[8], f);
+                put(kSplitD + mt * 2 + 1, u1[9], zero, f);
+            } else {
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+                    put(kSplitH + 8 * (l - 2) + mt * 2 + kb, uh[l > 1 ? l - 2 : 0][2 * kb], uh[l > 1 ? l - 2 : 0][2 * kb + 1], f);
+            }
+            if (l == 4 && mt == 0) {
+                const float fo = ldexpf(1.0f, ew[4]);
+                put(kSplitO, uo[0], uo[1], fo);
+                put(kSplitO + 1, uo[2], uo[3], fo);
+            }
+        }
+        __syncthreads();
+    }
+    sc.ez = -(ea[4] + ew[4]);
+    return __builtin_amdgcn_readfirstlane(ok && prep->ez <= kSplitFloor);
 }
 
 // acc[tt][mt] += K-block kb of a section (first fragment `frag`, KB K-blocks) times the operand

@@ -321,19 +321,6 @@ __device__ __forceinline__ int exp_of(const u32x4 *waves) {
     const int e = (int)(__builtin_amdgcn_readfirstlane(m) >> 23) - 127;
     return e < -100 ? -100 : e;
 }
-// Largest of a wave's values.
-__device__ __forceinline__ uint32_t wave_max(uint32_t m) {
-#define NIRC_DPP_MAX(ctrl) m = max(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, ctrl, 0xF, 0xF, false))
-    NIRC_DPP_MAX(0xB1);    // lanes 1 apart
-    NIRC_DPP_MAX(0x4E);    // 2 apart
-    NIRC_DPP_MAX(0x141);   // mirrored in 8
-    NIRC_DPP_MAX(0x140);   // mirrored in 16
-#undef NIRC_DPP_MAX
-    const auto a = __builtin_amdgcn_permlane16_swap(m, m, false, false);
-    m = max((uint32_t)a[0], (uint32_t)a[1]);
-    const auto b = __builtin_amdgcn_permlane32_swap(m, m, false, false);
-    return max((uint32_t)b[0], (uint32_t)b[1]);
-}
 __device__ __forceinline__ float pow2f(int e) { return __builtin_bit_cast(float, (uint32_t)(127 + e) << 23); }
 __device__ __forceinline__ uint32_t mag_bits(float x) { return __builtin_bit_cast(uint32_t, x) & 0x7FFFFFFFu; }
 
