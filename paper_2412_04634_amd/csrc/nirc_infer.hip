@@ -277,9 +277,22 @@ __global__ __launch_bounds__(WAVES * 64) void k_infer_split(Points pts, Queries 
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt) acc[tt][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
         split_surface<T>(acc, wsm, xs, lane, g);
-        const f32x4 z = split_mlp<T>(acc, wsm, sc, dx, dy, dz, lane, g, col);
+        // queries with an input that is not a number (16 bits a tile): the FP16 unit's NaN carries a sign that
+        // ReLU takes to 0, so the outputs get it back here
+        uint64_t nans = 0;
+#pragma unroll
+        for (int u = 0; u < T; ++u) {
+            const float sum = attr_sum(xs[u]) + dx[u] + dy[u] + dz[u];
+            nans |= (__ballot(sum != sum) & 0xFFFFu) << (16 * u);
+        }
+        f32x4 z = split_mlp<T>(acc, wsm, sc, dx, dy, dz, lane, g, col);
         // lane (g, col): channel col % 3 of queries 4 g + i of tile col / 3
         const int tt = col / 3, c = col - 3 * tt;
+        if (nans) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (tt < T && (nans >> (16 * tt + 4 * g + i) & 1u)) z[i] = __builtin_nanf("");
+        }
         if (tt < T) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -481,6 +494,8 @@ __device__ __forceinline__ void tlmc_group_split(const Points &pts, int64_t p0, 
     const int64_t P = pts.count, pc = min(p0 + col, P - 1);
     const int n_tiles = n_cache + 1;
     const float xs[1][7] = {{pts.px[pc], pts.py[pc], pts.pz[pc], pts.nx[pc], pts.ny[pc], pts.nz[pc], pts.rough[pc]}};
+    const float sum = attr_sum(xs[0]);
+    const uint32_t nans = (uint32_t)__ballot(sum != sum);
     {
         f32x4 hsum[1][4];
 #pragma unroll
@@ -510,7 +525,8 @@ __device__ __forceinline__ void tlmc_group_split(const Points &pts, int64_t p0, 
         tb = tend;
     }
     wave_sync();
-    tlmc_finish<OCC>(gs, xs[0], rdx, rdy, rdz, p0, P, pc, n_cache, mode, rrad, out_tl, out_c, out_r, lobes, g, col);
+    tlmc_finish<OCC>(gs, xs[0], rdx, rdy, rdz, p0, P, pc, n_cache, mode, rrad, out_tl, out_c, out_r, lobes, g, col,
+                     nans);
 }
 
 // Fused estimator of FP32 models of width 64: the split chain, or the FP32 chain for models the

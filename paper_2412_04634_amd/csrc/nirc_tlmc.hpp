@@ -164,13 +164,20 @@ __device__ __forceinline__ void tlmc_sums(const f32x4 &z, int T0, int s0, int n_
     }
 }
 
+// NaN if a point's attribute is.
+__device__ __forceinline__ float attr_sum(const float x[7]) {
+    return ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + x[6]);
+}
+
 // The residual sample and the store of one point group (16 points from p0; the wave's sums and
 // residual predictions are in the slab, each lane holds its column's point and residual direction).
+// nans (bit: point): all results of a point whose attributes are not numbers (the split FP32 chain's
+// predictions are numbers then: see k_infer_split).
 template <bool OCC>
 __device__ __forceinline__ void tlmc_finish(const GroupSlab &gs, const float xs[7], float rdx, float rdy, float rdz,
                                             int64_t p0, int64_t P, int64_t pc, int n_cache, int mode,
                                             const float *rrad, float *out_tl, float *out_c, float *out_r,
-                                            const nirc_lobes &lobes, int g, int col) {
+                                            const nirc_lobes &lobes, int g, int col, uint32_t nans = 0u) {
     // residual sample: the caller's radiance (uniform branch), or the field: lane group g
     // evaluates lobe g at its column's point and residual direction, and the four lobes are
     // summed across the lane groups
@@ -194,7 +201,8 @@ __device__ __forceinline__ void tlmc_finish(const GroupSlab &gs, const float xs[
         }
     }
     if (g == 0 && p0 + col < P) {
-        const float inv_n = 1.0f / (float)n_cache;
+        float inv_n = 1.0f / (float)n_cache;
+        if ((nans >> col) & 1u) inv_n = Lr[0] = Lr[1] = Lr[2] = __builtin_nanf("");
         const float *ps = gs.psum + 4 * col, *yr = gs.yres + 4 * col;
         store_estimate(p0 + col, inv_n, ps[0], ps[1], ps[2], Lr[0] - yr[0], Lr[1] - yr[1], Lr[2] - yr[2], out_tl,
                        out_c, out_r);
