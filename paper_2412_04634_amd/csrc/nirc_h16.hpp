@@ -253,7 +253,7 @@ __device__ __forceinline__ void direction_operands(float dx, float dy, float dz,
 
 // Layer 1 (direction part, accumulating onto h) + ReLU, then layers 2..4, for T tiles; leaves
 // the hidden activations of layer 4 as chained B operands hb[tt][kb].  Each layer's weight
-// fragments are fetched from LDS a layer ahead, so LDS latency does not sit between the layers.
+// fragments are fetched from LDS ahead, so LDS latency does not sit between the layers.
 // `aout` receives the output layer's fragments (4 shifted copies x KB) for output16_packed.
 // A layer runs tile by tile, and a tile's ReLU and packing (16 vector instructions) are scheduled two by
 // two between the next tile's MFMAs: two 4-cycle instructions are free in the shadow of a 16-cycle MFMA,
@@ -274,13 +274,17 @@ __device__ __forceinline__ void load_dir_fragments(u32x4 (&dfrag)[W / 8], const 
             dfrag[kb * MT + mt] = *(const u32x4 *)(sD + ((mt * DKB + kb) * 64 + lane) * 8);
 }
 
-template <int W, int PREC, int T, int DKB = 2>
+// FB: fragment buffers.  With two, a layer's fragments are read while the layer before runs; a kernel without
+// the registers for the second reads them behind the last tile's MFMAs (hash grid, N not a multiple
+// of 16: 256 registers and spills with two; 230,399 points, N = 1 and 5: 171.4 and 185.1 us, with one 168.4 and 180.7;
+// N = 16, which has the registers: 221.9 and 223.3).
+template <int W, int PREC, int T, int DKB = 2, int FB = 2>
 __device__ __forceinline__ void mlp16(f32x4 (&h)[T][W / 16], u32x4 (&hb)[T][W / 32], const u32x4 (&bd)[T][2],
                                       const u32x4 (&dfrag)[W / 8], const uint16_t *sH, const uint16_t *sOS, int lane,
                                       u32x4 (&aout)[4 * (W / 32)]) {
     constexpr int MT = W / 16, KB = W / 32;
     static_assert(KB == 2, "fragment buffer sized for KB = 2");
-    u32x4 a[2][MT * 2];   // fragments of the hidden layer being computed and of the next: [kb][mt]
+    u32x4 a[FB][MT * 2];   // fragments of the hidden layer being computed (and of the next): [kb][mt]
     auto fetch = [&](int layer) {   // hidden layer `layer`'s fragments, or the output copies
         if (layer < 3) {
             const uint16_t *sec = sH + layer * (MT * KB * 512);
@@ -288,7 +292,7 @@ __device__ __forceinline__ void mlp16(f32x4 (&h)[T][W / 16], u32x4 (&hb)[T][W / 
             for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
-                    a[layer & 1][kb * MT + mt] = *(const u32x4 *)(sec + ((mt * KB + kb) * 64 + lane) * 8);
+                    a[layer & (FB - 1)][kb * MT + mt] = *(const u32x4 *)(sec + ((mt * KB + kb) * 64 + lane) * 8);
         } else {
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)
@@ -297,13 +301,13 @@ __device__ __forceinline__ void mlp16(f32x4 (&h)[T][W / 16], u32x4 (&hb)[T][W / 
                     aout[kb * 4 + t4] = *(const u32x4 *)(sOS + ((t4 * KB + kb) * 64 + lane) * 8);
         }
     };
-    fetch(0);
+    if (FB == 2) fetch(0);
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int layer = 0; layer < 4; ++layer) {
-        if (layer > 0) fetch(layer);
-        const u32x4(&af)[MT * 2] = layer == 0 ? dfrag : a[(layer - 1) & 1];
+        if (FB == 2 && layer > 0) fetch(layer);
+        const u32x4(&af)[MT * 2] = layer == 0 ? dfrag : a[(layer - 1) & (FB - 1)];
 #pragma unroll
         for (int tt = 0; tt < T; ++tt) {
             u32x4 bin[2];
@@ -316,6 +320,7 @@ __device__ __forceinline__ void mlp16(f32x4 (&h)[T][W / 16], u32x4 (&hb)[T][W / 
             for (int kb = 0; kb < (layer == 0 ? DKB : 2); ++kb)
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) h[tt][mt] = mfma16<PREC>(af[kb * MT + mt], bin[kb], h[tt][mt]);
+            if (FB == 1 && tt == T - 1) fetch(layer);
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) hb[tt][kb] = chain_operand<PREC>(h[tt][2 * kb], h[tt][2 * kb + 1]);
         }

@@ -247,7 +247,7 @@ __device__ __forceinline__ void tlmc_tiles_h16(int T0, int s0, int n_cache, DivN
     u32x4 hb[T][KB];
     u32x4 aout[4 * KB];
     if constexpr (lds_weights(W)) {
-        mlp16<W, PREC, T, ENC == 1 ? 1 : 2>(h, hb, bd, dfrag, sH, sOS, lane, aout);
+        mlp16<W, PREC, T, ENC == 1 ? 1 : 2, ENC == 1 && !N16 ? 1 : 2>(h, hb, bd, dfrag, sH, sOS, lane, aout);
     } else {   // weights in global memory: keep their loads inside the pass
         if constexpr (HL)
             mlp16_hl<W, PREC, T>(h, hb, bd, dl2, sH, opaque(sOS), lane, aout);

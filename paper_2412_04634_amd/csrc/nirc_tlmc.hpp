@@ -100,7 +100,10 @@ __device__ __forceinline__ void tlmc_sums(const f32x4 &z, int T0, int s0, int n_
         }
         if (valid && last && g == 0 && Tt < n_cache) gs.psum[div_n((uint32_t)(16 * Tt), dn) * 4 + c] += sum;
     } else if constexpr (!N16) {
-        if (n_cache <= 8 && (16 % n_cache) == 0) {
+        // In 16 bits, where a pass is short, the path of N = 1, 2, 4, 8 is laid out first (BF16, 230,399 points: N = 2
+        // 65.1 us behind the other, 63.1 before it; N = 12 130.9 and 131.8; FP32, N = 31: 798 and 820)
+        const bool inside = n_cache <= 8 && (n_cache & (n_cache - 1)) == 0;
+        if (LIBEXP ? inside : __builtin_expect(inside, 1)) {
             // every point of a cache tile lies inside the tile: plain stores of complete sums
             if (valid && Tt < n_cache) {
                 const int pbase = (int)div_n((uint32_t)(16 * Tt + q0), dn);   // point of this lane's first query
