@@ -826,7 +826,9 @@ __global__ __launch_bounds__(WAVES * 64) void k_hash_tlmc_f32(Points pts, nirc_l
                                      table);
 }
 
-template <int WAVES>
+// FEW: one turn of the grid covers the queries (first_unit), and a wave takes one tile.  Two instances, because
+// the loop with the choice inside is scheduled worse (500,009 queries: 397 us without it, 407 with it).
+template <int WAVES, bool FEW>
 __global__ __launch_bounds__(WAVES * 64) void k_hash_infer_f32(Points pts, Queries q, const float *__restrict__ packed,
                                                                const float2 *__restrict__ table, HashGridArgs grid,
                                                                float *__restrict__ rgb) {
@@ -845,7 +847,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_hash_infer_f32(Points pts, Queri
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
     const int64_t Q = q.count;
     const int64_t n_tiles = (Q + 15) >> 4;
-    for (int64_t tile = first_unit<WAVES>(n_tiles, wave); tile < n_tiles; tile += (int64_t)gridDim.x * WAVES) {
+    for (int64_t tile = FEW ? (int64_t)blockIdx.x + (int64_t)gridDim.x * wave : (int64_t)blockIdx.x * WAVES + wave;
+         tile < n_tiles; tile += (int64_t)gridDim.x * WAVES) {
         const int64_t qi = min((tile << 4) + col, Q - 1);
         const int64_t p = query_point(q, pts, qi);
         const float xs[7] = {pts.px[p], pts.py[p], pts.pz[p], pts.nx[p], pts.ny[p], pts.nz[p], pts.rough[p]};
@@ -882,9 +885,13 @@ hipError_t launch_hash_pack32(float *packed, const float *master, hipStream_t s,
 hipError_t launch_hash_infer32(const Points &pts, const Queries &q, const float *packed, const float *table,
                                const HashGridArgs &grid, float *rgb, hipStream_t s) {
     constexpr int WAVES = 4;
-    const unsigned nb = grid_for((q.count + 15) / 16, WAVES, 4 * kMaxResidentBlocks);
-    hipLaunchKernelGGL((k_hash_infer_f32<WAVES>), dim3(nb), dim3(WAVES * 64), 0, s, pts, q, packed,
-                       (const float2 *)table, grid, rgb);
+    const int64_t tiles = (q.count + 15) / 16;
+    const unsigned nb = grid_for(tiles, WAVES, 4 * kMaxResidentBlocks);
+    const float2 *t2 = (const float2 *)table;
+    if (tiles <= (int64_t)nb * WAVES)
+        hipLaunchKernelGGL((k_hash_infer_f32<WAVES, true>), dim3(nb), dim3(WAVES * 64), 0, s, pts, q, packed, t2, grid, rgb);
+    else
+        hipLaunchKernelGGL((k_hash_infer_f32<WAVES, false>), dim3(nb), dim3(WAVES * 64), 0, s, pts, q, packed, t2, grid, rgb);
     return hipGetLastError();
 }
 
