@@ -18,8 +18,8 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 bool width_ok(int32_t w) { return w == 64 || w == 128; }
 
 // State layout (each piece 256-byte aligned): master | m | v | packed FP32 | packed 16-bit (BF16
-// and FP16 models only) | step | flags | bad | loss scale (FP32), good-step count and the Adam
-// kernel's finished-workgroup count (uint32, zero between steps).
+// and FP16 models only) | step | flags | bad | loss scale (FP32), good-step count, the Adam kernel's
+// finished-workgroup count (uint32, zero between steps) and whether the units are far apart (uint32).
 struct StateLayout {
     size_t master, m, v, packed, packed16, step, flags, bad, scale, total;
     StateLayout(int W, int prec) {
@@ -34,7 +34,7 @@ struct StateLayout {
         step = o; o += align_up(sizeof(int64_t));
         flags = o; o += align_up(sizeof(uint32_t));
         bad = o; o += align_up(sizeof(uint32_t));
-        scale = o; o += align_up(3 * sizeof(uint32_t));
+        scale = o; o += align_up(4 * sizeof(uint32_t));   // loss scale, good steps, workgroup count, wide
         total = o;
     }
 };
@@ -104,6 +104,7 @@ struct nirc_model {
     float *scale;          // the current loss scale (dynamic for FP16 models)
     uint32_t *good;        // finite steps since the scale last changed
     uint32_t *done;        // finished workgroups of the running Adam launch (zero between steps)
+    uint32_t *wide;        // FP32, width 64: the loss gradient's sums take FP32 operands (units far apart)
     char *ws;
     size_t ws_bytes;
     // FP16 models scale their loss dynamically; BF16 and FP32 keep cfg.loss_scale
@@ -178,6 +179,7 @@ nirc_status nirc_create(const nirc_config *cfg, void *state, size_t state_bytes,
     m->scale = (float *)(base + sl.scale);
     m->good = (uint32_t *)(base + sl.scale + sizeof(float));
     m->done = (uint32_t *)(base + sl.scale + sizeof(float) + sizeof(uint32_t));
+    m->wide = (uint32_t *)(base + sl.scale + sizeof(float) + 2 * sizeof(uint32_t));
     m->ws = (char *)workspace;
     m->ws_bytes = workspace ? workspace_bytes : 0;
     st = nirc_set_weights(m, init_w, stream);
@@ -200,6 +202,15 @@ nirc_status nirc_destroy(nirc_model *model) {
     return NIRC_OK;
 }
 
+// What follows from FP32 weights that came in from outside: the packed copies, and whether the units are far apart.
+static hipError_t derive_copies(nirc_model *model, hipStream_t s) {
+    hipError_t e = launch_pack(model->packed, model->master, model->W, s);
+    if (e == hipSuccess && model->packed16)
+        e = launch_pack16(model->packed16, model->master, model->W, model->cfg.precision, s);
+    if (e == hipSuccess && !model->packed16 && model->W == 64) e = launch_weight_spread(model->master, model->wide, s);
+    return e;
+}
+
 nirc_status nirc_set_weights(nirc_model *model, const float *w, void *stream) {
     if (!model || !w) return NIRC_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
@@ -210,9 +221,7 @@ nirc_status nirc_set_weights(nirc_model *model, const float *w, void *stream) {
     // the loss scale starts again from the configured one
     if (e == hipSuccess) e = launch_fill_u32((uint32_t *)model->scale, 1, __builtin_bit_cast(uint32_t, model->cfg.loss_scale), s);
     if (e == hipSuccess) e = launch_fill_u32(model->good, 2, 0u, s);   // good-step and workgroup counts
-    if (e == hipSuccess) e = launch_pack(model->packed, model->master, model->W, s);
-    if (e == hipSuccess && model->packed16)
-        e = launch_pack16(model->packed16, model->master, model->W, model->cfg.precision, s);
+    if (e == hipSuccess) e = derive_copies(model, s);
     return hip_status(e);
 }
 
@@ -236,9 +245,7 @@ nirc_status nirc_set_state(nirc_model *model, const void *blob, size_t blob_byte
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = launch_copy_f32(model->master, (const float *)blob, (int64_t)(bytes / 4), s);
     // the packed copies follow the restored FP32 weights whatever precision wrote the blob
-    if (e == hipSuccess) e = launch_pack(model->packed, model->master, model->W, s);
-    if (e == hipSuccess && model->packed16)
-        e = launch_pack16(model->packed16, model->master, model->W, model->cfg.precision, s);
+    if (e == hipSuccess) e = derive_copies(model, s);
     return hip_status(e);
 }
 
@@ -402,7 +409,7 @@ static nirc_status grad_into(nirc_model *model, const nirc_points &points, const
     // near unit magnitude in the 16-bit operands; the reduction divides it out again
     const float scale = h16 ? model->cfg.loss_scale * (float)queries.count : model->cfg.loss_scale;
     TrainArgs a{target, d_rgb, model->cfg.loss_eps, scale, model->cfg.loss, nullptr,
-                model->cfg.output == NIRC_OUTPUT_VISIBILITY, model->dyn()};
+                model->cfg.output == NIRC_OUTPUT_VISIBILITY, model->dyn(), model->wide};
     if (var) {   // the residual-variance loss needs F_r = mean(t - y) of this batch first
         float *pred = (float *)(ws + wl.pred);
         float *fr = (float *)(ws + wl.fr);

@@ -522,6 +522,7 @@ struct TrainArgs {
     int32_t sig;           // sigmoid outputs (the visibility cache) instead of exp
     const float *dyn_scale;   // FP16 models: the current dynamic loss scale (device), which
                               // replaces loss_scale as dyn_scale * B; NULL: loss_scale as given
+    const uint32_t *wide = nullptr;   // FP32 models of width 64, loss gradients: k_weight_spread's finding
 };
 
 // Dynamic loss scaling of FP16 models: a step skipped for a non-finite gradient halves the scale,
@@ -574,6 +575,7 @@ __device__ inline void commit_step(int64_t *step, uint32_t *flags, uint32_t *bad
 // summed in a fixed order; part holds kFrBlocks x 3 floats.
 constexpr int kFrBlocks = 256;
 hipError_t launch_residual_mean(const float *y, const float *t, int64_t B, float *part, float *fr, hipStream_t s);
+hipError_t launch_weight_spread(const float *w, uint32_t *wide, hipStream_t s);
 int train_blocks(int64_t batch);     // partial slabs an FP32 model's workspace holds for a batch
 int grad_blocks32(int W, int64_t batch, bool loss);   // ... that it launches (slabs written); loss: targets given
 int train_blocks16(int64_t batch);   // partial slabs a 16-bit model's workspace holds for a batch

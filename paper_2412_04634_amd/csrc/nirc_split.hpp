@@ -83,7 +83,7 @@ __device__ __forceinline__ void split8(const float *x, float f, u32x4 &h, u32x4 
     }
 }
 
-// Sum over the four lanes of a row (16 apart), and the largest of a wave's 16 rows.
+// Sum and maximum over the four lanes of a row (16 apart), and the largest of a wave's 16 rows.
 __device__ __forceinline__ float rows_sum(float x) {
     const uint32_t v = __builtin_bit_cast(uint32_t, x);
     const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
@@ -92,6 +92,12 @@ __device__ __forceinline__ float rows_sum(float x) {
     const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
     const uint32_t b0 = b[0], b1 = b[1];
     return __builtin_bit_cast(float, b0) + __builtin_bit_cast(float, b1);
+}
+__device__ __forceinline__ uint32_t rows_max(uint32_t m) {
+    const auto a = __builtin_amdgcn_permlane16_swap(m, m, false, false);
+    m = max((uint32_t)a[0], (uint32_t)a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+    return max((uint32_t)b[0], (uint32_t)b[1]);
 }
 __device__ __forceinline__ uint32_t row_max(uint32_t m) {   // (the same in the four lanes of a row)
 #pragma unroll
@@ -108,13 +114,7 @@ __device__ __forceinline__ uint32_t row_max(uint32_t m) {   // (the same in the 
 __device__ __forceinline__ float row_max(float x) {   // x >= 0
     return __builtin_bit_cast(float, row_max(__builtin_bit_cast(uint32_t, x)));
 }
-__device__ __forceinline__ uint32_t wave_max(uint32_t m) {
-    m = row_max(m);
-    const auto a = __builtin_amdgcn_permlane16_swap(m, m, false, false);
-    m = max((uint32_t)a[0], (uint32_t)a[1]);
-    const auto b = __builtin_amdgcn_permlane32_swap(m, m, false, false);
-    return max((uint32_t)b[0], (uint32_t)b[1]);
-}
+__device__ __forceinline__ uint32_t wave_max(uint32_t m) { return rows_max(row_max(m)); }
 
 // The waves' largest, uniform.
 __device__ __forceinline__ uint32_t largest(const u32x4 &v) {

@@ -283,18 +283,25 @@ __global__ __launch_bounds__(kTrainWaves * 64) void k_grad_f32(Points pts, Queri
 }
 
 // ------------------------------------------------------------------------------------------
-// Loss gradients of FP32 models.  The forward pass and the deltas keep the FP32 MFMA chain (operation
-// for operation: a ReLU decision that rounding moved would change a sample's gradient by more than
-// rounding does, and an FP16 MFMA cuts the smaller products of a group at 2^-24 of the largest, which
-// every sample's deltas would share).  The weight gradients' sums over the samples take two-term FP16
-// operands (x s = h + l; h h + h l + l h in three 16x16x32 MFMAs of 16 cycles instead of eight FP32 ones
-// of 32): their errors are the samples' own and average out.
+// Loss gradients of FP32 models.  The forward pass and the deltas stay FP32: a ReLU decision that rounding
+// moved would change a sample's gradient by more than rounding does, and an FP16 MFMA cuts the smaller
+// products of a group at 2^-24 of the largest, which every sample's deltas would share.  (Layers 1..4 and
+// the deltas below the last hidden layer are k_grad_f32's FP32 MFMAs in its order; the output layer and the
+// last hidden layer's delta are vector multiply-adds in another.)  The weight gradients' sums over the
+// samples take two-term FP16 operands (x s = h + l; h h + h l + l h in three 16x16x32 MFMAs of 16 cycles
+// instead of eight FP32 ones of 32): their errors are the samples' own and average out.
 //
 // Scales: every operand set is scaled by an exact power of two that puts the largest magnitude the
 // workgroup has met in it (a layer's activations, a layer's deltas) in [2^14, 2^15), so that a value's
 // error is at most 2^-39 of that largest, and 22 bits are kept of a value within 2^-16 of it.  The maxima
 // only grow; when one does, the sums held in registers are rescaled (exactly).  An upstream gradient of
 // the caller's may span any range and stays with k_grad_f32.
+//
+// One scale for a layer's units suits models whose units are of like size.  Where the weights into the
+// units of a layer, or out of them, differ by more than 2^kSpreadMax from unit to unit (largest magnitudes;
+// initialised models 2^2, trained for 150,000 steps up to 2^9), or by more than 2^kSpreadSum over all layers
+// (trained 2^22), the sums over the samples are FP32 MFMAs instead, on the same values in the same room of
+// the LDS (WIDE): with units 2^40 apart the smaller ones' gradients came out 0.
 //
 // The weight gradient's operands hold a neuron per lane and samples in registers: each term is turned by
 // an MFMA with a 0/1 selection matrix, as in the 16-bit kernels.  A workgroup of 8 waves takes rounds of
@@ -312,6 +319,42 @@ struct GradSplit {
     static constexpr int mH = 0, mD5 = 4, mD = 5, mCount = 9;
 };
 constexpr int kSplitGradWaves = 8;
+constexpr int kSpreadMax = 12, kSpreadSum = 24;
+
+// Whether the units of an FP32 model are too far apart for one scale per layer (*wide, see k_grad_split):
+// looked at when weights come in from outside.  (Training moves them by a learning rate per step: a spread
+// that matters, 2^17 and more, does not come about that way.)
+__global__ __launch_bounds__(512) void k_weight_spread(const float *__restrict__ w, uint32_t *wide) {
+    __shared__ uint32_t most[8][64];   // incoming weights of layers 1..4, outgoing ones (layers 2..5)
+    __shared__ uint32_t spread[8];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    most[wave][lane] = 0u;
+    __syncthreads();
+    for (int i = threadIdx.x; i < 64 * kFeat; i += 512)
+        atomicMax(&most[0][i / kFeat], __builtin_bit_cast(uint32_t, w[i]) & 0x7FFFFFFFu);
+    for (int i = threadIdx.x; i < (int)n_params(64) - 64 * kFeat; i += 512) {
+        const uint32_t m = __builtin_bit_cast(uint32_t, w[64 * kFeat + i]) & 0x7FFFFFFFu;
+        const int l = i >> 12;   // 0..2: W2..W4, 3: W5
+        if (l < 3) atomicMax(&most[1 + l][(i >> 6) & 63], m);
+        atomicMax(&most[4 + l][i & 63], m);
+    }
+    __syncthreads();
+    const uint32_t m = most[wave][lane];
+    const uint32_t hi = wave_max(m), lo = ~wave_max(m ? ~m : 0u);   // (units without weights do not count)
+    if (lane == 0) spread[wave] = hi ? (hi >> 23) - (lo >> 23) : 0u;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t most1 = 0u, in = 0u, out = 0u;
+        for (int k = 0; k < 8; ++k) most1 = max(most1, spread[k]);
+        for (int k = 0; k < 4; ++k) in += spread[k], out += spread[4 + k];
+        *wide = most1 > kSpreadMax || max(in, out) > kSpreadSum;
+    }
+}
+
+hipError_t launch_weight_spread(const float *w, uint32_t *wide, hipStream_t s) {
+    hipLaunchKernelGGL(k_weight_spread, dim3(1), dim3(512), 0, s, w, wide);
+    return hipGetLastError();
+}
 
 // The workgroup's exponent of a magnitude from its waves' (FP32 bits), within the range that scales can
 // follow.
@@ -342,6 +385,19 @@ __device__ __forceinline__ void add_split(f32x4 *acc, bool four, const A &a, con
     block(3);
 }
 
+// acc += a b over a round's samples in FP32: tiles [16 samples][4 samples][16 units].
+template <int N, typename A, typename B>
+__device__ __forceinline__ void add_wide(f32x4 *acc, bool four, const A &a, const B &b) {
+#pragma unroll 1
+    for (int sq = 0; sq < (four ? 8 : 4); ++sq)
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const f32x4 av = a(i, sq), bv = b(i, sq);
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) acc[i] = mfma4(av[kk], bv[kk], acc[i]);
+        }
+}
+
 template <bool PLAIN, bool DRAW>
 __global__ __launch_bounds__(kSplitGradWaves * 64) void k_grad_split(Points pts, Queries q, TrainDraw draw,
                                                                      const float *__restrict__ packed, TrainArgs args,
@@ -361,6 +417,7 @@ __global__ __launch_bounds__(kSplitGradWaves * 64) void k_grad_split(Points pts,
     uint32_t *sMax = (uint32_t *)(smem + G::kMax);
     const bool use_loss = PLAIN || DRAW || args.target != nullptr;
     const float kscale = use_loss ? 2.0f * args.loss_scale / (3.0f * (float)B) : args.loss_scale;
+    const uint32_t wide_model = *args.wide;
     const int round_samples = split_round(B);
     const bool four = round_samples == 128, active = four || wave < 4;
     const int64_t n_chunks = (B + round_samples - 1) / round_samples, nblk = gridDim.x;
@@ -393,6 +450,10 @@ __global__ __launch_bounds__(kSplitGradWaves * 64) void k_grad_split(Points pts,
         if constexpr (DRAW) draw_target(draw.lobes, draw.keys, drawn);
     }
     __syncthreads();
+    // the rounds and the partial gradient, the operands of the sums over the samples in two terms or FP32 (two
+    // loops, because the choice inside one costs 4 % of it; this way 1 to 3 %)
+    auto rounds = [&](auto wide) {
+    constexpr bool WIDE = decltype(wide)::value;
     // this wave's tiles: W2..W4 column tile wave % 4, row tiles 2 (wave / 4) and the next; W5 column
     // tile wave (waves 0..3); W1 row tile wave % 4, inputs wave / 4 + 2 j
     const int own_n = wave & 3, own_m = 2 * (wave >> 2);
@@ -406,6 +467,7 @@ __global__ __launch_bounds__(kSplitGradWaves * 64) void k_grad_split(Points pts,
     // exponents of the operands in the sums: W1, W2, W3, W4, W5
     int eg[5] = {-1000, -1000, -1000, -1000, -1000};
     auto rescale = [&](int k, int e, f32x4 *acc, int n) {
+        if (WIDE) e = 28;   // (the operands carry no scale)
         if (e == eg[k]) return;
         if (eg[k] != -1000)
 #pragma unroll
@@ -424,7 +486,17 @@ __global__ __launch_bounds__(kSplitGradWaves * 64) void k_grad_split(Points pts,
         d[0] = make_uint2(pack2<NIRC_FP16>(th[0], th[1]), pack2<NIRC_FP16>(th[2], th[3]));
         d[128] = make_uint2(pack2<NIRC_FP16>(tl[0], tl[1]), pack2<NIRC_FP16>(tl[2], tl[3]));
     };
+    // a lane's four units (4 g ..) of its sample, FP32
+    auto put_wide = [&](u32x4 *tile, float a, float b, float c, float d) {
+        float *o = (float *)(tile + wave * 64 + (col >> 2) * 16 + 4 * g) + (col & 3);
+        o[0] = a, o[4] = b, o[8] = c, o[12] = d;
+    };
     auto put_layer = [&](u32x4 *tiles, const f32x4 (&v)[MT], float scale) {
+        if constexpr (WIDE) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) put_wide(tiles + mt * G::kRows, v[mt][0], v[mt][1], v[mt][2], v[mt][3]);
+            return;
+        }
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
             const float x[8] = {v[2 * kb][0],     v[2 * kb][1],     v[2 * kb][2],     v[2 * kb][3],
@@ -502,7 +574,7 @@ __global__ __launch_bounds__(kSplitGradWaves * 64) void k_grad_split(Points pts,
 #pragma unroll
                 for (int i = 0; i < 3; ++i) x[7 + i] = ws[i];
             }
-            // ---------------- forward (the operations of grad_f32_block)
+            // ---------------- forward (layers 1..4 operation for operation as k_grad_f32)
             const float *sw = (const float *)smem;
             {
                 f32x4 a1[1][MT];
@@ -587,7 +659,10 @@ __global__ __launch_bounds__(kSplitGradWaves * 64) void k_grad_split(Points pts,
         take_max(eD5, G::mD5);
         take_max(eD[3], G::mD + 3);
         if (active) {
-            if (g == 0) {
+            if (WIDE && g == 0) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) ((float *)sD5)[128 * c + 16 * wave + col] = d5[c];
+            } else if (g == 0) {
                 const float f = pow2f(14 - eD5);
                 uint16_t *o = sD5 + ((wave >> 1) * 24 + (col >> 2) * 3) * 8 + 4 * (wave & 1) + (col & 3);
 #pragma unroll
@@ -604,7 +679,15 @@ __global__ __launch_bounds__(kSplitGradWaves * 64) void k_grad_split(Points pts,
         // ---------------- W5
         if (wave < 4) {
             rescale(4, eD5 + eH[3], &g5, 1);
-            add_split<1>(&g5, four,
+            if constexpr (WIDE)
+                add_wide<1>(&g5, four,
+                            [&](int, int sq) {
+                                const f32x4 v = *(const f32x4 *)((const float *)sD5 + 128 * (col < 3 ? col : 0) + 16 * sq + 4 * g);
+                                return col < 3 ? v : f32x4{0.f, 0.f, 0.f, 0.f};
+                            },
+                            [&](int, int sq) { return ((const f32x4 *)sAct)[own_n * G::kRows + sq * 64 + lane]; });
+            else
+                add_split<1>(&g5, four,
                          [&](int, int k, int t) {
                              const u32x4 v = *(const u32x4 *)(sD5 + ((2 * k + t) * 12 + g * 3 + (col < 3 ? col : 0)) * 8);
                              return col < 3 ? v : u32x4{0u, 0u, 0u, 0u};
@@ -629,6 +712,11 @@ __global__ __launch_bounds__(kSplitGradWaves * 64) void k_grad_split(Points pts,
                         float e[8];
                         enc_pair2(x[i], 2 * g, e[0], e[1], e[2], e[3]);
                         enc_pair2(x[i + 1], 2 * g, e[4], e[5], e[6], e[7]);
+                        if constexpr (WIDE) {
+                            put_wide(sE + i * G::kRows, e[0], e[1], e[2], e[3]);
+                            put_wide(sE + (i + 1) * G::kRows, e[4], e[5], e[6], e[7]);
+                            continue;
+                        }
                         u32x4 eh, el;
                         split8(e, kSplitFeat, eh, el);
                         put(sE + i * G::kRows, eh, el, sel[0]);
@@ -656,7 +744,12 @@ __global__ __launch_bounds__(kSplitGradWaves * 64) void k_grad_split(Points pts,
                     }
                 }
                 rescale(k, eD[k] + eH[k - 1], gh[k - 1], 2);
-                add_split<2>(gh[k - 1], four,
+                if constexpr (WIDE)
+                    add_wide<2>(gh[k - 1], four,
+                                [&](int m, int sq) { return ((const f32x4 *)sDel)[(own_m + m) * G::kRows + sq * 64 + lane]; },
+                                [&](int, int sq) { return ((const f32x4 *)sAct)[own_n * G::kRows + sq * 64 + lane]; });
+                else
+                    add_split<2>(gh[k - 1], four,
                              [&](int m, int kb, int t) { return sDel[(own_m + m) * G::kRows + kb * 128 + t * 64 + lane]; },
                              [&](int, int kb, int t) { return sAct[own_n * G::kRows + kb * 128 + t * 64 + lane]; });
                 if (active) {
@@ -669,7 +762,14 @@ __global__ __launch_bounds__(kSplitGradWaves * 64) void k_grad_split(Points pts,
                 __syncthreads();
             } else {
                 rescale(0, eD[0], g1, 5);
-                add_split<5>(g1, four,
+                if constexpr (WIDE)
+                    add_wide<5>(g1, four,
+                                [&](int, int sq) { return ((const f32x4 *)sDel)[own_n * G::kRows + sq * 64 + lane]; },
+                                [&](int j, int sq) {
+                                    return ((const f32x4 *)sE)[((wave >> 2) + 2 * j) * G::kRows + sq * 64 + lane];
+                                });
+                else
+                    add_split<5>(g1, four,
                              [&](int, int kb, int t) { return sDel[own_n * G::kRows + kb * 128 + t * 64 + lane]; },
                              [&](int j, int kb, int t) {
                                  return sE[((wave >> 2) + 2 * j) * G::kRows + kb * 128 + t * 64 + lane];
@@ -709,6 +809,11 @@ __global__ __launch_bounds__(kSplitGradWaves * 64) void k_grad_split(Points pts,
         for (int w = 0; w < kSplitGradWaves; ++w) t += sLoss[w];
         loss_partials[blockIdx.x] = t;
     }
+    };
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(wide_model) == 0u, 1))
+        rounds(std::false_type{});
+    else
+        rounds(std::true_type{});
 }
 
 // ------------------------------------------------------------------------------------------
