@@ -187,7 +187,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_infer_h16(Points pts, Queries q,
 // in global memory (widths above 64).
 // N16: n_cache is a multiple of 16 (the per-point sums take only the first of the three paths
 // below; compiling the others out measured 2.4 % shorter estimates at N = 16).
-template <int W, int PREC, int T, bool OCC, int ENC = 0, bool HL = false, bool N16 = false>
+// FEW: see tlmc_sums.
+template <int W, int PREC, int T, bool OCC, int ENC = 0, bool HL = false, bool N16 = false, bool FEW = true>
 __device__ __forceinline__ void tlmc_tiles_h16(int T0, int s0, int n_cache, DivN dn, const GroupSlab &gs,
                                                const uint16_t *sD, const uint16_t *sH, const uint16_t *sOS,
                                                const u32x4 (&dfrag)[W / 8], int lane, int g, int col, float &rdx,
@@ -256,7 +257,7 @@ __device__ __forceinline__ void tlmc_tiles_h16(int T0, int s0, int n_cache, DivN
     }
     const f32x4 z = output16_packed<W, PREC, T>(hb, aout);
 
-    tlmc_sums<T, OCC, N16, false>(z, T0, s0, n_cache, dn, gs, lane, g, col, pts, p0, mode, lobes);
+    tlmc_sums<T, OCC, N16, false, FEW>(z, T0, s0, n_cache, dn, gs, lane, g, col, pts, p0, mode, lobes);
 }
 
 // One point group (16 points from p0) of the fused estimator: surface projection once per point
@@ -265,7 +266,7 @@ __device__ __forceinline__ void tlmc_tiles_h16(int T0, int s0, int n_cache, DivN
 // surface columns are read from global memory (gS).
 // ENC 1: the hash-grid model (surface part from the grid `slv`/`table` and phi, direction part
 // from spherical harmonics).
-template <int W, int PREC, int TP, bool OCC, int ENC = 0, bool HL = false, bool N16 = false>
+template <int W, int PREC, int TP, bool OCC, int ENC = 0, bool HL = false, bool N16 = false, bool FEW = true>
 __device__ __forceinline__ void tlmc_group_h16(const Points &pts, int64_t p0, int n_cache, DivN dn, uint32_t key0,
                                                uint32_t key1, uint32_t frame, int mode, const float *rrad,
                                                float *out_tl,
@@ -319,11 +320,11 @@ __device__ __forceinline__ void tlmc_group_h16(const Points &pts, int64_t p0, in
         int t = tb;
 #pragma unroll 1
         for (; t + TP <= tend; t += TP)
-            tlmc_tiles_h16<W, PREC, TP, OCC, ENC, HL, N16>(t, t - tb, n_cache, dn, gs, sD, sH, sOS, dfrag, lane, g, col, rdx, rdy,
+            tlmc_tiles_h16<W, PREC, TP, OCC, ENC, HL, N16, FEW>(t, t - tb, n_cache, dn, gs, sD, sH, sOS, dfrag, lane, g, col, rdx, rdy,
                                                  rdz, pts, p0, mode, lobes);
 #pragma unroll 1
         for (; t < tend; ++t)
-            tlmc_tiles_h16<W, PREC, 1, OCC, ENC, HL, N16>(t, t - tb, n_cache, dn, gs, sD, sH, sOS, dfrag, lane, g, col, rdx, rdy,
+            tlmc_tiles_h16<W, PREC, 1, OCC, ENC, HL, N16, FEW>(t, t - tb, n_cache, dn, gs, sD, sH, sOS, dfrag, lane, g, col, rdx, rdy,
                                                 rdz, pts, p0, mode, lobes);
         tb = tend;
     }
@@ -406,7 +407,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_tlmc_multi_h16(const BatchDesc *
         }
         const int64_t grp = (int64_t)(chunk - s_req.chunk_begin) * WAVES + wave;
         if (grp < (s_req.pts.count + 15) >> 4)
-            tlmc_group_h16<W, PREC, 4, OCC>(s_req.pts, grp << 4, s_req.n_cache, s_req.dn, s_req.key0, s_req.key1, s_req.frame,
+            tlmc_group_h16<W, PREC, 4, OCC, 0, false, false, false>(s_req.pts, grp << 4, s_req.n_cache, s_req.dn, s_req.key0, s_req.key1, s_req.frame,
                                     __builtin_amdgcn_readfirstlane(s_req.mode), uniform_ptr(s_req.rrad), s_req.out_tl,
                                     s_req.out_c, s_req.out_r, s_req.lobes,
                                     (const uint16_t *)s_req.packed + L.offset(SEC_S), sD, sH, sOS, gs, lane, g, col);

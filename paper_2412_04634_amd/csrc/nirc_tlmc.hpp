@@ -43,7 +43,11 @@ __device__ inline GroupSlab group_slab(float *base, int W) {
 // output16_packed leaves it.  A lane exponentiates its four queries of one tile and channel, adds
 // cache tiles to the per-point sums and leaves the residual tile's predictions in the slab.
 // LIBEXP: the library's exponential for sigmoid outputs (the FP32 models).
-template <int T, bool OCC, bool N16, bool LIBEXP>
+// FEW: the sums of N = 1, 2, 4, 8 are laid out before the general ones.  That suits the 16-bit estimate of one
+// request, whose passes are short (BF16, 230,399 points: N = 2 65.4 us behind them, 63.6 before; N = 12 131.8 and
+// 132.2).  FP32 and the batched lists want the other order (FP32, N = 31: 798 us and 820; five streams of 83,566
+// points, N = 12, with their training: 291 and 298).
+template <int T, bool OCC, bool N16, bool LIBEXP, bool FEW = false>
 __device__ __forceinline__ void tlmc_sums(const f32x4 &z, int T0, int s0, int n_cache, DivN dn, const GroupSlab &gs,
                                           int lane, int g, int col, const Points &pts, int64_t p0, int mode,
                                           const nirc_lobes &lobes) {
@@ -100,10 +104,8 @@ __device__ __forceinline__ void tlmc_sums(const f32x4 &z, int T0, int s0, int n_
         }
         if (valid && last && g == 0 && Tt < n_cache) gs.psum[div_n((uint32_t)(16 * Tt), dn) * 4 + c] += sum;
     } else if constexpr (!N16) {
-        // In 16 bits, where a pass is short, the path of N = 1, 2, 4, 8 is laid out first (BF16, 230,399 points: N = 2
-        // 65.1 us behind the other, 63.1 before it; N = 12 130.9 and 131.8; FP32, N = 31: 798 and 820)
-        const bool inside = n_cache <= 8 && (n_cache & (n_cache - 1)) == 0;
-        if (LIBEXP ? inside : __builtin_expect(inside, 1)) {
+        if (FEW ? __builtin_expect(n_cache <= 8 && (n_cache & (n_cache - 1)) == 0, 1)
+                : n_cache <= 8 && (16 % n_cache) == 0) {
             // every point of a cache tile lies inside the tile: plain stores of complete sums
             if (valid && Tt < n_cache) {
                 const int pbase = (int)div_n((uint32_t)(16 * Tt + q0), dn);   // point of this lane's first query
