@@ -49,7 +49,17 @@ typedef int32_t nirc_status;
 #define NIRC_ERR_WORKSPACE (-3)   /* state or workspace buffer too small */
 #define NIRC_ERR_HIP (-5)
 
-/* Arithmetic of the MLP layer products (FP32 accumulation in every case). */
+/* Arithmetic of the MLP layer products (FP32 accumulation in every case).
+ * NIRC_FP32 at width 64 with the frequency input: nirc_infer, tlmc_estimate and the batched lists hold
+ * every operand of a layer product as two FP16 terms (22 to 24 significant bits, the product of the
+ * second terms left out), scaled so that nothing overflows.  The error that FP16's range adds to a
+ * prediction is bounded from the weights, and a model for which the bound exceeds 2^-17 (relative; the actual
+ * error is far below) runs in FP32 throughout: one whose units differ widely, whose sums cancel, or
+ * that holds a value that is not finite.  nirc_loss_grad and the training steps run forward and
+ * backward in FP32 and take two-term operands in the weight gradients' sums over the samples: 22 bits of a
+ * value within 2^-16 of the largest of its layer in a workgroup's samples, and 2^-39 of that largest below it; FP32
+ * operands where the model's units are far apart when its weights come in (by more than 2^12 in a layer or
+ * 2^24 over all).  nirc_backward is FP32 throughout, as are width 128 and the hash-grid model. */
 #define NIRC_FP32 0
 #define NIRC_BF16 1
 #define NIRC_FP16 2
@@ -150,9 +160,9 @@ int64_t nirc_n_params(int32_t width);
 size_t nirc_state_bytes(const nirc_config *cfg /* host */);
 
 /* Bytes of workspace needed by training calls on batches of up to max_batch queries
- * (per-workgroup gradient partials, reduced gradient, loss, and the sample buffers of
- * nirc_train_frame for the models whose samples are not drawn in the gradient kernel: width 128
- * and the residual-variance loss).  Inference needs none. */
+ * (per-workgroup gradient partials, reduced gradient, loss, and 112 bytes per query for the samples
+ * of nirc_train_frame: nirc_train_frame and nirc_train_list_build ask for them of every model,
+ * width 128 and the residual-variance loss use them).  Inference needs none. */
 size_t nirc_workspace_bytes(const nirc_config *cfg /* host */, int64_t max_batch);
 
 /* Create a model over caller-owned device buffers.  `state` must hold nirc_state_bytes and be
@@ -201,7 +211,8 @@ nirc_status nirc_encode(nirc_points points, nirc_queries queries, float *feature
 
 /* Cache predictions n(x, w) for explicit queries (eq. 11's network term): rgb is
  * [queries.count][3] FP32.  Every query is evaluated independently (no sharing of the surface
- * encoding between queries of one point). */
+ * encoding between queries of one point): its prediction does not depend on the others or on how
+ * many there are. */
 nirc_status nirc_infer(const nirc_model *model, nirc_points points, nirc_queries queries,
                        float *rgb, void *stream);
 
@@ -364,8 +375,7 @@ nirc_status tlmc_train_batch(nirc_points points, const nirc_lobes *field /* host
  *   loss = (1/(3B)) sum_{b,c} (y - t)^2 / (sg(y)^2 + loss_eps)
  * w.r.t. the weights, written to grad [n_params] (canonical FP32); loss (device float, may be
  * NULL) receives the loss.  Needs the workspace.  Deterministic (fixed reduction order).
- * FP32 models run FP32 MFMA (width 64: the weight gradients' sums over the samples on two-term FP16
- * operands with FP32 accumulation, errors at FP32's own level); BF16 / FP16 models run the forward and backward with 16-bit
+ * FP32 models: see NIRC_FP32; BF16 / FP16 models run the forward and backward with 16-bit
  * operands and FP32 accumulation, with the output gradient scaled by loss_scale * B before the
  * backward and the gradient unscaled after the reduction.  Width 128 sweeps the batch several
  * times (each sweep owns a disjoint part of the gradient). */

@@ -64,7 +64,9 @@ __device__ __forceinline__ void draw_target(const nirc_lobes &lobes, const DrawK
 }
 
 // Selection operands (B: lane (g, c) holds K positions 8 g + j of column c): column c takes K position
-// 8 (c / 4) + c % 4 + 4 half, times `odd` where c is odd.
+// 8 (c / 4) + c % 4 + 4 half, times `odd` where c is odd.  (0 x inf and 0 x NaN are NaN: a value that is not
+// finite spoils its sample's other positions of the operand too, so that such a sample leaves more entries of the
+// gradient not finite than it would by itself.  It leaves some in any case, and the step is skipped.)
 template <int PREC>
 __device__ __forceinline__ u32x4 select_operand(int half, float odd, int g, int col) {
     u32x4 v = u32x4{0u, 0u, 0u, 0u};

@@ -176,9 +176,12 @@ struct HashCell {
 
 // Cell of x (clamped to the unit cube) at resolution N: lower corner and fractions.  EXACT: the
 // fraction takes the unrounded product x N (a fused multiply-add); otherwise the product is rounded
-// first, which moves the fraction by up to 2^-24 N.  Written out, because a compiler that contracts
-// one kernel's expression and not another's would give the lookup and the scatter of one step
-// different weights.
+// first, which moves the fraction by up to 2^-24 N.  Written out, so that no compiler contracts one kernel's
+// expression and not another's.  Everything takes the exact fraction but one: the lookup of a training step of
+// 16-bit models, whose blended values are then rounded to 16 bits.  That step's entry gradients take the
+// exact weights, and so differ from the derivative of its own forward pass by up to 2^-24 N of a weight (8e-5
+// on the default grid's finest level, beside the 2^-9 or 2^-12 of its operands).  It has always been so; a
+// change would move the 16-bit roundings, and with them every later weight.
 template <bool EXACT = true>
 __host__ __device__ __forceinline__ HashCell hash_cell(float x0, float x1, float x2, int N) {
 #pragma clang fp contract(off)

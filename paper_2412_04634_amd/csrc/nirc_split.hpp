@@ -21,12 +21,12 @@
 // which it exceeds kSplitFloor takes the FP32 MFMA chain instead: units of a layer far apart, sums that
 // cancel, large units that are hardly ever on, layers that have grown in long training; also one with a
 // weight that is not finite.  The bound takes all roundings the same way and every unit at its worst; where it
-// is 2^-17, independent roundings come to 2^-25, less than FP32's own.  Restated in 64 bits (bound; error of the
-// predictions, plain FP32's): Glorot weights 2^-23.2, 0.6e-7, 1.0e-7; after 3,000, 30,000 and 150,000 training
-// steps at a learning rate of 1e-3 2^-23.0, 2^-21.1 and 2^-19.5, 2.0e-7, 1.2e-7 and 1.1e-7 against 3.3e-7, 2.7e-7 and
-// 2.3e-7; at 1e-2 2^-22.2, 2^-15.8 and 2^-11.4, the last two on the FP32 chain.  (Scales from products of the
-// layers' largest row sums, without the bound on the error, left models of the last kind 10 times plain
-// FP32's error, and one with a unit 2^9 larger than the others in each of two layers 3,000 times.)
+// is 2^-17, independent roundings come to 2^-25, less than FP32's own.  Predictions of 20,000 queries against 64
+// bits (bound; rel-L2 here, on the FP32 chain): Glorot weights 2^-22.5, 1.04e-7, 1.29e-7; trained for 30,000 steps
+// at a learning rate of 1e-3 2^-20.7, 2.08e-7, 2.44e-7; for 150,000 2^-18.5, 1.64e-7, 2.08e-7; for 3,000 at 1e-2
+// 2^-21.9, 1.23e-7, 1.20e-7; for 150,000 2^-10.3: FP32 chain, 1.23e-7.  (Scales from products of the layers' largest
+// row sums, without the bound on the error, gave 6.45e-7 for the last, and 2.8e-4 for a model with one unit 2^9
+// larger than the others in each of two layers.)
 // All this is found once per workgroup, from the packed FP32 weights while they are staged.
 #pragma once
 
