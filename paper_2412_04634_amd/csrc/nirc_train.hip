@@ -328,16 +328,30 @@ __global__ __launch_bounds__(512) void k_weight_spread(const float *__restrict__
     __shared__ uint32_t most[8][64];   // incoming weights of layers 1..4, outgoing ones (layers 2..5)
     __shared__ uint32_t spread[8];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    most[wave][lane] = 0u;
+    if (wave >= 4) most[wave][lane] = 0u;
     __syncthreads();
-    for (int i = threadIdx.x; i < 64 * kFeat; i += 512)
-        atomicMax(&most[0][i / kFeat], __builtin_bit_cast(uint32_t, w[i]) & 0x7FFFFFFFu);
-    for (int i = threadIdx.x; i < (int)n_params(64) - 64 * kFeat; i += 512) {
-        const uint32_t m = __builtin_bit_cast(uint32_t, w[64 * kFeat + i]) & 0x7FFFFFFFu;
-        const int l = i >> 12;   // 0..2: W2..W4, 3: W5
-        if (l < 3) atomicMax(&most[1 + l][(i >> 6) & 63], m);
-        atomicMax(&most[4 + l][i & 63], m);
+    auto mag = [&](int64_t i) { return __builtin_bit_cast(uint32_t, w[i]) & 0x7FFFFFFFu; };
+    // a wave takes every eighth row of each matrix; lane: column
+    uint32_t col[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const int r = wave + 8 * k;
+        const int64_t o = (int64_t)r * kFeat + lane;
+        uint32_t in[4] = {max(max(mag(o), mag(o + 64)), lane < kFeat - 128 ? mag(o + 128) : 0u)};
+#pragma unroll
+        for (int l = 0; l < 3; ++l) {
+            in[1 + l] = mag(w_offset(64, 1 + l) + r * 64 + lane);
+            col[l] = max(col[l], in[1 + l]);
+        }
+#pragma unroll
+        for (int l = 0; l < 4; ++l) {
+            in[l] = wave_max(in[l]);
+            if (lane == 0) most[l][r] = in[l];
+        }
     }
+    if (wave < 3) col[3] = mag(w_offset(64, 4) + wave * 64 + lane);
+#pragma unroll
+    for (int l = 0; l < 4; ++l) atomicMax(&most[4 + l][lane], col[l]);
     __syncthreads();
     const uint32_t m = most[wave][lane];
     const uint32_t hi = wave_max(m), lo = ~wave_max(m ? ~m : 0u);   // (units without weights do not count)
