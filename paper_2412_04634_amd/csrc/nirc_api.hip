@@ -34,7 +34,7 @@ struct StateLayout {
         step = o; o += align_up(sizeof(int64_t));
         flags = o; o += align_up(sizeof(uint32_t));
         bad = o; o += align_up(sizeof(uint32_t));
-        scale = o; o += align_up(4 * sizeof(uint32_t));   // loss scale, good steps, workgroup count, wide
+        scale = o; o += align_up(5 * sizeof(uint32_t));   // loss scale, good steps, workgroup count, wide [2]
         total = o;
     }
 };
@@ -104,7 +104,8 @@ struct nirc_model {
     float *scale;          // the current loss scale (dynamic for FP16 models)
     uint32_t *good;        // finite steps since the scale last changed
     uint32_t *done;        // finished workgroups of the running Adam launch (zero between steps)
-    uint32_t *wide;        // FP32, width 64: the loss gradient's sums take FP32 operands (units far apart)
+    uint32_t *wide;        // FP32, width 64: the loss gradient's sums take FP32 operands (units far apart);
+                           // [1]: the mark that this has been looked at
     char *ws;
     size_t ws_bytes;
     // FP16 models scale their loss dynamically; BF16 and FP32 keep cfg.loss_scale
@@ -202,12 +203,14 @@ nirc_status nirc_destroy(nirc_model *model) {
     return NIRC_OK;
 }
 
-// What follows from FP32 weights that came in from outside: the packed copies, and whether the units are far apart.
-static hipError_t derive_copies(nirc_model *model, hipStream_t s) {
+// What follows from FP32 weights that came in from outside: the packed copies, and whether the units are far apart
+// (a saved state says so itself: the resumed model continues as the saved one).
+static hipError_t derive_copies(nirc_model *model, bool saved_state, hipStream_t s) {
     hipError_t e = launch_pack(model->packed, model->master, model->W, s);
     if (e == hipSuccess && model->packed16)
         e = launch_pack16(model->packed16, model->master, model->W, model->cfg.precision, s);
-    if (e == hipSuccess && !model->packed16 && model->W == 64) e = launch_weight_spread(model->master, model->wide, s);
+    if (e == hipSuccess && !model->packed16 && model->W == 64)
+        e = launch_weight_spread(model->master, model->wide, saved_state, s);
     return e;
 }
 
@@ -221,7 +224,7 @@ nirc_status nirc_set_weights(nirc_model *model, const float *w, void *stream) {
     // the loss scale starts again from the configured one
     if (e == hipSuccess) e = launch_fill_u32((uint32_t *)model->scale, 1, __builtin_bit_cast(uint32_t, model->cfg.loss_scale), s);
     if (e == hipSuccess) e = launch_fill_u32(model->good, 2, 0u, s);   // good-step and workgroup counts
-    if (e == hipSuccess) e = derive_copies(model, s);
+    if (e == hipSuccess) e = derive_copies(model, false, s);
     return hip_status(e);
 }
 
@@ -245,7 +248,7 @@ nirc_status nirc_set_state(nirc_model *model, const void *blob, size_t blob_byte
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = launch_copy_f32(model->master, (const float *)blob, (int64_t)(bytes / 4), s);
     // the packed copies follow the restored FP32 weights whatever precision wrote the blob
-    if (e == hipSuccess) e = derive_copies(model, s);
+    if (e == hipSuccess) e = derive_copies(model, true, s);
     return hip_status(e);
 }
 

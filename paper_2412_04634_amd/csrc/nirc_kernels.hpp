@@ -575,7 +575,7 @@ __device__ inline void commit_step(int64_t *step, uint32_t *flags, uint32_t *bad
 // summed in a fixed order; part holds kFrBlocks x 3 floats.
 constexpr int kFrBlocks = 256;
 hipError_t launch_residual_mean(const float *y, const float *t, int64_t B, float *part, float *fr, hipStream_t s);
-hipError_t launch_weight_spread(const float *w, uint32_t *wide, hipStream_t s);
+hipError_t launch_weight_spread(const float *w, uint32_t *wide /* [2] */, bool saved_state, hipStream_t s);
 int train_blocks(int64_t batch);     // partial slabs an FP32 model's workspace holds for a batch
 int grad_blocks32(int W, int64_t batch, bool loss);   // ... that it launches (slabs written); loss: targets given
 int train_blocks16(int64_t batch);   // partial slabs a 16-bit model's workspace holds for a batch

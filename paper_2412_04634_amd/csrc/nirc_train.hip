@@ -320,14 +320,17 @@ struct GradSplit {
 };
 constexpr int kSplitGradWaves = 8;
 constexpr int kSpreadMax = 12, kSpreadSum = 24;
+constexpr uint32_t kSpreadMark = 0x53707264u;   // wide[1] once a model's weights have been looked at
 
 // Whether the units of an FP32 model are too far apart for one scale per layer (*wide, see k_grad_split):
 // looked at when weights come in from outside.  (Training moves them by a learning rate per step: a spread
-// that matters, 2^17 and more, does not come about that way.)
-__global__ __launch_bounds__(512) void k_weight_spread(const float *__restrict__ w, uint32_t *wide) {
+// that matters, 2^17 and more, does not come about that way.)  A saved state that holds the answer keeps it, so
+// that the resumed model sums as the saved one would have; one written without the mark is looked at.
+__global__ __launch_bounds__(512) void k_weight_spread(const float *__restrict__ w, uint32_t *wide, bool saved_state) {
     __shared__ uint32_t most[8][64];   // incoming weights of layers 1..4, outgoing ones (layers 2..5)
     __shared__ uint32_t spread[8];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (saved_state && wide[1] == kSpreadMark) return;
     if (wave >= 4) most[wave][lane] = 0u;
     __syncthreads();
     auto mag = [&](int64_t i) { return __builtin_bit_cast(uint32_t, w[i]) & 0x7FFFFFFFu; };
@@ -361,12 +364,13 @@ __global__ __launch_bounds__(512) void k_weight_spread(const float *__restrict__
         uint32_t most1 = 0u, in = 0u, out = 0u;
         for (int k = 0; k < 8; ++k) most1 = max(most1, spread[k]);
         for (int k = 0; k < 4; ++k) in += spread[k], out += spread[4 + k];
-        *wide = most1 > kSpreadMax || max(in, out) > kSpreadSum;
+        wide[0] = most1 > kSpreadMax || max(in, out) > kSpreadSum;
+        wide[1] = kSpreadMark;
     }
 }
 
-hipError_t launch_weight_spread(const float *w, uint32_t *wide, hipStream_t s) {
-    hipLaunchKernelGGL(k_weight_spread, dim3(1), dim3(512), 0, s, w, wide);
+hipError_t launch_weight_spread(const float *w, uint32_t *wide, bool saved_state, hipStream_t s) {
+    hipLaunchKernelGGL(k_weight_spread, dim3(1), dim3(512), 0, s, w, wide, saved_state);
     return hipGetLastError();
 }
 

@@ -109,3 +109,30 @@ def test_drawn_step(nirc, B):
     q, t = nirc.tlmc_train_batch(dp, lob, B, 5, 2, 0)
     nirc.nirc_train_step(b, dp, q, t)
     assert torch.equal(a.get_weights(), b.get_weights()) and a.read_flags() == 0
+
+
+def test_resumed_training_sums_as_the_saved(nirc):
+    """Steps that take the weights over the line between the operands: a model resumed from the saved state
+    continues bit for bit, where one made from the same weights takes the other operands."""
+    pts, w = wl.make_points(SEED, P), wl.make_weights(SEED, W)
+    m = npref.split_weights(w, W)
+    m[2][:] = np.clip(m[2], -0.1249, 0.1249)   # exponents of the rows' largest: -4; after a step of 0.01 some -3
+    m[2][7] = -1.5 * 2.0 ** -16                # never on, so it stays, 2^12 from the others and then 2^13
+    w = np.concatenate([a.ravel() for a in m]).astype(np.float32)
+    sm = Samples(pts, wl.make_lobes(SEED).packed(), 3000, 92, 0, 0)
+    dp, q, t = nirc.Points.from_workload(pts), sm.queries(nirc), sm.target()
+    make = lambda w: nirc.Model(w, nirc.make_config(lr=1e-2), max_batch=3000)
+    saved, resumed = make(w), make(wl.make_weights(SEED + 1, W))
+    for _ in range(3):
+        nirc.nirc_train_step(saved, dp, q, t)
+    blob = saved.get_state()
+    resumed.set_state(blob)
+    fresh = make(host(saved.get_weights()))
+    grads = [nirc.nirc_loss_grad(k, dp, q, t)[1].clone() for k in (saved, resumed, fresh)]
+    assert torch.equal(resumed.get_state(), blob)
+    assert torch.equal(grads[1], grads[0])
+    assert not torch.equal(grads[2], grads[0])
+    assert rel_l2(host(grads[2]), host(grads[0])) <= 1e-5
+    for k in (saved, resumed):
+        nirc.nirc_train_step(k, dp, q, t)
+    assert torch.equal(resumed.get_state(), saved.get_state())
