@@ -43,7 +43,7 @@ def measured_peak(probe: dict, name: str, W: int) -> float:
 # HBM bytes per launch of k_tlmc_split in the frame configuration (1080p, N = 16, F_tl + F_c + F_r
 # written), from FETCH_SIZE x 2.0 + WRITE_SIZE (factors from a plain 512 MiB copy); recorded in
 # profiles/k_tlmc_hbm_counters_1080p_n16.md and to be measured again whenever the kernel changes.
-TRAFFIC_K_TLMC_SPLIT = 135595648
+TRAFFIC_K_TLMC_SPLIT = 136281216
 
 
 def algorithmic_flops_estimate(P: int, N: int, W: int) -> float:
@@ -914,7 +914,8 @@ def main():
         "config": {"workload": f"dynamic lobe scene, {P} shading points (1920x1080), N={N} cache + 1 residual, "
                                f"MLP 4x{W} ReLU, {S} Adam steps of {B} samples per frame",
                    "points": P, "n_cache": N, "width": W, "train_batch": B, "train_steps_per_frame": S,
-                   "precision": "fp32"},
+                   "precision": "fp32",
+                   "products": "FP32 operands as two FP16 terms, FP32 accumulation" if W == 64 else "FP32"},
         "roofline": {"bound": "mfma", "kernel": "k_tlmc_split", "achieved": achieved / 1e12,
                      "peak": estimate_peak(0, W) / 1e12, "unit": "TFLOP/s", "frac": achieved / estimate_peak(0, W),
                      "traffic": TRAFFIC_K_TLMC_SPLIT if cfgw is wl.WORKLOADS["1080p_n16"] else None,
